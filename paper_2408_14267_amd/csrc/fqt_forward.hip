@@ -215,31 +215,34 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t s, uint32_t n) {
   return ((i / FWD_RUN) * XCDS + x) * FWD_RUN + i % FWD_RUN;
 }
 
-// Stores of one 32 (channels d0 ..) x 32 (rows r0 ..) tile of integers from its LDS copy
-// [channel][row] (pitch ST_PITCH) when P % 4 == 0: pieces of 4 consecutive pixels of one channel, consecutive
-// lanes on consecutive memory (along the pixels of a map, then, for maps below 32 pixels,
-// along the channels of the sample).
-constexpr int ST_PITCH = 36;       // ints; 16-byte pieces of different channels on different banks
+// Stores of one tile of 32 channels from d0 x 32 RT rows from r0 of integers from its LDS copy
+// [channel][row] (pitch st_pitch(RT)) when P % 4 == 0: pieces of 4 consecutive pixels of one
+// channel, consecutive lanes on consecutive memory (along the pixels of a map, then, for maps
+// below 32 pixels, along the channels of the sample).  64 rows at once (RT = 2) write whole
+// 128-byte lines also in bfloat16.
+constexpr int st_pitch(int rt) { return 32 * rt + 4; }   // ints; channels on different banks
+template <int RT>
 __device__ __forceinline__ void store_tile(const FwdArgs &a, const int32_t *st, uint32_t d0,
                                            uint32_t r0, int lane) {
-  const uint32_t qs = a.P >= 32 ? 8 : (a.P & 7) == 0 && a.P <= 16 ? a.P / 4 : 1;
-  const uint32_t qsh = qs == 8 ? 3 : qs == 4 ? 2 : qs == 2 ? 1 : 0;
-  float gm[4];
-  uint32_t dd[4], pq[4];
+  constexpr int PIECES = 4 * RT;
+  const uint32_t qsh = a.P >= 64 && RT == 2 ? 4 : a.P >= 32 ? 3 : a.P == 16 ? 2 : a.P == 8 ? 1 : 0;
+  const uint32_t qs = 1u << qsh;
+  float gm[PIECES];
+  uint32_t dd[PIECES], pq[PIECES];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < PIECES; ++k) {
     const uint32_t e = uint32_t(lane) + 64 * k;
     dd[k] = (e >> qsh) & 31;
     pq[k] = (e & (qs - 1)) + qs * (e >> (qsh + 5));
     gm[k] = d0 + dd[k] < a.D ? a.gamma[d0 + dd[k]] : 0.0f;
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < PIECES; ++k) {
     const uint32_t d = d0 + dd[k], r = r0 + 4 * pq[k];
     if (d >= a.D || r >= a.R) continue;
     const uint32_t n = fdiv(r, a.divP), p = r - n * a.P;
     const size_t o = (size_t(n) * a.D + d) * a.P + p;
-    const int4 I = *reinterpret_cast<const int4 *>(st + dd[k] * ST_PITCH + 4 * pq[k]);
+    const int4 I = *reinterpret_cast<const int4 *>(st + dd[k] * st_pitch(RT) + 4 * pq[k]);
     const float y0 = __fmul_rn(gm[k], float(I.x)), y1 = __fmul_rn(gm[k], float(I.y));
     const float y2 = __fmul_rn(gm[k], float(I.z)), y3 = __fmul_rn(gm[k], float(I.w));
     if (a.y_t == FQT_BF16) {
@@ -271,10 +274,11 @@ __device__ __forceinline__ void store_elem(const FwdArgs &a, uint32_t d, uint32_
 // products and its X fragments CT.  NB steps' loads issue together.
 // VEC: Y pieces of 4 pixels (P % 4 == 0, aligned Y and I_out).  BIG: 64-bit addresses.
 template <int RT, int CT, int KS, int NB, bool LIN, bool BIG>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RT * CT == 1 ? 4 : KS == 1 ? 3 : 2)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RT * CT == 1 || KS == 1 ? 4 : 2)))
 void k_fwd(FwdArgs a, uint32_t vec) {
   constexpr int TPB = WAVES / KS, TILES = RT * CT;
-  constexpr int RED = KS > 1 ? KS * TILES * 1024 : 0, STG = WAVES * 32 * ST_PITCH;
+  constexpr int RED = KS > 1 ? KS * TILES * 1024 : 0, SRT = KS > 1 ? 1 : RT,
+                STG = WAVES * 32 * st_pitch(SRT);
   __shared__ __align__(16) int32_t lds[RED > STG ? RED : STG];
   const int lane = threadIdx.x & 63, i = lane & 31, g = lane >> 5;
   const uint32_t wave = wave_id(), tile = wave / KS, part = wave - tile * KS;
@@ -387,11 +391,11 @@ void k_fwd(FwdArgs a, uint32_t vec) {
       const uint32_t rr = r0 + 32 * rt, dd = d0 + 32 * ct;
       if (!LIN && vec) {
         __syncthreads();
-        int32_t *st = lds + wave * (32 * ST_PITCH);
+        int32_t *st = lds + wave * (32 * st_pitch(1));
 #pragma unroll
-        for (int v = 0; v < 16; ++v) st[acc_row(v, g) * ST_PITCH + i] = I[v];
+        for (int v = 0; v < 16; ++v) st[acc_row(v, g) * st_pitch(1) + i] = I[v];
         __builtin_amdgcn_wave_barrier();    // LDS operations of a wave run in order
-        store_tile(a, st, dd, rr, lane);
+        store_tile<1>(a, st, dd, rr, lane);
         return;
       }
 #pragma unroll
@@ -403,27 +407,30 @@ void k_fwd(FwdArgs a, uint32_t vec) {
       return;
     }
   } else {
-    int32_t *st = lds + wave * (32 * ST_PITCH);
+    int32_t *st = lds + wave * (32 * st_pitch(RT));
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int ct = 0; ct < CT; ++ct) {
+      const uint32_t dd = d0 + 32 * ct;
+      if (!LIN && vec) {
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const uint32_t rr = r0 + 32 * rt, dd = d0 + 32 * ct;
-        if (!LIN && vec) {
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) st[acc_row(v, g) * ST_PITCH + i] = int(acc[rt][ct][v]);
-          __builtin_amdgcn_wave_barrier();  // LDS operations of a wave run in order
-          store_tile(a, st, dd, rr, lane);
-          __builtin_amdgcn_wave_barrier();  // the next tile's copy waits for these reads
-        } else {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const uint32_t r = rr + uint32_t(LIN ? acc_row(v, g) : i);
-            const uint32_t d = dd + uint32_t(LIN ? i : acc_row(v, g));
-            if (r < a.R && d < a.D) store_elem(a, d, r, int(acc[rt][ct][v]));
-          }
-        }
+          for (int v = 0; v < 16; ++v)
+            st[acc_row(v, g) * st_pitch(RT) + 32 * rt + i] = int(acc[rt][ct][v]);
+        __builtin_amdgcn_wave_barrier();    // LDS operations of a wave run in order
+        store_tile<RT>(a, st, dd, r0, lane);
+        __builtin_amdgcn_wave_barrier();    // the next tile's copy waits for these reads
+        continue;
       }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const uint32_t r = r0 + 32 * rt + uint32_t(LIN ? acc_row(v, g) : i);
+          const uint32_t d = dd + uint32_t(LIN ? i : acc_row(v, g));
+          if (r < a.R && d < a.D) store_elem(a, d, r, int(acc[rt][ct][v]));
+        }
+    }
   }
 }
 
@@ -698,7 +705,7 @@ int launch_forward(const Layer &L, const void *X, const void *W, const float *ga
   a.nblocks = a.dblocks * ((a.R + rows_b - 1) / rows_b);
   const dim3 g2(a.nblocks);
   auto go = [&]<bool LIN, bool BIG>() {
-    if (form == 0) hipLaunchKernelGGL((k_fwd<2, 2, 1, 4, LIN, BIG>), g2, dim3(THREADS), 0, s, a, vec);
+    if (form == 0) hipLaunchKernelGGL((k_fwd<2, 2, 1, 2, LIN, BIG>), g2, dim3(THREADS), 0, s, a, vec);
     else if (form == 1)
       hipLaunchKernelGGL((k_fwd<2, 2, 4, 4, LIN, BIG>), g2, dim3(THREADS), 0, s, a, vec);
     else if (a.steps <= 16)
