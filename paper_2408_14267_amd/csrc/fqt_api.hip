@@ -3,6 +3,7 @@
 #include <mutex>
 
 #include "fqt_internal.hpp"
+#include "fqt_train.h"
 
 namespace fqt {
 
@@ -175,7 +176,8 @@ void carve_quant_ws(void *ws, const Layer &L, QuantWs *q) {
 namespace {
 
 int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg, const void *X, const void *W,
-                       const void *dY, void *dX, float *dW, void *ws, hipStream_t s);
+                       const void *dY, void *dX, float *dW, void *ws, hipStream_t s,
+                       TrainJob *train = nullptr);
 
 // Validation shared by the layer backward entry points (everything but the workspace).
 int check_layer_backward(const fqt_layer_desc *desc, const fqt_quant_cfg *cfg, const void *X,
@@ -440,7 +442,8 @@ int fqt_layer_backward_noalloc(const fqt_layer_desc *desc, const fqt_quant_cfg *
 namespace fqt {
 namespace {
 int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X, const void *W,
-                       const void *dY, void *dX, float *dW, void *ws, hipStream_t s) {
+                       const void *dY, void *dX, float *dW, void *ws, hipStream_t s,
+                       TrainJob *train) {
   const fqt_quant_cfg *cfg = &cfg_;
   LayerWs w;
   carve_layer_ws(ws, L, *cfg, &w);
@@ -449,7 +452,7 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
   SignJob sj{X, W, w.xsign, w.wsb, w.wlsum, false};
   // The products read the byte codes; the bit planes (the paper's packed form) are left to
   // fqt_agp_scq_quantize callers.
-  FQT_TRY(launch_quantize(L, *cfg, dY, w.q, w.qws, s, &sj, false));
+  FQT_TRY(launch_quantize(L, *cfg, dY, w.q, w.qws, s, &sj, false, train));
   if (!sj.done) {
     if (L.kind == FQT_LINEAR)
       FQT_TRY(launch_pack_bits(X, L.x_t, L.N, L.C, L.C, FQT_PACK_ALONG_ROWS, nullptr, w.xsign,
@@ -460,7 +463,7 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
     FQT_TRY(launch_pack_w_i8(W, L, w.wsb, w.wlsum, s));
   }
   return launch_products(L, *cfg, w.q, w.xsign, w.wsb, w.wlsum, dX, dW, w.dw_ws, w.qws.sslot,
-                         w.qws.cslot, s);
+                         w.qws.cslot, s, train);
 }
 }  // namespace
 }  // namespace fqt
@@ -481,6 +484,40 @@ int fqt_binary_forward(const fqt_layer_desc *desc, const void *X, const void *W,
   if (Dp * Kp > LIMIT31 || (Kp / 64) * L.Wr * 64 * 8 > LIMIT31 || int64_t(L.N) * L.D * L.P > LIMIT31)
     return FQT_E_SHAPE;
   return launch_forward(L, X, W, gamma, Y, I_out, ws, static_cast<hipStream_t>(hip_stream));
+}
+
+// A layer workspace followed by the partial sums of dgamma.
+static size_t train_ws_bytes(const Layer &L, const fqt_quant_cfg &cfg, size_t *part_at) {
+  *part_at = carve_layer_ws(nullptr, L, cfg, nullptr);
+  return *part_at + align256(train_part_bytes(L));
+}
+
+int fqt_train_workspace_size(const fqt_layer_desc *desc, const fqt_quant_cfg *cfg, size_t *bytes) {
+  Layer L;
+  FQT_TRY(make_layer(desc, &L));
+  FQT_TRY(check_cfg(cfg, L));
+  if (!bytes) return FQT_E_NULL;
+  size_t at;
+  *bytes = train_ws_bytes(L, *cfg, &at);
+  return FQT_OK;
+}
+
+int fqt_train_backward(const fqt_layer_desc *desc, const fqt_quant_cfg *cfg, const float *X,
+                       const float *W, const float *gamma, const int32_t *I, const float *dH,
+                       float *dX, float *dW, float *dgamma, void *ws, size_t ws_bytes,
+                       void *hip_stream) {
+  Layer L;
+  FQT_TRY(check_layer_backward(desc, cfg, X, W, dH, dX, dW, &L));
+  if (L.dy_t != FQT_F32 || L.x_t != FQT_F32 || L.w_t != FQT_F32 || L.dx_t != FQT_F32)
+    return FQT_E_DTYPE;
+  if (!gamma || !I || !dgamma || !ws) return FQT_E_NULL;
+  if (!aligned(gamma, 4) || !aligned(dgamma, 4) || !aligned(I, 16) || !aligned(ws, 256))
+    return FQT_E_ALIGN;
+  size_t at;
+  if (ws_bytes < train_ws_bytes(L, *cfg, &at)) return FQT_E_WORKSPACE;
+  TrainJob t{gamma, I, reinterpret_cast<float *>(static_cast<char *>(ws) + at), dgamma, X, 0};
+  return layer_backward_run(L, *cfg, X, W, dH, dX, dW, ws, static_cast<hipStream_t>(hip_stream),
+                            &t);
 }
 
 }  // extern "C"

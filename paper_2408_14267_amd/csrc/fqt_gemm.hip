@@ -806,7 +806,13 @@ struct DxArgs {
   uint32_t wide;                 // 0: split form; CT >= 1: register tiles, CT channel tiles
   uint32_t cblocks;              // register-tile form: channel blocks of 32 CT channels
   FastDiv divCb;
+  const float *ste;              // training: X; dX (float32) is 0 where |X| <= 1 does not hold
 };
+
+// The straight-through estimator's mask of element o.
+__device__ __forceinline__ bool ste_pass(const DxArgs &a, size_t o) {
+  return !a.ste || __builtin_fabsf(a.ste[o]) <= 1.0f;
+}
 
 constexpr int DX_MAX_TAPS = 64;
 constexpr uint32_t DX_ZCHUNK = 65536;    // elements of a pruned sample one block zeroes
@@ -949,6 +955,18 @@ __device__ __forceinline__ void dx_body(const DxArgs &a, uint32_t bid, DxLds &sm
   dx_row_table<32, DX_THREADS>(a, m0, live_rows, sm.rowoff);
   __syncthreads();
 
+  // Training: the mask of this lane's four outputs, loaded ahead of the contraction.
+  const int r0 = 8 * int(wave) + 4 * g;   // channel rows r0 .. r0 + 3 of this lane
+  const int off = sm.pix_out[i];
+  bool pass[4] = {true, true, true, true};
+  if (a.ste && off >= 0) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t cc = min(c0 + uint32_t(r0 + u), a.C - 1);
+      pass[u] = ste_pass(a, size_t(off) + size_t(cc) * a.HW);
+    }
+  }
+
   // This lane: A row = channel c0 + i, B column = pixel m0 + i.
   const uint32_t ch = c0 + i;
   const uint32_t abase = ch < a.C ? ch * 32 + 16 * g : BUF_NONE;
@@ -978,10 +996,8 @@ __device__ __forceinline__ void dx_body(const DxArgs &a, uint32_t bid, DxLds &sm
 #pragma unroll
   for (int v = 0; v < 16; ++v) sm.red[wave][v][lane] = acc[v];
   __syncthreads();
-  const int off = sm.pix_out[i];
   if (off < 0) return;                    // rows past the count belong to the zero blocks
   const float S = sm.pix_s[i], Z = sm.pix_z[i];
-  const int r0 = 8 * int(wave) + 4 * g;   // channel rows r0 .. r0 + 3 of this lane
   int I[4], c[4] = {0, 0, 0, 0}, lt[4] = {0, 0, 0, 0};
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -1000,7 +1016,7 @@ __device__ __forceinline__ void dx_body(const DxArgs &a, uint32_t bid, DxLds &sm
     const uint32_t cc = c0 + uint32_t(r0 + u);
     if (cc >= a.C) continue;
     const int Iu = I[u] + (B8 ? 128 * lt[u] : 0);
-    const float out = rescale(S, Iu, Z, float(c[u]));
+    const float out = pass[u] ? rescale(S, Iu, Z, float(c[u])) : 0.0f;
     const size_t o = size_t(off) + size_t(cc) * a.HW;
     if (a.dx_t == FQT_BF16) static_cast<uint16_t *>(a.dX)[o] = f32_to_bf16(out);
     else static_cast<float *>(a.dX)[o] = out;
@@ -1051,15 +1067,34 @@ __device__ __forceinline__ void dx_store_tile(const DxArgs &a, const int32_t *pi
   const size_t base = size_t(o0) + size_t(cc) * a.HW;
   // (o15 = o0 + 15 with both live: the 16 offsets are consecutive, also where a sample
   // boundary falls inside, which only C = 1 allows.)
-  if (o0 >= 0 && o15 == o0 + 15 && (reinterpret_cast<uintptr_t>(dst + base) & 15) == 0) {
+  if (o0 >= 0 && o15 == o0 + 15 &&
+      ((reinterpret_cast<uintptr_t>(dst + base) | reinterpret_cast<uintptr_t>(a.ste ? a.ste + base : nullptr)) & 15) == 0) {
     const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
     uint4 *d4 = reinterpret_cast<uint4 *>(dst + base);
+    if constexpr (sizeof(T) == 4) {
+      if (a.ste) {
+        const float4 *x4 = reinterpret_cast<const float4 *>(a.ste + base);
+        float4 x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = x4[k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint4 v = s4[k];
+          d4[k] = make_uint4(__builtin_fabsf(x[k].x) <= 1.0f ? v.x : 0u,
+                             __builtin_fabsf(x[k].y) <= 1.0f ? v.y : 0u,
+                             __builtin_fabsf(x[k].z) <= 1.0f ? v.z : 0u,
+                             __builtin_fabsf(x[k].w) <= 1.0f ? v.w : 0u);
+        }
+        return;
+      }
+    }
 #pragma unroll
     for (int k = 0; k < 16 / PER16; ++k) d4[k] = s4[k];
   } else {
     for (int j = 0; j < 16; ++j) {
       const int o = pix_out[pb + j];
-      if (o >= 0) dst[size_t(o) + size_t(cc) * a.HW] = src[j];
+      const size_t at = size_t(o) + size_t(cc) * a.HW;
+      if (o >= 0) dst[at] = ste_pass(a, at) ? src[j] : T(0);
     }
   }
 }
@@ -1229,8 +1264,8 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
         if (B8)
           for (int tap = 0; tap < taps; ++tap) lt += sm.wl[tap][row];
         const int Iv = acc[rt][ct][v] + (B8 ? 128 * lt : 0);
-        const float out = rescale(S, Iv, Z, cz[v]);
         const size_t o = size_t(off) + size_t(cc) * a.HW;
+        const float out = ste_pass(a, o) ? rescale(S, Iv, Z, cz[v]) : 0.0f;
         if (a.dx_t == FQT_BF16) static_cast<uint16_t *>(a.dX)[o] = f32_to_bf16(out);
         else static_cast<float *>(a.dX)[o] = out;
         if (a.I_out) a.I_out[o] = Iv;
@@ -1258,20 +1293,43 @@ void k_mfma_dx(DxArgs a) {
 // waves and reduced in LDS (KRED).
 enum DwForm { DWF_PARTS = 0, DWF_DIRECT = 1, DWF_KRED = 2 };
 
-// Both products in one launch (the layer backward): blocks [0, ndw) are dW blocks, the rest
-// dX blocks; the two share one LDS allocation.
+// Training: dgamma of 64 channels per block, the sum of their partial sums [parts][D] (in
+// float64: the partial sums are what rounds).
+struct DgArgs {
+  const float *part;
+  float *out;
+  uint32_t parts, D;
+};
+__device__ __forceinline__ void dgamma_body(const DgArgs &a, uint32_t bid, double (*sm)[64]) {
+  const uint32_t lane = threadIdx.x & 63, d = bid * 64 + lane;
+  const uint32_t wave = wave_id();
+  double s = 0.0;
+  if (d < a.D) {
+#pragma unroll 8
+    for (uint32_t p = wave; p < a.parts; p += DX_WAVES) s += double(a.part[size_t(p) * a.D + d]);
+  }
+  sm[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && d < a.D) a.out[d] = float(sm[0][lane] + sm[1][lane] + sm[2][lane] + sm[3][lane]);
+}
+
+// Both products in one launch (the layer backward): blocks [0, ndw) are dW blocks, the next
+// dxa.nblocks dX blocks, those past them sum dgamma; all share one LDS allocation.
 template <int WT>
 union ProductsLds {
   DxLdsOf<WT> dx;
   DwRedLds dw;
+  double dg[DX_WAVES][64];
 };
 template <bool B8, int NB, int DWF, int WT>
 __global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT != 0 ? 3 : 1)))
-void k_products(DxArgs dxa, DwArgs dwa, uint32_t ndw) {
+void k_products(DxArgs dxa, DwArgs dwa, uint32_t ndw, DgArgs dg) {
   __shared__ ProductsLds<WT> sm;
   if (blockIdx.x < ndw) {
     if constexpr (DWF == DWF_KRED) dw_kred_body<B8>(dwa, blockIdx.x, sm.dw);
     else dw_part_body<B8, DWF == DWF_DIRECT>(dwa, blockIdx.x);
+  } else if (blockIdx.x - ndw >= dxa.nblocks) {
+    dgamma_body(dg, blockIdx.x - ndw - dxa.nblocks, sm.dg);
   } else {
     if constexpr (WT != 0) dx_body_tiles<B8, WT>(dxa, blockIdx.x - ndw, sm.dx);
     else dx_body<B8, NB>(dxa, blockIdx.x - ndw, sm.dx);
@@ -1370,7 +1428,7 @@ DxArgs make_dx_args(const Layer &L, const fqt_qgrad &q, const int8_t *wsb,
   DxArgs a;
   a.codes = q.psq_codes; a.kept = q.psq_kept; a.count = q.psq_count;
   a.scale = q.psq_scale; a.offset = q.psq_offset; a.slot_sz = nullptr; a.wsb = wsb;
-  a.wlsum = wlsum;
+  a.wlsum = wlsum; a.ste = nullptr;
   a.dX = dX; a.I_out = I_out; a.dx_t = L.dx_t;
   a.N = uint32_t(L.N); a.C = uint32_t(L.C); a.H = uint32_t(L.H); a.W = uint32_t(L.W);
   a.HW = uint32_t(L.HW); a.Ho = uint32_t(L.Ho); a.Wo = uint32_t(L.Wo); a.P = uint32_t(L.P);
@@ -1512,7 +1570,7 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
 int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
-                    hipStream_t s) {
+                    hipStream_t s, const TrainJob *train) {
   if (L.kh * L.kw > DX_MAX_TAPS) return FQT_E_SHAPE;
   DwArgs dwa = make_dw_args(L, cfg, q, xsign, dW, nullptr, dw_ws);
   DxArgs dxa = make_dx_args(L, q, wsb, wlsum, dX, nullptr);
@@ -1533,21 +1591,26 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
   }
   const uint32_t ndw = (big || split_big) ? 0u
                       : kred ? dw_kred_blocks(L, dwa) : dw_part_blocks(L, dwa);
-  const dim3 grid(ndw + dxa.nblocks);
+  DgArgs dg{};
+  if (train) {
+    dxa.ste = train->X;
+    dg = DgArgs{train->part, train->dgamma, train->parts, uint32_t(L.D)};
+  }
+  const dim3 grid(ndw + dxa.nblocks + (train ? unsigned((L.D + 63) / 64) : 0u));
   const int nb = dx_batch(dxa);
   auto go = [&]<bool B8, int DWF, int WT>() {
     if constexpr (WT != 0)
       hipLaunchKernelGGL((k_products<B8, 4, DWF, WT>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
-                         ndw);
+                         ndw, dg);
     else if (nb == 4)
       hipLaunchKernelGGL((k_products<B8, 4, DWF, 0>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
-                         ndw);
+                         ndw, dg);
     else if (nb == 8)
       hipLaunchKernelGGL((k_products<B8, 8, DWF, 0>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
-                         ndw);
+                         ndw, dg);
     else
       hipLaunchKernelGGL((k_products<B8, 10, DWF, 0>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
-                         ndw);
+                         ndw, dg);
     if (DWF == DWF_PARTS) launch_dw_finish<B8>(L, dwa, s);
   };
   auto go2 = [&]<bool B8, int DWF>() {

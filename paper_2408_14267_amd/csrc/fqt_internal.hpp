@@ -102,12 +102,24 @@ struct SignJob {
   int32_t *wlsum;
   bool done;
 };
+// What a training step adds around the layer backward (float32 layers; fqt_train.h): the
+// quantized gradient is dH * gamma (formed where dH is read), dgamma = sum dH * I (partial sums
+// by the statistics, added up beside the products) and dX is kept where |X| <= 1.
+struct TrainJob {
+  const float *gamma;    // [D]
+  const int32_t *I;      // [N][D][P], 16-byte aligned
+  float *part;           // [parts][D] partial sums (train_part_bytes)
+  float *dgamma;         // [D]
+  const float *X;
+  uint32_t parts;        // set by launch_quantize
+};
+size_t train_part_bytes(const Layer &L);
 // Zero-fills the FQT_WS_STATE_BYTES of state at the start of a quantize / layer workspace.
 int launch_state_clear(void *state, hipStream_t s);
 // planes = false: the codes one byte each only (what the products read), no bit planes.
 int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, const fqt_qgrad &q,
                     const QuantWs &w, hipStream_t s, SignJob *signs = nullptr,
-                    bool planes = true);
+                    bool planes = true, TrainJob *train = nullptr);
 int launch_pack_bits(const void *src, int dtype, int64_t rows, int64_t cols, int64_t ld, int axis,
                      const Layer *conv, uint64_t *dst, int32_t *linesum, hipStream_t s,
                      bool word_major = false);
@@ -123,7 +135,7 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
 int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
-                    hipStream_t s);
+                    hipStream_t s, const TrainJob *train = nullptr);
 
 // The dW product from the code planes and line-major sign bits (popcount or fp4 engine).
 size_t engine_ws_bytes(const Layer &L, const fqt_quant_cfg &cfg, int engine);
@@ -321,6 +333,10 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
     const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
     return uint32_t((__lane_id() & 32) ? r[0] : r[1]);
   }
+}
+template <int M>
+__device__ __forceinline__ float lane_xor_f(float v) {
+  return __uint_as_float(lane_xor<M>(__float_as_uint(v)));
 }
 template <int M>
 __device__ __forceinline__ uint64_t lane_xor64(uint64_t v) {

@@ -85,15 +85,19 @@ struct StatsGeom {
 
 // Load the quads of tile rows [r0, r0 + 64) x channels [d0, d0 + 64) into x (element 0 of
 // dY outside the layer, so the loads issue back to back).
-template <int MODE, int DT>
-__device__ __forceinline__ void stats_load(const void *dy, const TileGeom &g, uint32_t r0,
-                                           uint32_t d0, int t, float (&x)[QUADS][4],
-                                           bool (&ok)[QUADS]) {
+// I: the integers of the same quads, in training.
+template <int MODE, int DT, bool TR>
+__device__ __forceinline__ void stats_load(const void *dy, const int32_t *I, const TileGeom &g,
+                                           uint32_t r0, uint32_t d0, int t,
+                                           float (&x)[QUADS][4], bool (&ok)[QUADS],
+                                           int4 (&iv)[TR ? QUADS : 1]) {
   for (int q = 0; q < QUADS; ++q) {
     int dd, rr;
     quad_coord<MODE>(t, q, 0, dd, rr);
     ok[q] = d0 + dd < g.D && r0 + rr < g.R;      // quads are all-valid or all-invalid
-    load_quad<DT>(dy, ok[q] ? elem_index(g, d0 + dd, r0 + rr) : 0, x[q]);
+    const uint32_t e = ok[q] ? elem_index(g, d0 + dd, r0 + rr) : 0;
+    load_quad<DT>(dy, e, x[q]);
+    if constexpr (TR) iv[q] = *reinterpret_cast<const int4 *>(I + e);
   }
 }
 
@@ -110,6 +114,33 @@ __device__ __forceinline__ int2 merged_key(uint2 u) {
   return make_int2(int(~u.x ^ 0x80000000u), int(u.y ^ 0x80000000u));
 }
 
+// gamma and I of a training step in the statistics: the keys are those of dH * gamma, and
+// part[block][d] gets the block's sum of dH * I.
+struct StatsTrain {
+  const float *gamma;
+  const int32_t *I;
+  float *part;
+};
+__device__ __forceinline__ float dot4(const float (&x)[4], int4 i, float acc) {
+  acc = __builtin_fmaf(x[0], float(i.x), acc);
+  acc = __builtin_fmaf(x[1], float(i.y), acc);
+  acc = __builtin_fmaf(x[2], float(i.z), acc);
+  return __builtin_fmaf(x[3], float(i.w), acc);
+}
+// Sum of v over groups of 2^(LOG) lanes, in every lane of the group.
+template <int LOG>
+__device__ __forceinline__ float lanes_sum(float v) {
+  v += lane_xor_f<1>(v);
+  v += lane_xor_f<2>(v);
+  v += lane_xor_f<4>(v);
+  v += lane_xor_f<8>(v);
+  if constexpr (LOG > 4) {
+    v += lane_xor_f<16>(v);
+    v += lane_xor_f<32>(v);
+  }
+  return v;
+}
+
 // One block per (rs row tiles, 64 channels).  Each 64 x 64 tile goes through LDS as
 // order-preserving integer keys; channel rows are reduced over the rows (kept across the
 // block's row tiles), row columns over the channels and then over the rows of each sample
@@ -117,12 +148,12 @@ __device__ __forceinline__ int2 merged_key(uint2 u) {
 // With mks / mkc set (merged keys), the sample and channel keys are combined into them
 // with atomics instead of being stored as partials: channel keys into replica
 // (row block) % MKEY_REP, sample keys into replica (channel tile) % MKEY_REP.
-template <int MODE, int DT>
+template <int MODE, int DT, bool TR>
 __global__ __launch_bounds__(THREADS) void k_stats(const void *__restrict__ dy, StatsGeom sg,
                                                    int2 *__restrict__ part_c,
                                                    int2 *__restrict__ part_s,
                                                    uint2 *__restrict__ mks,
-                                                   uint2 *__restrict__ mkc) {
+                                                   uint2 *__restrict__ mkc, StatsTrain tr) {
   __shared__ int32_t key[TILE][TILE + 1];
   __shared__ int32_t pmin[WAVES][TILE], pmax[WAVES][TILE];
   const TileGeom &g = sg.g;
@@ -135,33 +166,71 @@ __global__ __launch_bounds__(THREADS) void k_stats(const void *__restrict__ dy, 
   int clo = INT_MAX, chi = INT_MIN;             // channel d0 + lane over this wave's rows
   // Two register sets of row tiles: two tiles' loads are in flight behind each reduction.
   float xa[QUADS][4], xb[QUADS][4];
-  bool oka[QUADS], okb[QUADS];
-  if (MODE != TILE_SCALAR) {
-    stats_load<MODE, DT>(dy, g, rt0 * TILE, d0, t, xa, oka);
-    if (sg.rs > 1 && rt0 + 1 < sg.nrt) stats_load<MODE, DT>(dy, g, (rt0 + 1) * TILE, d0, t, xb, okb);
+  // Training: gamma of this thread's channels and its sums of dH * I (per quad in PIX, per
+  // element of the quad in CHAN, per pass in SCALAR), all loaded and summed as keys are formed.
+  constexpr int GS = !TR ? 1 : MODE == TILE_PIX ? QUADS : MODE == TILE_CHAN ? 4 : 4 * QUADS;
+  float gam[GS], gsum[GS];
+  if constexpr (TR) {
+#pragma unroll
+    for (int m = 0; m < GS; ++m) {
+      int dd, rr;
+      if (MODE == TILE_PIX) quad_coord<MODE>(t, m, 0, dd, rr);
+      else if (MODE == TILE_CHAN) quad_coord<MODE>(t, 0, m, dd, rr);
+      else quad_coord<MODE>(t, m >> 2, m & 3, dd, rr);
+      gam[m] = d0 + dd < g.D ? tr.gamma[d0 + dd] : 0.0f;
+      gsum[m] = 0.0f;
+    }
   }
-  auto tile = [&](uint32_t s, float (&x)[QUADS][4], bool (&ok)[QUADS]) -> bool {
+  bool oka[QUADS], okb[QUADS];
+  int4 ia[TR ? QUADS : 1], ib[TR ? QUADS : 1];
+  if (MODE != TILE_SCALAR) {
+    stats_load<MODE, DT, TR>(dy, tr.I, g, rt0 * TILE, d0, t, xa, oka, ia);
+    if (sg.rs > 1 && rt0 + 1 < sg.nrt)
+      stats_load<MODE, DT, TR>(dy, tr.I, g, (rt0 + 1) * TILE, d0, t, xb, okb, ib);
+  }
+  auto tile = [&](uint32_t s, float (&x)[QUADS][4], bool (&ok)[QUADS],
+                  int4 (&ivs)[TR ? QUADS : 1]) -> bool {
     const uint32_t rt = rt0 + s;
     if (rt >= sg.nrt) return false;
     const uint32_t r0 = rt * TILE;
     if (MODE != TILE_SCALAR) {
       for (int q = 0; q < QUADS; ++q) {
         if (!ok[q]) continue;
+        if constexpr (TR) {
+          const int4 iv = ivs[q];
+          if constexpr (MODE == TILE_PIX) {
+            gsum[q] = dot4(x[q], iv, gsum[q]);
+          } else if constexpr (MODE == TILE_CHAN) {
+            gsum[0] = __builtin_fmaf(x[q][0], float(iv.x), gsum[0]);
+            gsum[1] = __builtin_fmaf(x[q][1], float(iv.y), gsum[1]);
+            gsum[2] = __builtin_fmaf(x[q][2], float(iv.z), gsum[2]);
+            gsum[3] = __builtin_fmaf(x[q][3], float(iv.w), gsum[3]);
+          }
+        }
         for (int k = 0; k < 4; ++k) {
           int dk, rk;
           quad_coord<MODE>(t, q, k, dk, rk);
-          key[dk][rk] = f2key(x[q][k] + 0.0f);
+          float v = x[q][k];
+          if constexpr (TR) v = __fmul_rn(v, gam[MODE == TILE_PIX ? q : MODE == TILE_CHAN ? k : 0]);
+          key[dk][rk] = f2key(v + 0.0f);
         }
       }
       // The row tile two ahead loads into these registers while this one is reduced.
       if (s + 2 < sg.rs && rt + 2 < sg.nrt)
-        stats_load<MODE, DT>(dy, g, r0 + 2 * TILE, d0, t, x, ok);
+        stats_load<MODE, DT, TR>(dy, tr.I, g, r0 + 2 * TILE, d0, t, x, ok, ivs);
     } else {
       for (int q = 0; q < 4 * QUADS; ++q) {
         int dd, rr;
         quad_coord<MODE>(t, q >> 2, q & 3, dd, rr);
-        if (d0 + dd < g.D && r0 + rr < g.R)
-          key[dd][rr] = f2key(load_elem<DT>(dy, elem_index(g, d0 + dd, r0 + rr)) + 0.0f);
+        if (d0 + dd < g.D && r0 + rr < g.R) {
+          const uint32_t e = elem_index(g, d0 + dd, r0 + rr);
+          float v = load_elem<DT>(dy, e);
+          if constexpr (TR && MODE == TILE_SCALAR) {
+            gsum[q] = __builtin_fmaf(v, float(tr.I[e]), gsum[q]);
+            v = __fmul_rn(v, gam[q]);
+          }
+          key[dd][rr] = f2key(v + 0.0f);
+        }
       }
     }
     __syncthreads();
@@ -247,7 +316,7 @@ __global__ __launch_bounds__(THREADS) void k_stats(const void *__restrict__ dy, 
       return true;
   };
   for (uint32_t s = 0; s < sg.rs; s += 2) {
-    if (!tile(s, xa, oka) || s + 1 >= sg.rs || !tile(s + 1, xb, okb)) break;
+    if (!tile(s, xa, oka, ia) || s + 1 >= sg.rs || !tile(s + 1, xb, okb, ib)) break;
   }
   // Channel partials of this row block, [row block][D]: the waves' partials combined,
   // then one coalesced store.
@@ -264,6 +333,34 @@ __global__ __launch_bounds__(THREADS) void k_stats(const void *__restrict__ dy, 
     if (mkc) merge_key(mkc + (bxr % MKEY_REP) * MKEY_GROUPS + d0 + lane, lo, hi);
     else part_c[size_t(bxr) * g.D + d0 + lane] = make_int2(lo, hi);
   }
+  if constexpr (TR) {
+    float *out = tr.part + size_t(bxr) * g.D + d0;
+    if constexpr (MODE == TILE_CHAN) {
+      // The rows of a channel lie in lanes 16 apart and in all the waves.
+      float *sums = reinterpret_cast<float *>(&key[0][0]);      // [WAVES][TILE]
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float v = gsum[k] + lane_xor_f<16>(gsum[k]);
+        v += lane_xor_f<32>(v);
+        if (lane < 16) sums[wave * TILE + 4 * lane + k] = v;
+      }
+      __syncthreads();
+      if (t < TILE && d0 + t < g.D) {
+        float v = sums[t];
+        for (int w = 1; w < WAVES; ++w) v += sums[w * TILE + t];
+        out[t] = v;
+      }
+    } else {
+#pragma unroll
+      for (int m = 0; m < GS; ++m) {
+        const float v = lanes_sum<MODE == TILE_PIX ? 4 : 6>(gsum[m]);
+        int dd, rr;
+        if (MODE == TILE_PIX) quad_coord<MODE>(t, m, 0, dd, rr);
+        else quad_coord<MODE>(t, m >> 2, m & 3, dd, rr);
+        if (rr == 0 && d0 + dd < g.D) out[dd] = v;
+      }
+    }
+  }
 }
 
 // Large maps (Ho*Wo >= 1024): the (min, max) key of every (sample, channel) plane of dY,
@@ -271,53 +368,56 @@ __global__ __launch_bounds__(THREADS) void k_stats(const void *__restrict__ dy, 
 // flight; ppl[n * D + d].  A sample's key is the reduction of its D planes, a channel's of
 // its N planes.
 constexpr int PLANE_U = 8;
-template <int DT>
+template <int DT, bool TR>
 __global__ __launch_bounds__(256) void k_stats_planes(const void *__restrict__ dy,
                                                       uint32_t planes, uint32_t P4,
-                                                      int2 *__restrict__ ppl) {
+                                                      int2 *__restrict__ ppl, uint32_t D,
+                                                      StatsTrain tr) {
+  constexpr int U = TR ? PLANE_U / 2 : PLANE_U;      // (two tensors stream in training)
   const int lane = threadIdx.x & 63;
   const uint32_t nwaves = gridDim.x * 4;
   for (uint32_t pl = blockIdx.x * 4 + (threadIdx.x >> 6); pl < planes; pl += nwaves) {
     int lo = INT_MAX, hi = INT_MIN;
     const int64_t base = int64_t(pl) * P4 * 4;
+    const float gam = TR ? tr.gamma[pl % D] : 1.0f;
+    float gsum = 0.0f;
+    auto take = [&](float (&v)[4], const int4 &iv, bool in) {
+      if (TR) gsum = dot4(v, in ? iv : make_int4(0, 0, 0, 0), gsum);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int key = f2key((TR ? __fmul_rn(v[k], gam) : v[k]) + 0.0f);
+        lo = min(lo, in ? key : INT_MAX);
+        hi = max(hi, in ? key : INT_MIN);
+      }
+    };
     // Whole batches (no per-lane test: every load issues before the first use), then the
     // tail with out-of-plane quads reading element 0 and masked.
-    uint32_t qb = 0;
-    for (; qb + 64 * PLANE_U <= P4; qb += 64 * PLANE_U) {
-      float v[PLANE_U][4];
+    for (uint32_t qb = 0; qb < P4; qb += 64 * U) {
+      const bool whole = qb + 64 * U <= P4;
+      float v[U][4];
+      int4 iv[U];
 #pragma unroll
-      for (int u = 0; u < PLANE_U; ++u)
-        load_quad<DT>(dy, base + 4 * int64_t(qb + 64 * u + lane), v[u]);
-#pragma unroll
-      for (int u = 0; u < PLANE_U; ++u)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int key = f2key(v[u][k] + 0.0f);
-          lo = min(lo, key);
-          hi = max(hi, key);
-        }
-    }
-    if (qb < P4) {
-      float v[PLANE_U][4];
-#pragma unroll
-      for (int u = 0; u < PLANE_U; ++u) {
+      for (int u = 0; u < U; ++u) {
         const uint32_t q = qb + 64 * u + lane;
-        load_quad<DT>(dy, q < P4 ? base + 4 * int64_t(q) : 0, v[u]);
+        const int64_t at = whole || q < P4 ? base + 4 * int64_t(q) : 0;
+        load_quad<DT>(dy, at, v[u]);
+        if (TR) iv[u] = *reinterpret_cast<const int4 *>(tr.I + at);
       }
+      if (whole) {
 #pragma unroll
-      for (int u = 0; u < PLANE_U; ++u) {
-        const bool in = qb + 64 * u + lane < P4;
+        for (int u = 0; u < U; ++u) take(v[u], iv[u], true);
+      } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int key = f2key(v[u][k] + 0.0f);
-          lo = min(lo, in ? key : INT_MAX);
-          hi = max(hi, in ? key : INT_MIN);
-        }
+        for (int u = 0; u < U; ++u) take(v[u], iv[u], qb + 64 * u + lane < P4);
       }
     }
     lo = wave_min(lo);
     hi = wave_max(hi);
-    if (lane == 0) ppl[pl] = make_int2(lo, hi);
+    if (TR) gsum = lanes_sum<6>(gsum);
+    if (lane == 0) {
+      ppl[pl] = make_int2(lo, hi);
+      if (TR) tr.part[pl] = gsum;                    // [N][D]
+    }
   }
 }
 
@@ -1301,6 +1401,7 @@ struct QPackArgs {
   uint32_t eager;       // read every quad of the layer before the parameters
   uint32_t chan_fast;   // grid x walks the channel tiles (rows of dY read as long runs)
   uint32_t planes;      // 1: also write the bit planes (0: the byte codes only)
+  const float *gamma;   // training: the gradient is dy * gamma[d]
 };
 
 // Codes of a thread's quads into the LDS tiles.  The four codes of a quad share one
@@ -1343,7 +1444,7 @@ __device__ __forceinline__ void qpack_quads(const QPackArgs &a, const TileGeom &
   }
 }
 
-template <int MODE, int DT>
+template <int MODE, int DT, bool TR>
 __global__ __launch_bounds__(THREADS) void k_qpack(QPackArgs a) {
   __shared__ __align__(16) uint8_t cs[TILE][PITCH];   // PSQ codes, [rr][dd]
   __shared__ __align__(16) uint8_t cc[TILE][PITCH];   // PCQ codes, [dd][rr]
@@ -1411,6 +1512,13 @@ __global__ __launch_bounds__(THREADS) void k_qpack(QPackArgs a) {
       }
       need[q] = nd;
       if (!a.eager) load_quad<DT>(a.dy, nd ? elem_index(g, d0 + dd, r0 + rr) : 0, x[q]);
+      if constexpr (TR) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t d = d0 + (MODE == TILE_CHAN ? dd + k : dd);
+          x[q][k] = __fmul_rn(x[q][k], d < g.D ? a.gamma[d] : 0.0f);
+        }
+      }
     }
     if (a.bits == 1) qpack_quads<MODE, true>(a, g, d0, r0, t, x, need, Bf, spar, cpar, cs, cc);
     else qpack_quads<MODE, false>(a, g, d0, r0, t, x, need, Bf, spar, cpar, cs, cc);
@@ -1423,7 +1531,9 @@ __global__ __launch_bounds__(THREADS) void k_qpack(QPackArgs a) {
       const GroupParam ps = spar[rr], pc = cpar[dd];
       if (d < g.D && r < g.R && (ps.rank >= 0 || pc.rank >= 0)) {
         const uint32_t e = elem_index(g, d, r);
-        const float xv = load_elem<DT>(a.dy, e) + 0.0f;
+        float xv = load_elem<DT>(a.dy, e);
+        if constexpr (TR) xv = __fmul_rn(xv, a.gamma[d]);
+        xv += 0.0f;
         const Ctr4 u = philox_block(e >> 2, STREAM_ELEM, a.seed, a.step, a.layer);
         const float uf = unit24(ctr_word(u, e & 3u));
         qs = sr_any<false>(xv, ps, Bf, uf);
@@ -1524,6 +1634,11 @@ int64_t stats_row_blocks(const Layer &L) {
   return (L.Wr + rs - 1) / rs;
 }
 
+// Partial sums of dgamma: one row per row block of the statistics, or per sample (planes).
+size_t train_part_bytes(const Layer &L) {
+  return size_t(std::max(stats_row_blocks(L), L.N)) * size_t(L.D) * 4;
+}
+
 int launch_state_clear(void *state, hipStream_t s) {
   constexpr uint32_t n16 = FQT_WS_STATE_BYTES / 16;
   hipLaunchKernelGGL(k_state_clear, dim3((n16 + 255) / 256), dim3(256), 0, s,
@@ -1532,7 +1647,8 @@ int launch_state_clear(void *state, hipStream_t s) {
 }
 
 int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, const fqt_qgrad &q,
-                    const QuantWs &w, hipStream_t s, SignJob *signs, bool write_planes) {
+                    const QuantWs &w, hipStream_t s, SignJob *signs, bool write_planes,
+                    TrainJob *train) {
   TileGeom g{uint32_t(L.D), uint32_t(L.P), uint32_t(L.R), make_fastdiv(uint32_t(L.P))};
   const uint32_t nrt = uint32_t(L.Wr), ndt = uint32_t(L.Wd);
   const uint32_t nrb = uint32_t(stats_row_blocks(L));
@@ -1555,23 +1671,34 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   const bool merged = !planes && !many_partials && gmax <= 1024;
   uint2 *mks = merged ? w.mkeys : nullptr;
   uint2 *mkc = merged ? w.mkeys + L.N : nullptr;
+  StatsTrain st_train{};
+  if (train) {
+    st_train = StatsTrain{train->gamma, train->I, train->part};
+    train->parts = planes ? uint32_t(L.N) : nrb;
+  }
+  // Calls f<DT, TR>: the training form is float32.
+  auto by_type = [&](auto &&f) {
+    if (train) f.template operator()<FQT_F32, true>();
+    else if (L.dy_t == FQT_BF16) f.template operator()<FQT_BF16, false>();
+    else f.template operator()<FQT_F32, false>();
+  };
   if (planes) {
     const uint32_t np = uint32_t(L.N * L.D);
     const uint32_t blocks = std::min<uint32_t>((np + 3) / 4, 4096);
-    dispatch_dtype(L.dy_t, [&]<int DT>() {
-      hipLaunchKernelGGL(k_stats_planes<DT>, dim3(blocks), dim3(256), 0, s, dY, np,
-                         uint32_t(L.P / 4), w.part_c);
+    by_type([&]<int DT, bool TR>() {
+      hipLaunchKernelGGL((k_stats_planes<DT, TR>), dim3(blocks), dim3(256), 0, s, dY, np,
+                         uint32_t(L.P / 4), w.part_c, uint32_t(L.D), st_train);
     });
-  } else dispatch_dtype(L.dy_t, [&]<int DT>() {
+  } else by_type([&]<int DT, bool TR>() {
     if (mode == TILE_PIX)
-      hipLaunchKernelGGL((k_stats<TILE_PIX, DT>), grid, dim3(THREADS), 0, s, dY, sg, w.part_c,
-                         w.part_s, mks, mkc);
+      hipLaunchKernelGGL((k_stats<TILE_PIX, DT, TR>), grid, dim3(THREADS), 0, s, dY, sg, w.part_c,
+                         w.part_s, mks, mkc, st_train);
     else if (mode == TILE_CHAN)
-      hipLaunchKernelGGL((k_stats<TILE_CHAN, DT>), grid, dim3(THREADS), 0, s, dY, sg, w.part_c,
-                         w.part_s, mks, mkc);
+      hipLaunchKernelGGL((k_stats<TILE_CHAN, DT, TR>), grid, dim3(THREADS), 0, s, dY, sg, w.part_c,
+                         w.part_s, mks, mkc, st_train);
     else
-      hipLaunchKernelGGL((k_stats<TILE_SCALAR, DT>), grid, dim3(THREADS), 0, s, dY, sg,
-                         w.part_c, w.part_s, mks, mkc);
+      hipLaunchKernelGGL((k_stats<TILE_SCALAR, DT, TR>), grid, dim3(THREADS), 0, s, dY, sg,
+                         w.part_c, w.part_s, mks, mkc, st_train);
   });
   if (last_launch_status() != FQT_OK) return FQT_E_HIP;
 
@@ -1710,13 +1837,14 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   // groups of each encoding kept), above 3/4 for b <= 2.
   qa.eager = (cfg.agp_mode == FQT_AGP_OFF || cfg.bits <= 2) ? 1u : 0u;
   qa.planes = write_planes ? 1u : 0u;
-  dispatch_dtype(L.dy_t, [&]<int DT>() {
+  qa.gamma = train ? train->gamma : nullptr;
+  by_type([&]<int DT, bool TR>() {
     if (mode == TILE_PIX)
-      hipLaunchKernelGGL((k_qpack<TILE_PIX, DT>), qgrid, dim3(THREADS), 0, s, qa);
+      hipLaunchKernelGGL((k_qpack<TILE_PIX, DT, TR>), qgrid, dim3(THREADS), 0, s, qa);
     else if (mode == TILE_CHAN)
-      hipLaunchKernelGGL((k_qpack<TILE_CHAN, DT>), qgrid, dim3(THREADS), 0, s, qa);
+      hipLaunchKernelGGL((k_qpack<TILE_CHAN, DT, TR>), qgrid, dim3(THREADS), 0, s, qa);
     else
-      hipLaunchKernelGGL((k_qpack<TILE_SCALAR, DT>), qgrid, dim3(THREADS), 0, s, qa);
+      hipLaunchKernelGGL((k_qpack<TILE_SCALAR, DT, TR>), qgrid, dim3(THREADS), 0, s, qa);
   });
   return last_launch_status();
 }

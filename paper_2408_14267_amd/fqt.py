@@ -92,6 +92,8 @@ def _load():
                                         c_void_p, c_void_p, c_size_t, c_void_p]),
         "fqt_layer_backward_noalloc": (c_int, [D, Q, c_void_p, c_void_p, c_void_p, c_void_p,
                                                c_void_p, c_void_p]),
+        "fqt_train_workspace_size": (c_int, [D, Q, POINTER(c_size_t)]),
+        "fqt_train_backward": (c_int, [D, Q] + [c_void_p] * 9 + [c_size_t, c_void_p]),
         "fqt_binary_forward": (c_int, [D, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,
                                        c_void_p, c_size_t, c_void_p]),
     }
@@ -328,6 +330,25 @@ def fqt_binary_forward(desc, X, W, gamma, Y, I_out, ws, stream=None):
            "fqt_binary_forward")
 
 
+def fqt_train_workspace_size(desc, cfg):
+    n = c_size_t()
+    _check(_lib.fqt_train_workspace_size(desc, cfg, ctypes.byref(n)), "fqt_train_workspace_size")
+    return n.value
+
+
+def fqt_train_backward(desc, cfg, X, W, gamma, I, dH, dX, dW, dgamma, ws, stream=None):
+    z = _sizes(desc)
+    _need("fqt_train_backward",
+          (X, torch.float32, z["X"], "X"), (W, torch.float32, z["W"], "W"),
+          (gamma, torch.float32, desc.D, "gamma"), (I, torch.int32, z["dY"], "I"),
+          (dH, torch.float32, z["dY"], "dH"), (dX, torch.float32, z["X"], "dX"),
+          (dW, torch.float32, z["W"], "dW"), (dgamma, torch.float32, desc.D, "dgamma"))
+    _check(_lib.fqt_train_backward(desc, cfg, _ptr(X), _ptr(W), _ptr(gamma), _ptr(I), _ptr(dH),
+                                   _ptr(dX), _ptr(dW), _ptr(dgamma), _ptr(ws),
+                                   ws.numel() * ws.element_size(), _stream(stream)),
+           "fqt_train_backward")
+
+
 # ----------------------------------------------------------------------------- buffers
 
 class QGrad:
@@ -361,4 +382,11 @@ def workspace(desc, cfg, which=FQT_WS_LAYER, device="cuda", stream=None):
     ws = torch.empty(max(n, 1), dtype=torch.uint8, device=device)
     if which in (FQT_WS_QUANTIZE, FQT_WS_LAYER):
         fqt_workspace_init(ws, stream)
+    return ws
+
+
+def train_workspace(desc, cfg, device="cuda", stream=None):
+    """The workspace of fqt_train_backward, prepared by fqt_workspace_init."""
+    ws = torch.empty(fqt_train_workspace_size(desc, cfg), dtype=torch.uint8, device=device)
+    fqt_workspace_init(ws, stream)
     return ws

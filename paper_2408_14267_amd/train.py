@@ -42,18 +42,33 @@ class _BinaryLayerFn(torch.autograd.Function):
     def backward(ctx, dy):
         x, w, gamma, i = ctx.saved_tensors
         layer = ctx.layer
-        shape = (1, -1) + (1,) * (dy.dim() - 2)
-        g = (dy * gamma.view(shape)).contiguous()          # gradient of the binary product
         dx = torch.empty_like(x)
         dw = torch.empty_like(w)
         desc = layer.desc(x.shape)
         cfg = fqt.quant_cfg(layer.bits, layer.agp_mode, layer.seed, layer.step, layer.layer_id)
-        fqt.fqt_layer_backward(desc, cfg, x, w, g, dx, dw, layer.ws_backward(desc, cfg))
+        ws = layer.ws_backward(desc, cfg)
+        if torch.is_grad_enabled():
+            # A graph of this backward is asked for (create_graph): its parts that torch can
+            # differentiate stay torch operations.
+            shape = (1, -1) + (1,) * (dy.dim() - 2)
+            g = (dy * gamma.view(shape)).contiguous()      # gradient of the binary product
+            fqt.fqt_layer_backward(desc, cfg, x, w, g, dx, dw, ws)
+            dx = dx * (x.abs() <= 1)                        # straight-through estimator
+            dims = [0] + list(range(2, dy.dim()))
+            dgamma = (dy * i.to(torch.float32)).sum(dim=dims)
+        else:
+            # The same three steps inside the library's launches.
+            dgamma = torch.empty_like(gamma)
+            fqt.fqt_train_backward(desc, cfg, x, w, gamma, _aligned(i), _aligned(dy), dx, dw, dgamma,
+                                   ws)
         layer.step += 1
-        dx = dx * (x.abs() <= 1)                            # straight-through estimator
-        dims = [0] + list(range(2, dy.dim()))
-        dgamma = (dy * i.to(torch.float32)).sum(dim=dims)
         return dx, dw, dgamma, None
+
+
+def _aligned(t):
+    """t contiguous on a 16-byte address (a gradient may be expanded, or a view at any offset)."""
+    t = t.contiguous()
+    return t if t.data_ptr() % 16 == 0 else t.clone()
 
 
 class _BinaryBase(nn.Module):
@@ -68,18 +83,19 @@ class _BinaryBase(nn.Module):
         self.step = 0
         self._ws = {}
 
-    def _workspace(self, key, desc, cfg, which):
+    def _workspace(self, key, make):
         ws = self._ws.get(key)
         if ws is None:
-            ws = fqt.workspace(desc, cfg, which, device=self.weight.device)
-            self._ws[key] = ws
+            ws = self._ws[key] = make()
         return ws
 
     def ws_forward(self, desc):
-        return self._workspace(("f", desc.N, desc.H, desc.W), desc, None, fqt.FQT_WS_FORWARD)
+        return self._workspace(("f", desc.N, desc.H, desc.W), lambda: fqt.workspace(
+            desc, None, fqt.FQT_WS_FORWARD, device=self.weight.device))
 
     def ws_backward(self, desc, cfg):
-        return self._workspace(("b", desc.N, desc.H, desc.W), desc, cfg, fqt.FQT_WS_LAYER)
+        return self._workspace(("b", desc.N, desc.H, desc.W), lambda: fqt.train_workspace(
+            desc, cfg, device=self.weight.device))
 
     def forward(self, x):
         return _BinaryLayerFn.apply(x.contiguous(), self.weight, self.gamma, self)
