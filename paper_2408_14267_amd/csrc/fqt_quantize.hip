@@ -1591,6 +1591,146 @@ __global__ __launch_bounds__(THREADS) void k_qpack(QPackArgs a) {
   }
 }
 
+// The byte codes alone on maps of whole quads (Ho*Wo % 4 == 0), the layer backward's form on
+// larger layers.  k_qpack spends the VALU (its bound) on every element of a tile that holds
+// one kept group, since a wave there meets four channels at once; here a wave walks lines of
+// one channel x 256 rows, so that the channel's parameters are scalars and a channel (or a
+// tile of pruned samples) that is not kept costs nothing beyond its test.
+//
+// Codes in fixed point (b <= 7): with V = ceil(v 2^24), floor(v) + [u24 < frac(v) 2^24] is
+// (V + 2^24 - 1 - u24) >> 24 (u24 is whole: u24 < y and u24 < ceil(y) are the same test).
+// code_top returns the complement of that sum, -V + u24 - 2^24, whose top byte is ~q: one
+// conversion (floor of -v 2^24), one addition, and the bytes of four codes gather by v_perm.
+constexpr int QL_ROWS = 256, QL_THREADS = 256, QL_WAVES = QL_THREADS / 64;
+constexpr int64_t QL_MIN_BLOCKS = 256;
+constexpr int QL_PITCH = TILE + 16;      // bytes per LDS row: 16 lanes' dwords on distinct banks
+
+enum QlBits { QL_ONE = 0, QL_FIX = 1, QL_EIGHT = 2 };   // b = 1, 2..7, 8
+template <int BM>
+__device__ __forceinline__ uint32_t code_uniform(uint32_t u) {   // shared by both codes
+  if constexpr (BM == QL_FIX) return __builtin_amdgcn_alignbit(0xFFFFFFFFu, u, 8);   // u24 - 2^24
+  return __float_as_uint(unit24(u));
+}
+template <int BM>
+__device__ __forceinline__ uint32_t code_top(float x, float z, float inv, float Bf, uint32_t u) {
+  if constexpr (BM == QL_ONE)
+    return sr_bit(x, z, inv, __uint_as_float(u)) ? 0xFEFFFFFFu : 0xFFFFFFFFu;
+  if constexpr (BM == QL_EIGHT) return ~(sr_code(x, z, inv, Bf, __uint_as_float(u)) << 24);
+  const float v = __builtin_amdgcn_fmed3f(__fmul_rn(__fsub_rn(x, z), inv), 0.0f, Bf);
+  int nv;                                                   // floor(-v 2^24) = -V
+  asm("v_cvt_flr_i32_f32 %0, -%1" : "=v"(nv) : "v"(__fmul_rn(v, 16777216.0f)));
+  return uint32_t(nv) + u;
+}
+// The codes of four code_top values as bytes.
+__device__ __forceinline__ uint32_t code_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  return ~(__builtin_amdgcn_perm(b, a, 0x0c0c0703u) | __builtin_amdgcn_perm(d, c, 0x07030c0cu));
+}
+
+// Grid: ceil(R / 256) x ceil(D / 64) blocks; wave w takes channels d0 + 16 w .. + 15, lane l
+// rows r0 + 4 l .. + 3 (a quad of one sample).  PCQ codes leave from registers (8 lanes fill a
+// 32-byte chunk of a line), PSQ codes through LDS, where row 4 l + k lies in slot 64 k + l.
+template <int DT, int BM, bool TR>
+__global__ __launch_bounds__(QL_THREADS) void k_qpack_lines(QPackArgs a) {
+  __shared__ __align__(16) uint8_t cs[QL_ROWS][QL_PITCH];
+  __shared__ int32_t prow[QL_ROWS];        // PSQ row of each row, -1 if pruned or outside
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const TileGeom &g = a.g;
+  const uint32_t r0 = blockIdx.x * QL_ROWS, d0 = blockIdx.y * TILE, dw0 = d0 + 16 * wave;
+  const float Bf = float((1 << a.bits) - 1);
+  // This lane's sample and, in lane i < 16, channel dw0 + i.
+  const uint32_t r = r0 + 4 * lane;
+  const bool valid = r < g.R;
+  const uint32_t n = fdiv(valid ? r : 0, g.divP), p = (valid ? r : 0) - n * g.P;
+  GroupParam sp = a.sp[n], cp{0.0f, 0.0f, -1, 0};
+  if (lane < 16 && dw0 + lane < g.D) cp = a.cp[dw0 + lane];
+  float cgam = 1.0f;
+  if (TR && lane < 16 && dw0 + lane < g.D) cgam = a.gamma[dw0 + lane];
+  const bool keep_s = valid && sp.rank >= 0;
+  if (!keep_s) sp.inv = 0.0f;                               // every code 0
+  const uint64_t any_s = __ballot(keep_s);
+  const uint32_t kept_c = uint32_t(__ballot(cp.rank >= 0));  // bit i: channel dw0 + i
+  const uint32_t e0 = n * g.D * g.P + p;
+  if (wave == 0)
+    *reinterpret_cast<int4 *>(&prow[4 * lane]) =
+        keep_s ? make_int4(sp.rank * g.P + p, sp.rank * g.P + p + 1, sp.rank * g.P + p + 2,
+                           sp.rank * g.P + p + 3)
+               : make_int4(-1, -1, -1, -1);
+  if (!any_s && !kept_c) {
+    __syncthreads();
+    return;                                 // (such a block has no PSQ rows either)
+  }
+  const bool in_line = r < a.Wr * 64;       // rows past R to the end of the last word hold 0
+  uint8_t *pc = a.pcq_codes + (size_t(r >> 5) * g.D) * 32 + (r & 31);
+
+  float x[2][4][4];
+  auto load = [&](int grp, float (&v)[4][4]) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t d = dw0 + 4 * grp + c;
+      const bool in = valid && (((kept_c >> (4 * grp + c)) & 1u) || (keep_s && d < g.D));
+      load_quad<DT>(a.dy, in ? e0 + d * g.P : 0, v[c]);
+    }
+  };
+  load(0, x[0]);
+#pragma unroll
+  for (int grp = 0; grp < 4; ++grp) {
+    if (grp < 3) load(grp + 1, x[(grp + 1) & 1]);
+    uint32_t rows[4][4];                    // [row of the quad][channel]: ~code in the top byte
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int ci = 4 * grp + c;
+      const uint32_t d = dw0 + ci;
+      const bool kc = (kept_c >> ci) & 1u;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) rows[k][c] = 0xFFFFFFFFu;
+      if (!kc && (!any_s || d >= g.D)) continue;
+      float (&xv)[4] = x[grp & 1][c];
+      if constexpr (TR) {
+        const float gm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cgam), ci));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xv[k] = __fmul_rn(xv[k], gm);
+      }
+      Ctr4 u = philox_block((e0 + d * g.P) >> 2, STREAM_ELEM, a.seed, a.step, a.layer);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u.v[k] = code_uniform<BM>(u.v[k]);
+      if (any_s) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rows[k][c] = code_top<BM>(xv[k], sp.z, sp.inv, Bf, u.v[k]);
+      }
+      if (kc) {
+        const float z = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cp.z), ci));
+        const float inv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cp.inv), ci));
+        const uint32_t rank = uint32_t(__builtin_amdgcn_readlane(cp.rank, ci));
+        uint32_t q[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = code_top<BM>(xv[k], z, inv, Bf, u.v[k]);
+        const uint32_t word = code_bytes(q[0], q[1], q[2], q[3]);
+        if (in_line) *reinterpret_cast<uint32_t *>(pc + size_t(rank) * 32) = valid ? word : 0u;
+      }
+    }
+    if (any_s) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        *reinterpret_cast<uint32_t *>(&cs[64 * k + lane][16 * wave + 4 * grp]) =
+            code_bytes(rows[k][0], rows[k][1], rows[k][2], rows[k][3]);
+    }
+  }
+  __syncthreads();
+  if (!any_s) return;                       // (the same over the block: the waves share the rows)
+  // Consecutive threads store consecutive 16-byte pieces of the chunk-major rows.
+  const uint32_t part = threadIdx.x & 3;
+  uint8_t *out = a.psq_codes + size_t((d0 >> 5) + (part >> 1)) * g.R * 32 + 16 * (part & 1);
+#pragma unroll
+  for (int i = 0; i < QL_ROWS * 4 / QL_THREADS; ++i) {
+    const uint32_t rr = (threadIdx.x >> 2) + (QL_THREADS / 4) * i;
+    const int row = prow[rr];
+    if (row >= 0)
+      *reinterpret_cast<uint4 *>(out + size_t(row) * 32) =
+          *reinterpret_cast<const uint4 *>(&cs[64 * (rr & 3) + (rr >> 2)][16 * part]);
+  }
+}
+
 // Zero-fill of a quantize / layer workspace's state bytes (the merged group keys): one
 // 16-byte store per thread.  A kernel, not hipMemsetAsync, so that a captured graph replays
 // it like any other node.
@@ -1838,6 +1978,19 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   qa.eager = (cfg.agp_mode == FQT_AGP_OFF || cfg.bits <= 2) ? 1u : 0u;
   qa.planes = write_planes ? 1u : 0u;
   qa.gamma = train ? train->gamma : nullptr;
+  const uint32_t lblocks = uint32_t((L.R + QL_ROWS - 1) / QL_ROWS);
+  if (mode == TILE_PIX && !write_planes && int64_t(lblocks) * ndt >= QL_MIN_BLOCKS) {
+    const dim3 lgrid(lblocks, ndt);
+    by_type([&]<int DT, bool TR>() {
+      if (cfg.bits == 1)
+        hipLaunchKernelGGL((k_qpack_lines<DT, QL_ONE, TR>), lgrid, dim3(QL_THREADS), 0, s, qa);
+      else if (cfg.bits < 8)
+        hipLaunchKernelGGL((k_qpack_lines<DT, QL_FIX, TR>), lgrid, dim3(QL_THREADS), 0, s, qa);
+      else
+        hipLaunchKernelGGL((k_qpack_lines<DT, QL_EIGHT, TR>), lgrid, dim3(QL_THREADS), 0, s, qa);
+    });
+    return last_launch_status();
+  }
   by_type([&]<int DT, bool TR>() {
     if (mode == TILE_PIX)
       hipLaunchKernelGGL((k_qpack<TILE_PIX, DT, TR>), qgrid, dim3(THREADS), 0, s, qa);

@@ -1,0 +1,69 @@
+"""The layer backward (its own code kernels and operand formats) against the same layer through
+the separate entries: quantize, the sign packers and the products launch, bit for bit."""
+import sys
+
+import pytest
+
+from paper_2408_14267_amd.workloads import LayerShape
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _conv(N, C, D, H, W, k, s, p):
+    return LayerShape("c", "conv2d", N, C, D, H, W, k, k, s, s, p, p)
+
+
+# (layer, bits, agp, dtype, spread of the group ranges)
+CASES = [
+    # Lines of 256 rows: whole samples, tiles that meet several samples (100, 12 and 4 pixels a
+    # sample), ragged channels and rows, every code width; nearly all groups pruned (spread 6).
+    (_conv(64, 8, 130, 32, 32, 3, 1, 1), 4, 0, "f32", 1.5),
+    (_conv(250, 5, 170, 10, 10, 3, 1, 1), 2, 0, "bf16", 1.5),
+    (_conv(701, 3, 520, 3, 4, 3, 1, 1), 8, 0, "f32", 1.0),
+    (_conv(1001, 4, 1020, 2, 2, 3, 1, 1), 3, 0, "bf16", 1.5),
+    (_conv(70, 6, 65, 40, 36, 3, 1, 1), 1, 2, "f32", 1.0),
+    (_conv(64, 8, 128, 64, 64, 3, 2, 1), 1, 0, "bf16", 1.5),
+    (_conv(96, 8, 128, 28, 28, 3, 1, 1), 6, 0, "f32", 6.0),
+    (_conv(66, 9, 70, 34, 34, 1, 1, 0), 2, 1, "f32", 2.0),
+]
+
+
+@pytest.mark.parametrize("layer,bits,agp,dtype,spread", CASES)
+def test_layer_matches_the_entries(layer, bits, agp, dtype, spread):
+    from paper_2408_14267_amd import fqt
+    print(f"[gpu layer codes] {layer} b={bits} agp={agp} {dtype}", flush=True)
+    sys.stdout.flush()
+    g = torch.Generator(device="cuda").manual_seed(8)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    ones = (1,) * (len(layer.dy_shape) - 2)
+    dy = normal(*layer.dy_shape) * torch.exp(spread * normal(layer.N)).view(layer.N, 1, *ones)
+    dy = (dy * torch.exp(spread * normal(layer.D)).view(1, layer.D, *ones)).to(td)
+    x, w = normal(*layer.x_shape).to(td), normal(*layer.w_shape)
+    dt = fqt.dtype_code(dtype)
+    desc = fqt.layer_desc(layer, dt, dt, fqt.FQT_F32, dt)
+    cfg = fqt.quant_cfg(bits, agp, 17, 3, 2)
+    q = fqt.QGrad(desc, cfg)
+    fqt.fqt_agp_scq_quantize(desc, cfg, dy, q, fqt.workspace(desc, cfg, fqt.FQT_WS_QUANTIZE))
+    K, R = layer.C * layer.kh * layer.kw, layer.N * layer.Ho * layer.Wo
+    xs = torch.empty((R + 63) // 64 * K, dtype=torch.int64, device="cuda")
+    wsb = torch.empty(K * 64 * ((layer.D + 63) // 64), dtype=torch.int8, device="cuda")
+    wsum = torch.empty(K, dtype=torch.int32, device="cuda")
+    fqt.fqt_pack_input_signs(desc, x, xs)
+    fqt.fqt_pack_weight_signs(desc, w, wsb, wsum)
+    dx, dw = torch.empty_like(x), torch.empty_like(w)
+    fqt.fqt_binary_products(desc, cfg, q, xs, wsb, wsum, dx, dw,
+                            fqt.workspace(desc, cfg, fqt.FQT_WS_GEMM_DW))
+    ws = torch.full((fqt.fqt_workspace_size(desc, cfg),), 0xAB, dtype=torch.uint8, device="cuda")
+    fqt.fqt_workspace_init(ws)
+    dx2, dw2 = torch.full_like(x, 7.0), torch.full_like(w, 7.0)
+    for _ in range(2):
+        fqt.fqt_layer_backward(desc, cfg, x, w, dy, dx2, dw2, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(dx2, dx), "dX"
+        assert torch.equal(dw2, dw), "dW"
+    assert torch.count_nonzero(dw).item() > 0
