@@ -363,62 +363,123 @@ __global__ __launch_bounds__(THREADS) void k_stats(const void *__restrict__ dy, 
   }
 }
 
-// Large maps (Ho*Wo >= 1024): the (min, max) key of every (sample, channel) plane of dY,
-// each a contiguous run of P elements, streamed by one wave with 8 quads per lane in
-// flight; ppl[n * D + d].  A sample's key is the reduction of its D planes, a channel's of
-// its N planes.
-constexpr int PLANE_U = 8;
+// Larger maps (Ho*Wo >= 256, whole quads): a wave streams channel planes of one sample, the four
+// waves of a block the same channels of four samples; lanes keep float minima and maxima (one
+// v_min3 / v_max3 per two elements: with the integer keys of the tile form, formed per element,
+// the VALU took as long as the memory), a sample's over the wave's channels, a channel's met over
+// the block in LDS, and both merge into the group keys by atomics.  Batches of LINE_U quads per
+// lane are double-buffered.  Grid: segments of the planes (where planes are few) x sample
+// groups x channel groups of cpw channels, the channel groups fastest.
+constexpr int LINE_U = 4, LINE_MAX_CPW = 16;
+struct LineGeom {
+  uint32_t N, D, P4, cpw, cgroups, sgroups, seg;   // seg: quads per segment, a multiple of 64 LINE_U
+  FastDiv divCg, divSg;
+};
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
 template <int DT, bool TR>
-__global__ __launch_bounds__(256) void k_stats_planes(const void *__restrict__ dy,
-                                                      uint32_t planes, uint32_t P4,
-                                                      int2 *__restrict__ ppl, uint32_t D,
-                                                      StatsTrain tr) {
-  constexpr int U = TR ? PLANE_U / 2 : PLANE_U;      // (two tensors stream in training)
+__global__ __launch_bounds__(256) void k_stats_lines(const void *__restrict__ dy, LineGeom g,
+                                                     uint2 *__restrict__ mks,
+                                                     uint2 *__restrict__ mkc, StatsTrain tr) {
+  __shared__ int32_t clo[4][LINE_MAX_CPW], chi[4][LINE_MAX_CPW];
+  __shared__ float cg[4][LINE_MAX_CPW];
   const int lane = threadIdx.x & 63;
-  const uint32_t nwaves = gridDim.x * 4;
-  for (uint32_t pl = blockIdx.x * 4 + (threadIdx.x >> 6); pl < planes; pl += nwaves) {
-    int lo = INT_MAX, hi = INT_MIN;
-    const int64_t base = int64_t(pl) * P4 * 4;
-    const float gam = TR ? tr.gamma[pl % D] : 1.0f;
-    float gsum = 0.0f;
-    auto take = [&](float (&v)[4], const int4 &iv, bool in) {
-      if (TR) gsum = dot4(v, in ? iv : make_int4(0, 0, 0, 0), gsum);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t rest = fdiv(blockIdx.x, g.divCg), cgrp = blockIdx.x - rest * g.cgroups;
+  const uint32_t sgm = fdiv(rest, g.divSg), n = 4 * (rest - sgm * g.sgroups) + wave;
+  const uint32_t d0 = cgrp * g.cpw, nc = min(g.cpw, g.D - d0);
+  const uint32_t q0 = sgm * g.seg, q1 = min(g.P4, q0 + g.seg);
+  const uint32_t rep = (blockIdx.x % MKEY_REP) * MKEY_GROUPS;
+  if (n < g.N) {
+    const float inf = __builtin_inff();
+    float slo = inf, shi = -inf, lo = inf, hi = -inf, gsum = 0.0f;
+    float xa[LINE_U][4], xb[LINE_U][4];
+    int4 ia[TR ? LINE_U : 1], ib[TR ? LINE_U : 1];
+    // Quad q of channel c; a quad past the segment repeats its last one (which changes no
+    // minimum or maximum, and is not summed).
+    auto load = [&](uint32_t c, uint32_t qb, float (&x)[LINE_U][4], int4 (&iv)[TR ? LINE_U : 1]) {
+      const int64_t base = (int64_t(n) * g.D + d0 + c) * g.P4;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int key = f2key((TR ? __fmul_rn(v[k], gam) : v[k]) + 0.0f);
-        lo = min(lo, in ? key : INT_MAX);
-        hi = max(hi, in ? key : INT_MIN);
+      for (int u = 0; u < LINE_U; ++u) {
+        const int64_t at = 4 * (base + min(qb + 64 * u + lane, q1 - 1));
+        load_quad<DT>(dy, at, x[u]);
+        if constexpr (TR) iv[u] = *reinterpret_cast<const int4 *>(tr.I + at);
       }
     };
-    // Whole batches (no per-lane test: every load issues before the first use), then the
-    // tail with out-of-plane quads reading element 0 and masked.
-    for (uint32_t qb = 0; qb < P4; qb += 64 * U) {
-      const bool whole = qb + 64 * U <= P4;
-      float v[U][4];
-      int4 iv[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t q = qb + 64 * u + lane;
-        const int64_t at = whole || q < P4 ? base + 4 * int64_t(q) : 0;
-        load_quad<DT>(dy, at, v[u]);
-        if (TR) iv[u] = *reinterpret_cast<const int4 *>(tr.I + at);
+    uint32_t c = 0, qb = q0, cn = 0, qn = q0;        // this batch and the next one
+    auto step = [&](uint32_t &cc, uint32_t &q) {
+      q += 64 * LINE_U;
+      if (q >= q1) {
+        q = q0;
+        ++cc;
       }
-      if (whole) {
+    };
+    float gam = TR ? tr.gamma[d0] : 1.0f;
+    auto take = [&](float (&x)[LINE_U][4], int4 (&iv)[TR ? LINE_U : 1]) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) take(v[u], iv[u], true);
-      } else {
+      for (int u = 0; u < LINE_U; ++u) {
+        if constexpr (TR) {
+          gsum = dot4(x[u], qb + 64 * u + lane < q1 ? iv[u] : make_int4(0, 0, 0, 0), gsum);
 #pragma unroll
-        for (int u = 0; u < U; ++u) take(v[u], iv[u], qb + 64 * u + lane < P4);
+          for (int k = 0; k < 4; ++k) x[u][k] = __fmul_rn(x[u][k], gam);
+        }
+        lo = min3(min3(lo, x[u][0], x[u][1]), x[u][2], x[u][3]);
+        hi = max3(max3(hi, x[u][0], x[u][1]), x[u][2], x[u][3]);
       }
+      const uint32_t was = c;
+      step(c, qb);
+      if (c != was) {                                // the plane's segment is done
+        slo = fminf(slo, lo);
+        shi = fmaxf(shi, hi);
+        // (adding zero turns -0 into +0)
+        const int klo = wave_min(f2key(lo + 0.0f)), khi = wave_max(f2key(hi + 0.0f));
+        if constexpr (TR) gsum = lanes_sum<6>(gsum);
+        if (lane == 0) {
+          clo[wave][was] = klo;
+          chi[wave][was] = khi;
+          if (TR) cg[wave][was] = gsum;
+        }
+        lo = inf;
+        hi = -inf;
+        gsum = 0.0f;
+        if (TR && c < nc) gam = tr.gamma[d0 + c];
+      }
+    };
+    load(cn, qn, xa, ia);
+    step(cn, qn);
+    for (;;) {
+      if (cn < nc) load(cn, qn, xb, ib);
+      __builtin_amdgcn_sched_barrier(0);
+      take(xa, ia);
+      if (cn >= nc) break;
+      step(cn, qn);
+      if (cn < nc) load(cn, qn, xa, ia);
+      __builtin_amdgcn_sched_barrier(0);
+      take(xb, ib);
+      if (cn >= nc) break;
+      step(cn, qn);
     }
-    lo = wave_min(lo);
-    hi = wave_max(hi);
-    if (TR) gsum = lanes_sum<6>(gsum);
-    if (lane == 0) {
-      ppl[pl] = make_int2(lo, hi);
-      if (TR) tr.part[pl] = gsum;                    // [N][D]
-    }
+    const int klo = wave_min(f2key(slo + 0.0f)), khi = wave_max(f2key(shi + 0.0f));
+    if (lane == 0) merge_key(mks + rep + n, klo, khi);
+  } else if (lane < int(nc)) {
+    clo[wave][lane] = INT_MAX;
+    chi[wave][lane] = INT_MIN;
+    if (TR) cg[wave][lane] = 0.0f;
   }
+  __syncthreads();
+  const uint32_t t = threadIdx.x;
+  if (t >= nc) return;
+  merge_key(mkc + rep + d0 + t, min(min(clo[0][t], clo[1][t]), min(clo[2][t], clo[3][t])),
+            max(max(chi[0][t], chi[1][t]), max(chi[2][t], chi[3][t])));
+  if (TR) tr.part[size_t(rest) * g.D + d0 + t] = (cg[0][t] + cg[1][t]) + (cg[2][t] + cg[3][t]);
 }
 
 // Large group sets: block b < N reduces sample b over its slots, block N + d channel d
@@ -488,8 +549,7 @@ struct SetArgs {
   uint32_t slots;      // 0: group g reduces part[u * ld + g], u < U (channels)
                        // 1: sample slots of part_s (P, nrt, SL, ndt)
                        // 2: key[g] already holds the group's key (k_stats_reduce ran)
-                       // 3: group g reduces part[g * ld + u], u < U (per-plane partials)
-                       // 4: key[r * MKEY_GROUPS + g], r < MKEY_REP, are the group's merged
+                       // 3: key[r * MKEY_GROUPS + g], r < MKEY_REP, are the group's merged
                        //    key replicas (cleared once read)
   uint32_t U, ld;
   uint32_t P, nrt, SL, ndt;
@@ -944,7 +1004,7 @@ __device__ __forceinline__ void select_fused_body(const SelectArgs &a, int set) 
         lo = k.x;
         hi = k.y;
       }
-    } else if (S.slots == 4) {          // merged keys, left zero for the next call
+    } else if (S.slots == 3) {          // merged keys, left zero for the next call
       if (g < G) {
         uint2 *mk = reinterpret_cast<uint2 *>(const_cast<int2 *>(S.key));
         uint2 u[(MKEY_REP + SPLIT - 1) / SPLIT];
@@ -973,22 +1033,6 @@ __device__ __forceinline__ void select_fused_body(const SelectArgs &a, int set) 
         for (int k = 0; k < 16; ++k) {
           const uint32_t u = u0 + k * SPLIT;
           v[k] = load8(prs, u < S.U ? voff : BUF_NONE, u < S.U ? u * S.ld * 8 : 0);
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          if (u0 + k * SPLIT >= S.U) break;
-          lo = min(lo, int(uint32_t(v[k])));
-          hi = max(hi, int(uint32_t(v[k] >> 32)));
-        }
-      }
-    } else if (g < G && S.slots == 3) { // group g reduces part[g * ld + u], u < U
-      const __amdgpu_buffer_rsrc_t prs = buffer_of(S.part, uint32_t(S.G) * S.ld * 8);
-      for (uint32_t u0 = r0; u0 < S.U; u0 += 16 * SPLIT) {
-        uint64_t v[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const uint32_t u = u0 + k * SPLIT;
-          v[k] = load8(prs, u < S.U ? (uint32_t(g) * S.ld + u) * 8 : BUF_NONE, 0);
         }
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
@@ -1774,9 +1818,32 @@ int64_t stats_row_blocks(const Layer &L) {
   return (L.Wr + rs - 1) / rs;
 }
 
-// Partial sums of dgamma: one row per row block of the statistics, or per sample (planes).
+// Line statistics: channels per wave for about 4096 waves, and planes cut into segments (at
+// least two batches each) where even one channel per wave gives fewer than 2048.
+bool line_geom(const Layer &L, LineGeom *g) {
+  if (L.P < 256 || L.P % 4 || L.N > 1024 || L.D > 1024) return false;
+  g->N = uint32_t(L.N); g->D = uint32_t(L.D); g->P4 = uint32_t(L.P / 4);
+  g->cpw = uint32_t(std::min<int64_t>(LINE_MAX_CPW, std::max<int64_t>(1, L.N * L.D / 4096)));
+  g->cgroups = (g->D + g->cpw - 1) / g->cpw;
+  g->sgroups = (g->N + 3) / 4;
+  const uint32_t batch = 64 * LINE_U, batches = (g->P4 + batch - 1) / batch;
+  const uint32_t want = 2048 / (g->cgroups * std::min<uint32_t>(g->N, 4 * g->sgroups)) + 1;
+  const uint32_t segs = std::max(1u, std::min(want, batches / 2));
+  g->seg = (batches + segs - 1) / segs * batch;
+  g->divCg = make_fastdiv(g->cgroups);
+  g->divSg = make_fastdiv(g->sgroups);
+  return true;
+}
+uint32_t line_parts(const Layer &, const LineGeom &g) {   // (segment, sample group) pairs
+  return g.sgroups * ((g.P4 + g.seg - 1) / g.seg);
+}
+
+// Partial sums of dgamma: one row per row block of the statistics, or per segment and sample
+// group of the lines.
 size_t train_part_bytes(const Layer &L) {
-  return size_t(std::max(stats_row_blocks(L), L.N)) * size_t(L.D) * 4;
+  LineGeom g;
+  const int64_t parts = line_geom(L, &g) ? int64_t(line_parts(L, g)) : stats_row_blocks(L);
+  return size_t(parts) * size_t(L.D) * 4;
 }
 
 int launch_state_clear(void *state, hipStream_t s) {
@@ -1799,22 +1866,24 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   const StatsGeom sg{g, nrt, stats_slots(L), stats_rows_per_block(L), chan_fast, ndt};
   const dim3 grid = chan_fast ? dim3(ndt, nrb) : dim3(nrb, ndt);
   const int64_t gmax = L.N > L.D ? L.N : L.D;
-  // Large maps with both group sets in one-workgroup selections: per-plane statistics
-  // (part_c holds the N * D plane keys: it has D * stats_row_blocks >= D * N entries).
-  const bool planes = L.P >= 1024 && L.P % 4 == 0 && gmax <= 1024;
+  // Maps of 256 pixels and more with both group sets in one-workgroup selections: line
+  // statistics (below, planes leave most lanes of a batch idle; k_stats at 14 x 14 x 512 x 64
+  // took 11.7 us).
+  LineGeom lg;
+  const bool planes = line_geom(L, &lg);
   // The one-workgroup selection reduces the partials itself; with many partials per group
   // (large N*Ho*Wo) a workgroup per group reduces them first.  With few partials per group
   // the statistics merge the keys with atomics instead (the selection then reads one key
   // per group).
   const bool many_partials =
       !planes && (nrb > 256 || int64_t(ndt) * ((L.P + TILE - 1) / TILE + 1) > 256);
-  const bool merged = !planes && !many_partials && gmax <= 1024;
+  const bool merged = planes || (!many_partials && gmax <= 1024);
   uint2 *mks = merged ? w.mkeys : nullptr;
   uint2 *mkc = merged ? w.mkeys + L.N : nullptr;
   StatsTrain st_train{};
   if (train) {
     st_train = StatsTrain{train->gamma, train->I, train->part};
-    train->parts = planes ? uint32_t(L.N) : nrb;
+    train->parts = planes ? line_parts(L, lg) : nrb;
   }
   // Calls f<DT, TR>: the training form is float32.
   auto by_type = [&](auto &&f) {
@@ -1823,11 +1892,10 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
     else f.template operator()<FQT_F32, false>();
   };
   if (planes) {
-    const uint32_t np = uint32_t(L.N * L.D);
-    const uint32_t blocks = std::min<uint32_t>((np + 3) / 4, 4096);
+    const dim3 lines(lg.cgroups * line_parts(L, lg));
     by_type([&]<int DT, bool TR>() {
-      hipLaunchKernelGGL((k_stats_planes<DT, TR>), dim3(blocks), dim3(256), 0, s, dY, np,
-                         uint32_t(L.P / 4), w.part_c, uint32_t(L.D), st_train);
+      hipLaunchKernelGGL((k_stats_lines<DT, TR>), lines, dim3(256), 0, s, dY, lg, mks, mkc,
+                         st_train);
     });
   } else by_type([&]<int DT, bool TR>() {
     if (mode == TILE_PIX)
@@ -1851,14 +1919,9 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
                       q.pcq_scale, q.pcq_offset, q.pcq_prob, w.cp, w.cslot};
   sa.bits = cfg.bits; sa.mode = cfg.agp_mode; sa.seed = cfg.seed; sa.step = cfg.step;
   sa.layer = cfg.layer_id;
-  if (planes) {
-    sa.set[0].slots = 3; sa.set[0].part = w.part_c; sa.set[0].U = uint32_t(L.D);
-    sa.set[0].ld = uint32_t(L.D);
-    sa.set[1].slots = 0; sa.set[1].U = uint32_t(L.N); sa.set[1].ld = uint32_t(L.D);
-  }
   if (merged) {
-    sa.set[0].slots = 4; sa.set[0].key = reinterpret_cast<const int2 *>(mks);
-    sa.set[1].slots = 4; sa.set[1].key = reinterpret_cast<const int2 *>(mkc);
+    sa.set[0].slots = 3; sa.set[0].key = reinterpret_cast<const int2 *>(mks);
+    sa.set[1].slots = 3; sa.set[1].key = reinterpret_cast<const int2 *>(mkc);
   }
   int st;
   if (gmax <= 1024 && many_partials) {
