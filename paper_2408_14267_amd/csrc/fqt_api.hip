@@ -32,6 +32,9 @@ struct LayerWs {
   int8_t *wsb;
   int32_t *wlsum;
   void *dw_ws;
+  char *arena;
+  bool taps_on;
+  TapsPlan taps;
 };
 
 void carve_quant_ws(Carver *c, const Layer &L, QuantWs *q) {
@@ -66,10 +69,14 @@ size_t carve_layer_ws(void *ws, const Layer &L, const fqt_quant_cfg &cfg, LayerW
   w.q.pcq_scale = c.take<float>(L.D);
   w.q.pcq_offset = c.take<float>(L.D);
   w.q.pcq_prob = c.take<float>(L.D);
-  w.xsign = c.take<uint64_t>(size_t(L.K) * L.Wr);
   w.wsb = c.take<int8_t>(size_t(L.K) * L.Wd * 64);
   w.wlsum = c.take<int32_t>(L.K);
+  // The im2col of the signs and the split partials, or the buffers of the tap form.
+  const size_t arena_at = c.off;
+  w.xsign = c.take<uint64_t>(size_t(L.K) * L.Wr);
   w.dw_ws = c.take<char>(gemm_dw_ws_bytes(L, cfg));
+  w.arena = reinterpret_cast<char *>(w.xsign);
+  w.taps_on = taps_plan(L, cfg, c.off - arena_at, &w.taps);
   if (out) *out = w;
   return c.off;
 }
@@ -449,7 +456,8 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
   carve_layer_ws(ws, L, *cfg, &w);
   // Statistics, then the selection (whose launch also packs the sign operands when the
   // layer allows), the quantizer, both products.
-  SignJob sj{X, W, w.xsign, w.wsb, w.wlsum, false};
+  const TapsPlan *taps = w.taps_on ? &w.taps : nullptr;
+  SignJob sj{X, W, w.xsign, w.wsb, w.wlsum, false, taps, w.arena};
   // The products read the byte codes; the bit planes (the paper's packed form) are left to
   // fqt_agp_scq_quantize callers.
   FQT_TRY(launch_quantize(L, *cfg, dY, w.q, w.qws, s, &sj, false, train));
@@ -463,7 +471,7 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
     FQT_TRY(launch_pack_w_i8(W, L, w.wsb, w.wlsum, s));
   }
   return launch_products(L, *cfg, w.q, w.xsign, w.wsb, w.wlsum, dX, dW, w.dw_ws, w.qws.sslot,
-                         w.qws.cslot, s, train);
+                         w.qws.cslot, s, train, taps, w.arena);
 }
 }  // namespace
 }  // namespace fqt

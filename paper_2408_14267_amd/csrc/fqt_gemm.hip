@@ -1570,7 +1570,7 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
 int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
-                    hipStream_t s, const TrainJob *train) {
+                    hipStream_t s, const TrainJob *train, const TapsPlan *taps, char *arena) {
   if (L.kh * L.kw > DX_MAX_TAPS) return FQT_E_SHAPE;
   DwArgs dwa = make_dw_args(L, cfg, q, xsign, dW, nullptr, dw_ws);
   DxArgs dxa = make_dx_args(L, q, wsb, wlsum, dX, nullptr);
@@ -1579,10 +1579,13 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
   // A large one-split dW runs as its own launch in the 2 x 2-tile form; the products
   // launch then holds only dX blocks.
   // Long split-R contractions likewise run their partials as their own launch.
-  const bool big = dw_big(L, dwa);
+  const bool big = taps || dw_big(L, dwa);
   const bool split_big = !big && dw_split_big(L, dwa);
   const bool kred = !big && !split_big && dw_kred_form(L, dwa.S);
-  if (big) {
+  if (taps) {
+    const int st = launch_dw_taps(L, cfg, *taps, q, arena, cslot, dW, s);
+    if (st != FQT_OK) return st;
+  } else if (big) {
     if (cfg.bits == 8) launch_dw_big<true>(dwa, s);
     else launch_dw_big<false>(dwa, s);
   } else if (split_big) {

@@ -92,6 +92,20 @@ void carve_quant_ws(void *ws, const Layer &L, QuantWs *q);
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
+// Formats of the PCQ codes: fqt_qgrad's, and the two operand orders of the tap form of the dW
+// product (fqt_taps.hip), which only the layer backward uses.
+enum PcqFormat : uint32_t { PCQ_PLAIN = 0, PCQ_TAPS8 = 1, PCQ_TAPS4 = 2 };
+// Layout of that form's buffers in the arena that otherwise holds the im2col of the signs and
+// the split partials: sign plane with its halo, masks, partial sums.
+struct TapsPlan {
+  uint32_t fmt, S, wps, Cp, halo, per;
+  size_t plane_bytes, mask_at, part_at, partT_at;
+};
+bool taps_plan(const Layer &L, const fqt_quant_cfg &cfg, size_t arena, TapsPlan *p);
+int launch_dw_taps(const Layer &L, const fqt_quant_cfg &cfg, const TapsPlan &p,
+                   const fqt_qgrad &q, char *arena, const float2 *slot_sz, float *dW,
+                   hipStream_t s);
+
 // Launchers (stream-ordered, no synchronisation).  They return an fqt_status.
 // The sign operands of the products, packed in spare blocks of the selection launch when
 // the layer allows it (launch_quantize then sets *done).
@@ -101,6 +115,8 @@ struct SignJob {
   int8_t *wsb;           // sign(W) bytes
   int32_t *wlsum;
   bool done;
+  const TapsPlan *taps;  // the sign plane of the tap form instead of xsign, at `arena`
+  char *arena;
 };
 // What a training step adds around the layer backward (float32 layers; fqt_train.h): the
 // quantized gradient is dH * gamma (formed where dH is read), dgamma = sum dH * I (partial sums
@@ -135,7 +151,8 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
 int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
-                    hipStream_t s, const TrainJob *train = nullptr);
+                    hipStream_t s, const TrainJob *train = nullptr,
+                    const TapsPlan *taps = nullptr, char *arena = nullptr);
 
 // The dW product from the code planes and line-major sign bits (popcount or fp4 engine).
 size_t engine_ws_bytes(const Layer &L, const fqt_quant_cfg &cfg, int engine);

@@ -1347,8 +1347,9 @@ __global__ __launch_bounds__(SEL_NT) void k_select_fused(SelectArgs a) {
 // im2col of X, in one of three forms: bit-level (block order of bit_im2col_body), through
 // the band (word group fastest, then 64-channel groups), or a wave per 64 positions of
 // IM2COL_CPW channels (any convolution; work items in wave order); for a linear layer the
-// sign words of X down its rows (a wave per work item of rows_wave_body).
-enum SignForm { SIGN_BITS = 0, SIGN_BAND = 1, SIGN_WAVE = 2, SIGN_ROWS = 3 };
+// sign words of X down its rows (a wave per work item of rows_wave_body); for the tap form of
+// the dW product the sign plane of X (no im2col) and its masks.
+enum SignForm { SIGN_BITS = 0, SIGN_BAND = 1, SIGN_WAVE = 2, SIGN_ROWS = 3, SIGN_PLANE = 4 };
 constexpr uint32_t SIGN_IPB = 4;     // work items per workgroup of the wave and rows forms
 struct SignArgs {
   const void *x;
@@ -1364,6 +1365,9 @@ struct SignArgs {
   int32_t *wlsum;
   uint32_t npw;
   uint32_t ipb;          // work items per workgroup of the wave and rows forms (waves past it idle)
+  PlaneGeom pl;          // the plane form: its first mblocks blocks write the masks
+  uint32_t *plane;
+  uint4 *masks;
 };
 // DT: dtype of X; WDT: dtype of W; KH, KW: the kernel size of the band and wave forms
 // (0: read from the geometry).
@@ -1384,6 +1388,12 @@ __global__ __launch_bounds__(SEL_NT) __attribute__((amdgpu_waves_per_eu(8))) voi
     const uint32_t f = b - 2 - sg.npw;
     const uint32_t cb = fdiv(f, sg.divNwb);
     band_im2col_body<DT, KH, KW, SEL_NT>(sg.x, sg.bg, sg.xsign, f - cb * sg.nwb, cb, band);
+  } else if constexpr (FORM == SIGN_PLANE) {
+    const uint32_t f = b - 2 - sg.npw;
+    if (f < sg.pl.mblocks) plane_mask_body(sg.pl, sg.masks, f * SEL_NT + threadIdx.x);
+    else plane_wave_body<DT>(sg.x, sg.pl, sg.plane,
+                             (f - sg.pl.mblocks) * SEL_NW +
+                                 __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
   } else {
     // Work items spread over workgroups: a CU's address unit, not the memory latency, bounds
     // these gathers when one workgroup takes sixteen waves of them.
@@ -1446,6 +1456,7 @@ struct QPackArgs {
   uint32_t chan_fast;   // grid x walks the channel tiles (rows of dY read as long runs)
   uint32_t planes;      // 1: also write the bit planes (0: the byte codes only)
   const float *gamma;   // training: the gradient is dy * gamma[d]
+  uint32_t pcq_fmt;     // PcqFormat (k_qpack_lines)
 };
 
 // Codes of a thread's quads into the LDS tiles.  The four codes of a quad share one
@@ -1670,6 +1681,22 @@ __device__ __forceinline__ uint32_t code_bytes(uint32_t a, uint32_t b, uint32_t 
   return ~(__builtin_amdgcn_perm(b, a, 0x0c0c0703u) | __builtin_amdgcn_perm(d, c, 0x07030c0cu));
 }
 
+// A line's codes in the operand orders of the tap form (fqt_taps.hip): bytes of the four lanes
+// of one parity among eight (32 positions) transposed as a 4 x 4 matrix, so that lane l of the
+// eight holds dword l / 2 of half-wave l % 2; as nibbles, both parities' dwords merged and
+// turned to e2m1 (0, 1, 2, 3 -> 0, 2, 4, 5).
+__device__ __forceinline__ uint32_t taps_transpose(uint32_t word, int lane) {
+  const uint32_t y = lane_xor<4>(word);
+  const uint32_t r = __builtin_amdgcn_perm(y, word, (lane & 4) ? 0x03020706u : 0x05040100u);
+  const uint32_t z = lane_xor<2>(r);
+  return __builtin_amdgcn_perm(z, r, (lane & 2) ? 0x03070105u : 0x06020400u);
+}
+__device__ __forceinline__ uint32_t taps_nibbles(uint32_t t) {   // valid in even lanes
+  const uint32_t q = t | (lane_xor<1>(t) << 4);
+  const uint32_t hi = q & 0x22222222u, lo = q & 0x11111111u;
+  return (hi << 1) | ((lo << 1) & ~hi) | (lo & (hi >> 1));
+}
+
 // Grid: ceil(R / 256) x ceil(D / 64) blocks; wave w takes channels d0 + 16 w .. + 15, lane l
 // rows r0 + 4 l .. + 3 (a quad of one sample).  PCQ codes leave from registers (8 lanes fill a
 // 32-byte chunk of a line), PSQ codes through LDS, where row 4 l + k lies in slot 64 k + l.
@@ -1705,7 +1732,12 @@ __global__ __launch_bounds__(QL_THREADS) void k_qpack_lines(QPackArgs a) {
     return;                                 // (such a block has no PSQ rows either)
   }
   const bool in_line = r < a.Wr * 64;       // rows past R to the end of the last word hold 0
-  uint8_t *pc = a.pcq_codes + (size_t(r >> 5) * g.D) * 32 + (r & 31);
+  // This lane's dword of a kept line: chunk [r / 32][D][32], or [r / 64][D][32] of nibbles.
+  const bool nibbles = a.pcq_fmt == PCQ_TAPS4;
+  uint8_t *pc = a.pcq_codes + size_t(nibbles ? r >> 6 : r >> 5) * g.D * 32 +
+                (a.pcq_fmt == PCQ_PLAIN ? r & 31
+                 : 4 * ((lane >> 1) & 3) + 16 * (nibbles ? (r >> 5) & 1 : lane & 1));
+  const bool pcq_lane = in_line && !(nibbles && (lane & 1));
 
   float x[2][4][4];
   auto load = [&](int grp, float (&v)[4][4]) {
@@ -1749,8 +1781,12 @@ __global__ __launch_bounds__(QL_THREADS) void k_qpack_lines(QPackArgs a) {
         uint32_t q[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) q[k] = code_top<BM>(xv[k], z, inv, Bf, u.v[k]);
-        const uint32_t word = code_bytes(q[0], q[1], q[2], q[3]);
-        if (in_line) *reinterpret_cast<uint32_t *>(pc + size_t(rank) * 32) = valid ? word : 0u;
+        uint32_t word = valid ? code_bytes(q[0], q[1], q[2], q[3]) : 0u;
+        if (a.pcq_fmt != PCQ_PLAIN) {
+          word = taps_transpose(word, lane);
+          if (nibbles) word = taps_nibbles(word);
+        }
+        if (pcq_lane) *reinterpret_cast<uint32_t *>(pc + size_t(rank) * 32) = word;
       }
     }
     if (any_s) {
@@ -1943,18 +1979,28 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   const int gp = gmax <= 256 ? 256 : 1024;
   const size_t lds_left = 65536 - 512 - select_signs_static_lds(gp);
   const bool sign_ok = signs && gmax <= 1024;
-  const bool with_bits = sign_ok && bit_geom(L, SEL_NT, 448, lds_left, &bt, &sign_lds);
-  const bool with_band = sign_ok && !with_bits && L.x_t == L.w_t &&
+  const bool with_plane = sign_ok && signs->taps;
+  const bool with_bits = sign_ok && !with_plane && bit_geom(L, SEL_NT, 448, lds_left, &bt, &sign_lds);
+  const bool with_band = sign_ok && !with_plane && !with_bits && L.x_t == L.w_t &&
                          band_geom(L, signs->X, L.x_t, SEL_NT, lds_left, &bg, &sign_lds);
-  const bool with_wave = sign_ok && !with_bits && !with_band && L.kind == FQT_CONV2D;
+  const bool with_wave = sign_ok && !with_plane && !with_bits && !with_band && L.kind == FQT_CONV2D;
   const bool with_rows = sign_ok && L.kind == FQT_LINEAR;
-  if (with_bits || with_band || with_wave || with_rows) {
+  if (with_plane || with_bits || with_band || with_wave || with_rows) {
     SignArgs sg{};
     sg.x = signs->X; sg.xsign = signs->xsign;
     sg.w = signs->W; sg.pg = pack_w_geom(L); sg.wsb = signs->wsb; sg.wlsum = signs->wlsum;
     sg.npw = pack_w_blocks(L);
     uint32_t xblocks;
-    if (with_bits) {
+    if (with_plane) {
+      const TapsPlan &tp = *signs->taps;
+      sg.pl = PlaneGeom{uint32_t(L.C), uint32_t(L.P), uint32_t(L.R), uint32_t(L.Wr),
+                        uint32_t(L.W), uint32_t(L.H), tp.per, (tp.per + SEL_NT - 1) / SEL_NT,
+                        make_fastdiv(uint32_t(L.P)), make_fastdiv(uint32_t(L.Wr)),
+                        make_fastdiv(uint32_t(L.W))};
+      sg.plane = reinterpret_cast<uint32_t *>(signs->arena) + size_t(tp.halo) * L.C;
+      sg.masks = reinterpret_cast<uint4 *>(signs->arena + tp.mask_at);
+      xblocks = sg.pl.mblocks + uint32_t((L.Wr * ((L.C + 63) / 64) + SEL_NW - 1) / SEL_NW);
+    } else if (with_bits) {
       bit_geom_vec(&bt, signs->X);
       sg.bt = bt;
       xblocks = bit_blocks(bt);
@@ -1991,7 +2037,8 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
           hipLaunchKernelGGL((k_select_signs<GPT, DT, FORM, KH, KW>), grid, dim3(SEL_NT),
                              sign_lds, s, sa, sg);
         };
-        if (with_rows) launch.template operator()<SIGN_ROWS, 0, 0>();
+        if (with_plane) launch.template operator()<SIGN_PLANE, 0, 0>();
+        else if (with_rows) launch.template operator()<SIGN_ROWS, 0, 0>();
         else if (with_bits) launch.template operator()<SIGN_BITS, 0, 0>();
         else if (with_band && L.kh == 3 && L.kw == 3) launch.template operator()<SIGN_BAND, 3, 3>();
         else if (with_band && L.kh == 1 && L.kw == 1) launch.template operator()<SIGN_BAND, 1, 1>();
@@ -2042,7 +2089,9 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   qa.planes = write_planes ? 1u : 0u;
   qa.gamma = train ? train->gamma : nullptr;
   const uint32_t lblocks = uint32_t((L.R + QL_ROWS - 1) / QL_ROWS);
-  if (mode == TILE_PIX && !write_planes && int64_t(lblocks) * ndt >= QL_MIN_BLOCKS) {
+  qa.pcq_fmt = signs && signs->taps ? signs->taps->fmt : uint32_t(PCQ_PLAIN);
+  if (mode == TILE_PIX && !write_planes &&
+      (qa.pcq_fmt != PCQ_PLAIN || int64_t(lblocks) * ndt >= QL_MIN_BLOCKS)) {
     const dim3 lgrid(lblocks, ndt);
     by_type([&]<int DT, bool TR>() {
       if (cfg.bits == 1)

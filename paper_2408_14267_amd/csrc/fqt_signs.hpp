@@ -599,6 +599,65 @@ __device__ __forceinline__ void pack_w_body(const void *__restrict__ w, const Pa
   if (t < 64 && l0 + t < g.K) lsum[l0 + t] = 2 * sm.pos[t] - int(g.D);
 }
 
+// ----------------------------------------------------------------------------- sign plane
+// sign(X) once per element for the tap form of the dW product (stride 1, same padding: input
+// and output positions are the same): dword m of channel c (positions 32 m ..) at m C + c.  A
+// wave takes 64 positions x 64 channels: lanes load a channel's 64 positions, the compare's
+// lane mask is the word, and lane c collects channel c's (v_writelane), so that each dword row
+// is stored in one piece.
+struct PlaneGeom {
+  uint32_t C, P, R, Wr, W, H, per, mblocks;
+  FastDiv divP, divWr, divW;
+};
+constexpr int PLANE_BATCH = 16;      // channels loaded back to back
+
+template <int DT>
+__device__ __forceinline__ void plane_wave_body(const void *__restrict__ x, const PlaneGeom &g,
+                                                uint32_t *__restrict__ dst, uint32_t item) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t cg = fdiv(item, g.divWr), w = item - cg * g.Wr, c0 = cg * 64;
+  if (c0 >= g.C) return;
+  const uint32_t r = w * 64 + uint32_t(lane);
+  const bool in = r < g.R;
+  const uint32_t n = fdiv(in ? r : 0, g.divP), p = (in ? r : 0) - n * g.P;
+  const int64_t at = (int64_t(n) * g.C + c0) * g.P + p;
+  const uint32_t nc = min(64u, g.C - c0);
+  uint32_t lo = 0, hi = 0;
+  for (uint32_t b = 0; b < nc; b += PLANE_BATCH) {
+    float v[PLANE_BATCH];
+#pragma unroll
+    for (int k = 0; k < PLANE_BATCH; ++k)
+      v[k] = load_elem<DT>(x, at + int64_t(min(b + k, nc - 1)) * g.P);
+#pragma unroll
+    for (int k = 0; k < PLANE_BATCH; ++k) {
+      const uint64_t m = __ballot(in && v[k] > 0.0f);
+      lo = writelane(uint32_t(m), int(b + k), lo);
+      hi = writelane(uint32_t(m >> 32), int(b + k), hi);
+    }
+  }
+  if (uint32_t(lane) < nc) {
+    dst[size_t(2 * w) * g.C + c0 + lane] = lo;
+    dst[size_t(2 * w + 1) * g.C + c0 + lane] = hi;
+  }
+}
+
+// Masks of the positions of dword m (m < per, the period of the image in dwords): bits whose
+// row above, row below, column to the left and to the right are inside the image.
+__device__ __forceinline__ void plane_mask_body(const PlaneGeom &g, uint4 *__restrict__ masks,
+                                                uint32_t m) {
+  if (m >= g.per) return;
+  uint4 v = make_uint4(0u, 0u, 0u, 0u);
+  for (uint32_t b = 0; b < 32; ++b) {
+    const uint32_t q = m * 32 + b, p = q - fdiv(q, g.divP) * g.P;
+    const uint32_t h = fdiv(p, g.divW), c = p - h * g.W;
+    v.x |= (h > 0 ? 1u : 0u) << b;
+    v.y |= (h + 1 < g.H ? 1u : 0u) << b;
+    v.z |= (c > 0 ? 1u : 0u) << b;
+    v.w |= (c + 1 < g.W ? 1u : 0u) << b;
+  }
+  masks[m] = v;
+}
+
 inline PackWGeom pack_w_geom(const Layer &L) {
   const uint32_t taps = uint32_t(L.kh * L.kw);
   return PackWGeom{uint32_t(L.D), uint32_t(L.K), uint32_t(L.Wd * 64), uint32_t(L.C), taps,

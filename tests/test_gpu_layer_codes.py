@@ -26,6 +26,14 @@ CASES = [
     (_conv(64, 8, 128, 64, 64, 3, 2, 1), 1, 0, "bf16", 1.5),
     (_conv(96, 8, 128, 28, 28, 3, 1, 1), 6, 0, "f32", 6.0),
     (_conv(66, 9, 70, 34, 34, 1, 1, 0), 2, 1, "f32", 2.0),
+    # The tap form of dW (3 x 3, at least 768 words): both code formats, rows whose length is and
+    # is not a multiple of 32, a ragged last word, one to three channel and slot blocks.
+    (_conv(65, 40, 70, 30, 26, 3, 1, 1), 2, 0, "bf16", 1.5),
+    (_conv(13, 33, 40, 66, 62, 3, 1, 1), 8, 2, "f32", 1.0),
+    (_conv(2, 5, 20, 224, 224, 3, 1, 1), 2, 2, "f32", 1.0),
+    (_conv(13, 70, 200, 64, 64, 3, 1, 1), 1, 2, "bf16", 1.0),
+    (_conv(13, 65, 150, 64, 64, 3, 1, 1), 3, 2, "f32", 1.0),
+    (_conv(800, 3, 80, 1, 64, 3, 1, 1), 5, 0, "f32", 1.0),
 ]
 
 
