@@ -1390,10 +1390,15 @@ __global__ __launch_bounds__(SEL_NT) __attribute__((amdgpu_waves_per_eu(8))) voi
     band_im2col_body<DT, KH, KW, SEL_NT>(sg.x, sg.bg, sg.xsign, f - cb * sg.nwb, cb, band);
   } else if constexpr (FORM == SIGN_PLANE) {
     const uint32_t f = b - 2 - sg.npw;
-    if (f < sg.pl.mblocks) plane_mask_body(sg.pl, sg.masks, f * SEL_NT + threadIdx.x);
-    else plane_wave_body<DT>(sg.x, sg.pl, sg.plane,
-                             (f - sg.pl.mblocks) * SEL_NW +
-                                 __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    if (f < sg.pl.mblocks)
+      plane_mask_body(sg.pl, sg.masks, f * SEL_NT + threadIdx.x);
+    else if (sg.pl.vec)
+      plane_tile_body<DT, SEL_NT>(sg.x, sg.pl, sg.plane, f - sg.pl.mblocks,
+                                  reinterpret_cast<uint32_t (*)[65]>(band));
+    else
+      plane_wave_body<DT>(sg.x, sg.pl, sg.plane,
+                          (f - sg.pl.mblocks) * SEL_NW +
+                              __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
   } else {
     // Work items spread over workgroups: a CU's address unit, not the memory latency, bounds
     // these gathers when one workgroup takes sixteen waves of them.
@@ -1993,13 +1998,17 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
     uint32_t xblocks;
     if (with_plane) {
       const TapsPlan &tp = *signs->taps;
+      const bool vec = L.P % 8 == 0 && aligned(signs->X, 16);
+      const uint32_t tiles = uint32_t(vec ? (L.Wr * 64 + PLANE_TILE - 1) / PLANE_TILE : L.Wr);
       sg.pl = PlaneGeom{uint32_t(L.C), uint32_t(L.P), uint32_t(L.R), uint32_t(L.Wr),
-                        uint32_t(L.W), uint32_t(L.H), tp.per, (tp.per + SEL_NT - 1) / SEL_NT,
-                        make_fastdiv(uint32_t(L.P)), make_fastdiv(uint32_t(L.Wr)),
+                        uint32_t(L.W), uint32_t(L.H), tp.per, tp.per / SEL_NT + 1, vec ? 1u : 0u,
+                        make_fastdiv(uint32_t(L.P)), make_fastdiv(tiles),
                         make_fastdiv(uint32_t(L.W))};
       sg.plane = reinterpret_cast<uint32_t *>(signs->arena) + size_t(tp.halo) * L.C;
       sg.masks = reinterpret_cast<uint4 *>(signs->arena + tp.mask_at);
-      xblocks = sg.pl.mblocks + uint32_t((L.Wr * ((L.C + 63) / 64) + SEL_NW - 1) / SEL_NW);
+      const uint64_t items = uint64_t(tiles) * ((L.C + 63) / 64);
+      xblocks = sg.pl.mblocks + uint32_t(vec ? items : (items + SEL_NW - 1) / SEL_NW);
+      sign_lds = vec ? PLANE_TILE / 32 * 65 * 4 : 0;
     } else if (with_bits) {
       bit_geom_vec(&bt, signs->X);
       sg.bt = bt;

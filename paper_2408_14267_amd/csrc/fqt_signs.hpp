@@ -601,21 +601,25 @@ __device__ __forceinline__ void pack_w_body(const void *__restrict__ w, const Pa
 
 // ----------------------------------------------------------------------------- sign plane
 // sign(X) once per element for the tap form of the dW product (stride 1, same padding: input
-// and output positions are the same): dword m of channel c (positions 32 m ..) at m C + c.  A
-// wave takes 64 positions x 64 channels: lanes load a channel's 64 positions, the compare's
-// lane mask is the word, and lane c collects channel c's (v_writelane), so that each dword row
-// is stored in one piece.
+// and output positions are the same): dword m of channel c (positions 32 m ..) at m C + c.
+//   vector form (Ho*Wo % 8 == 0, X on 16 bytes): a block takes 512 positions x 64 channels; a
+//     lane loads 8 positions of a channel, four lanes' sign bytes are a dword, and the tile
+//     goes through LDS so that each dword row is stored along the channels.
+//   wave form (any map): 64 positions x 64 channels; the compare's lane mask is the word, and
+//     lane c collects channel c's (v_writelane).
+// (128-byte pieces of 64 channels a wave, as the wave form reads bfloat16, reached 2 TB/s.)
 struct PlaneGeom {
-  uint32_t C, P, R, Wr, W, H, per, mblocks;
-  FastDiv divP, divWr, divW;
+  uint32_t C, P, R, Wr, W, H, per, mblocks, vec;
+  FastDiv divP, divTiles, divW;        // divTiles: 512-position tiles, or words, per channel group
 };
-constexpr int PLANE_BATCH = 16;      // channels loaded back to back
+constexpr int PLANE_BATCH = 16;        // channels a wave of the wave form loads back to back
+constexpr uint32_t PLANE_TILE = 512;
 
 template <int DT>
 __device__ __forceinline__ void plane_wave_body(const void *__restrict__ x, const PlaneGeom &g,
                                                 uint32_t *__restrict__ dst, uint32_t item) {
   const int lane = threadIdx.x & 63;
-  const uint32_t cg = fdiv(item, g.divWr), w = item - cg * g.Wr, c0 = cg * 64;
+  const uint32_t cg = fdiv(item, g.divTiles), w = item - cg * g.Wr, c0 = cg * 64;
   if (c0 >= g.C) return;
   const uint32_t r = w * 64 + uint32_t(lane);
   const bool in = r < g.R;
@@ -641,21 +645,59 @@ __device__ __forceinline__ void plane_wave_body(const void *__restrict__ x, cons
   }
 }
 
-// Masks of the positions of dword m (m < per, the period of the image in dwords): bits whose
-// row above, row below, column to the left and to the right are inside the image.
+// NT threads; tile: [PLANE_TILE / 32][65] dwords of LDS.
+template <int DT, int NT>
+__device__ __forceinline__ void plane_tile_body(const void *__restrict__ x, const PlaneGeom &g,
+                                                uint32_t *__restrict__ dst, uint32_t bid,
+                                                uint32_t (*tile)[65]) {
+  constexpr int CPW = 64 / (NT / 64);            // channels per wave
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t cg = fdiv(bid, g.divTiles), r0 = (bid - cg * g.divTiles.d) * PLANE_TILE;
+  const uint32_t c0 = cg * 64, r = r0 + 8 * uint32_t(lane);
+  const bool in = r < g.R;                       // (8 positions of one sample)
+  const uint32_t n = fdiv(in ? r : 0, g.divP), p = (in ? r : 0) - n * g.P;
+  float v[CPW][8];
+#pragma unroll
+  for (int k = 0; k < CPW; ++k) {
+    const uint32_t c = min(c0 + wave * CPW + k, g.C - 1);
+    load_oct<DT>(x, (int64_t(n) * g.C + c) * g.P + p, v[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < CPW; ++k) {
+    uint32_t b = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) b |= v[k][e] > 0.0f ? 1u << e : 0u;
+    b = in ? b << (8 * (lane & 3)) : 0u;
+    b |= lane_xor<1>(b);
+    b |= lane_xor<2>(b);
+    if ((lane & 3) == 0) tile[lane >> 2][wave * CPW + k] = b;
+  }
+  __syncthreads();
+  for (uint32_t e = threadIdx.x; e < PLANE_TILE / 32 * 64; e += NT) {
+    const uint32_t m = e >> 6, c = e & 63;
+    if (c0 + c < g.C && r0 / 32 + m < 2 * g.Wr) dst[size_t(r0 / 32 + m) * g.C + c0 + c] = tile[m][c];
+  }
+}
+
+// Masks of the positions of dword m (the image repeats every `per` dwords; entry `per` is entry
+// 0 again) for the taps of kernel row i: bits whose tap (i, j) lies inside the image in .x, .y,
+// .z for j = 0, 1, 2, at masks[i (per + 1) + m].
 __device__ __forceinline__ void plane_mask_body(const PlaneGeom &g, uint4 *__restrict__ masks,
                                                 uint32_t m) {
-  if (m >= g.per) return;
-  uint4 v = make_uint4(0u, 0u, 0u, 0u);
+  if (m > g.per) return;
+  uint32_t up = 0, down = 0, left = 0, right = 0;
   for (uint32_t b = 0; b < 32; ++b) {
     const uint32_t q = m * 32 + b, p = q - fdiv(q, g.divP) * g.P;
     const uint32_t h = fdiv(p, g.divW), c = p - h * g.W;
-    v.x |= (h > 0 ? 1u : 0u) << b;
-    v.y |= (h + 1 < g.H ? 1u : 0u) << b;
-    v.z |= (c > 0 ? 1u : 0u) << b;
-    v.w |= (c + 1 < g.W ? 1u : 0u) << b;
+    up |= (h > 0 ? 1u : 0u) << b;
+    down |= (h + 1 < g.H ? 1u : 0u) << b;
+    left |= (c > 0 ? 1u : 0u) << b;
+    right |= (c + 1 < g.W ? 1u : 0u) << b;
   }
-  masks[m] = v;
+  masks[m] = make_uint4(up & left, up, up & right, 0u);
+  masks[g.per + 1 + m] = make_uint4(left, 0xFFFFFFFFu, right, 0u);
+  masks[2 * (g.per + 1) + m] = make_uint4(down & left, down, down & right, 0u);
 }
 
 inline PackWGeom pack_w_geom(const Layer &L) {

@@ -26,6 +26,7 @@
 namespace fqt {
 namespace {
 
+typedef int v3i __attribute__((ext_vector_type(3)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -38,14 +39,14 @@ struct TapsArgs {
   const int32_t *kept, *count;
   const float2 *slot_sz;         // (scale, offset) by kept slot
   const uint32_t *plane;         // sign dwords, `halo` rows before and after the layer's
-  const uint4 *masks;            // [per]: bits whose row above / below, column left / right exists
+  const uint4 *masks;            // [3][per + 1]: bits of kernel row i's three taps inside the image
   float *dW;
   int32_t *part, *partT;         // [S][D][9 Cp], [S][9 Cp], column tap * Cp + c
   uint32_t C, Cp, D, R, Rp, Wr, S, wps, per, cblks, halo;
-  uint32_t codes_bytes, plane_bytes;
+  uint32_t codes_bytes, plane_bytes, mstep;   // mstep = 2 KS mod per
   int k[3];                      // per kernel row: dword and bit of position r + (i - 1) W - 1
   uint32_t sh[3];
-  FastDiv divS, divCb, divPer;
+  FastDiv divS, divCb;
 };
 
 constexpr int KS = 4;                         // waves that share a kernel row's contraction
@@ -58,7 +59,7 @@ struct Word {
   static constexpr int H = FP4 ? 1 : 2;       // MFMA steps per word
   v4i A[H][2];
   uint32_t d[FP4 ? 3 : 4];
-  uint4 m[H];
+  v3i m[H];                                   // masks of taps j = 0, 1, 2
 };
 
 // Grid: S slices (fastest: with S a multiple of eight each XCD keeps its slices' codes and
@@ -79,9 +80,11 @@ k_dw_taps(TapsArgs a) {
   const uint32_t pair = fdiv(rest, a.divCb), cb = rest - pair * a.cblks;
   const uint32_t j0 = pair * SLOTS, c = cb * 32 + uint32_t(i32);
   if (int(j0) >= count) return;
-  const bool two = int(j0) + 32 < count;      // the second row tile holds kept channels
+  // The second row tile holds kept channels.
+  const bool two = __builtin_amdgcn_readfirstlane(int(j0) + 32 < count ? 1 : 0);
   const __amdgpu_buffer_rsrc_t crs = buffer_of(a.codes, a.codes_bytes);
   const __amdgpu_buffer_rsrc_t prs = buffer_of(a.plane - size_t(a.halo) * a.C, a.plane_bytes);
+  const __amdgpu_buffer_rsrc_t mrs = buffer_of(a.masks + row * (a.per + 1), (a.per + 1) * 16);
   uint32_t aoff[2];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
@@ -101,11 +104,13 @@ k_dw_taps(TapsArgs a) {
 #pragma unroll
     for (int j = 0; j < 3; ++j) acc[rt][j] = Acc{0};
   uint32_t zeros[3] = {0, 0, 0}, qsum[2] = {0, 0}, words = 0;
+  uint32_t m0 = (2 * w0) % a.per;             // mask entry of the next word to be issued
+  uint32_t c88 = 0x88888888u;                 // (in a vector register: an instruction takes one scalar)
+  asm("" : "+v"(c88));
 
   auto issue = [&](uint32_t w, Word<FP4> &b) {
     const uint32_t cs = __builtin_amdgcn_readfirstlane(w * H * a.D * 32);
     const uint32_t ps = __builtin_amdgcn_readfirstlane(2 * w * a.C * 4);
-    const uint32_t m0 = 2 * w - fdiv(2 * w, a.divPer) * a.per;
 #pragma unroll
     for (int h = 0; h < H; ++h)
 #pragma unroll
@@ -113,13 +118,15 @@ k_dw_taps(TapsArgs a) {
 #pragma unroll
     for (int q = 0; q < (FP4 ? 3 : 4); ++q)
       b.d[q] = __builtin_amdgcn_raw_buffer_load_b32(prs, poff, ps + q * a.C * 4, 0);
-    const uint32_t m1 = m0 + 1 == a.per ? 0 : m0 + 1;
-    if constexpr (FP4) {
-      b.m[0] = a.masks[g ? m1 : m0];
-    } else {
-      b.m[0] = a.masks[m0];
-      b.m[1] = a.masks[m1];
-    }
+    // (the entry after the last repeats the first)
+    const uint32_t ms = __builtin_amdgcn_readfirstlane(m0 * 16);
+#pragma unroll
+    for (int h = 0; h < H; ++h)         // (three dwords: a fourth, unused, would make its register
+                                        //  free while the load is in flight, and a use wait for it)
+      b.m[h] = __builtin_bit_cast(v3i, __builtin_amdgcn_raw_buffer_load_b96(mrs, FP4 ? g * 16 : 0,
+                                                                           ms + 16 * h, 0));
+    m0 += a.mstep;
+    m0 -= m0 >= a.per ? a.per : 0;
   };
   auto consume = [&](uint32_t w, Word<FP4> &b) {
     ++words;
@@ -128,10 +135,10 @@ k_dw_taps(TapsArgs a) {
     for (int q = 0; q < H + 1; ++q) y[q] = __builtin_amdgcn_alignbit(b.d[q + 1], b.d[q], sh);
 #pragma unroll
     for (int h = 0; h < H; ++h) {
-      uint32_t rm = row == 0 ? b.m[h].x : row == 2 ? b.m[h].y : 0xFFFFFFFFu;
       if (w == a.Wr - 1 && tail) {            // positions past R count as clear bits
         const int keep = 64 - int(tail) - 32 * (FP4 ? g : h);
-        rm &= keep >= 32 ? 0xFFFFFFFFu : keep > 0 ? (1u << keep) - 1 : 0u;
+        const int km = keep >= 32 ? -1 : keep > 0 ? int((1u << keep) - 1) : 0;
+        b.m[h] = v3i{b.m[h].x & km, b.m[h].y & km, b.m[h].z & km};
       }
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
@@ -149,14 +156,14 @@ k_dw_taps(TapsArgs a) {
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         const uint32_t x = j == 0 ? y[h] : __builtin_amdgcn_alignbit(y[h + 1], y[h], j);
-        const uint32_t cm = j == 0 ? b.m[h].z : j == 2 ? b.m[h].w : 0xFFFFFFFFu;
-        const uint32_t n = ~(x & rm & cm);    // set: sign -1
+        const uint32_t n = ~(x & uint32_t(b.m[h][j]));   // set: sign -1
         zeros[j] += __popc(n);
         if constexpr (FP4) {
-          const v4i B = v4i{int(((n << 3) & 0x88888888u) | 0x22222222u),
-                            int(((n << 2) & 0x88888888u) | 0x22222222u),
-                            int(((n << 1) & 0x88888888u) | 0x22222222u),
-                            int((n & 0x88888888u) | 0x22222222u)};
+          // Bits 3, 7, ... of n << (3 - q) over 0x2 in every nibble: (a & b) | c.
+          v4i B;
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            B[q] = int(__builtin_amdgcn_bitop3_b32(n << (3 - q), c88, 0x22222222u, 0xEA));
           acc[0][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_v8(b.A[h][0]), as_v8(B),
                                                                      acc[0][j], 4, 4, 0, 127, 0, 127);
           if (two)
@@ -178,7 +185,10 @@ k_dw_taps(TapsArgs a) {
     Word<FP4> ring[ST];
     const uint32_t last = w0 + (w_end - 1 - w0) / KS * KS;
 #pragma unroll
-    for (int u = 0; u < ST; ++u) issue(min(w0 + KS * u, last), ring[u]);
+    for (int u = 0; u < ST; ++u) {
+      issue(min(w0 + KS * u, last), ring[u]);
+      __builtin_amdgcn_sched_barrier(0);        // in ring order, so that the waits count exactly
+    }
     for (uint32_t w = w0; w < w_end; w += KS * ST) {
 #pragma unroll
       for (int u = 0; u < ST; ++u) {
@@ -242,10 +252,10 @@ k_dw_taps(TapsArgs a) {
 }
 
 // dW from the slices: a block takes one slot and 64 channels (576 outputs, contiguous in dW);
-// thread (chunk, quad) sums every fourth slice of 4 channels of one tap, the chunks and the
-// order of the taps meet in LDS.
+// thread (chunk, quad) sums every fourth slice of 4 channels of one tap, U slices' loads
+// together; the chunks and the order of the taps meet in LDS.
 constexpr int FIN_QUADS = 9 * 16, FIN_CHUNKS = 4, FIN_THREADS = FIN_QUADS * FIN_CHUNKS;
-template <bool B8>
+template <bool B8, uint32_t U>
 __global__ __launch_bounds__(FIN_THREADS) void k_dw_taps_finish(TapsArgs a) {
   __shared__ int4 red[FIN_CHUNKS][FIN_QUADS], tred[FIN_CHUNKS][FIN_QUADS];
   __shared__ float out[64 * 9];
@@ -263,7 +273,6 @@ __global__ __launch_bounds__(FIN_THREADS) void k_dw_taps_finish(TapsArgs a) {
   }
   int4 acc = make_int4(0, 0, 0, 0), T = make_int4(0, 0, 0, 0);
   if (c0 + c < a.Cp) {
-    constexpr uint32_t U = 8;
     const uint32_t col = tap * a.Cp + c0 + c;
     for (uint32_t s0 = chunk; s0 < a.S; s0 += U * FIN_CHUNKS) {
       int4 v[U], tv[U];
@@ -327,7 +336,7 @@ bool taps_plan(const Layer &L, const fqt_quant_cfg &cfg, size_t arena, TapsPlan 
   const size_t row = size_t(L.C) * 4;
   p->plane_bytes = (size_t(2 * L.Wr) + 2 * p->halo) * row;
   p->mask_at = align256(p->plane_bytes);
-  p->part_at = p->mask_at + align256(size_t(p->per) * 16);
+  p->part_at = p->mask_at + align256(3 * (size_t(p->per) + 1) * 16);
   const size_t slice = (size_t(L.D) + 1) * 9 * p->Cp * 4;
   if (p->plane_bytes >= (size_t(1) << 31) || p->part_at + slice + 512 > arena) return false;
   int64_t S = std::min((TAPS_BLOCKS + blocks - 1) / blocks, L.Wr / 16);
@@ -361,7 +370,7 @@ int launch_dw_taps(const Layer &L, const fqt_quant_cfg &cfg, const TapsPlan &p,
     a.k[i] = int(o >= 0 ? o / 32 : -((-o + 31) / 32));
     a.sh[i] = uint32_t(o - int64_t(a.k[i]) * 32);
   }
-  a.divS = make_fastdiv(a.S); a.divCb = make_fastdiv(a.cblks); a.divPer = make_fastdiv(a.per);
+  a.divS = make_fastdiv(a.S); a.divCb = make_fastdiv(a.cblks); a.mstep = 2 * KS % a.per;
   const dim3 grid(a.S * a.cblks * unsigned((L.D + SLOTS - 1) / SLOTS));
   if (p.fmt == PCQ_TAPS4)
     hipLaunchKernelGGL((k_dw_taps<true, false>), grid, dim3(TAP_THREADS), 0, s, a);
@@ -370,9 +379,15 @@ int launch_dw_taps(const Layer &L, const fqt_quant_cfg &cfg, const TapsPlan &p,
   else hipLaunchKernelGGL((k_dw_taps<false, false>), grid, dim3(TAP_THREADS), 0, s, a);
   if (last_launch_status() != FQT_OK) return FQT_E_HIP;
   const dim3 fgrid(unsigned(L.D) * unsigned((L.C + 63) / 64));
-  if (cfg.bits == 8)
-    hipLaunchKernelGGL(k_dw_taps_finish<true>, fgrid, dim3(FIN_THREADS), 0, s, a);
-  else hipLaunchKernelGGL(k_dw_taps_finish<false>, fgrid, dim3(FIN_THREADS), 0, s, a);
+  auto finish = [&]<bool B8>() {
+    if (p.S <= FIN_CHUNKS)
+      hipLaunchKernelGGL((k_dw_taps_finish<B8, 1>), fgrid, dim3(FIN_THREADS), 0, s, a);
+    else if (p.S <= 2 * FIN_CHUNKS)
+      hipLaunchKernelGGL((k_dw_taps_finish<B8, 2>), fgrid, dim3(FIN_THREADS), 0, s, a);
+    else hipLaunchKernelGGL((k_dw_taps_finish<B8, 8>), fgrid, dim3(FIN_THREADS), 0, s, a);
+  };
+  if (cfg.bits == 8) finish.template operator()<true>();
+  else finish.template operator()<false>();
   return last_launch_status();
 }
 
