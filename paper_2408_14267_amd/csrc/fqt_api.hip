@@ -457,7 +457,8 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
   // Statistics, then the selection (whose launch also packs the sign operands when the
   // layer allows), the quantizer, both products.
   const TapsPlan *taps = w.taps_on ? &w.taps : nullptr;
-  SignJob sj{X, W, w.xsign, w.wsb, w.wlsum, false, taps, w.arena};
+  const bool wrows = dx_rows_form(L, W);
+  SignJob sj{X, W, w.xsign, w.wsb, w.wlsum, false, wrows, taps, w.arena};
   // The products read the byte codes; the bit planes (the paper's packed form) are left to
   // fqt_agp_scq_quantize callers.
   FQT_TRY(launch_quantize(L, *cfg, dY, w.q, w.qws, s, &sj, false, train));
@@ -468,10 +469,10 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
     else
       FQT_TRY(launch_pack_bits(X, L.x_t, 0, 0, 0, FQT_PACK_IM2COL, &L, w.xsign, nullptr, s,
                                true));
-    FQT_TRY(launch_pack_w_i8(W, L, w.wsb, w.wlsum, s));
+    if (!wrows) FQT_TRY(launch_pack_w_i8(W, L, w.wsb, w.wlsum, s));
   }
   return launch_products(L, *cfg, w.q, w.xsign, w.wsb, w.wlsum, dX, dW, w.dw_ws, w.qws.sslot,
-                         w.qws.cslot, s, train, taps, w.arena);
+                         w.qws.cslot, s, train, taps, w.arena, wrows ? W : nullptr);
 }
 }  // namespace
 }  // namespace fqt

@@ -532,13 +532,17 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
     }
     return;
   }
-  // The 32 x 32 tiles go out through a row-major LDS copy per wave, each lane storing 16
-  // consecutive columns of one kept row in 16-byte pieces (the integer debug output takes
-  // the element stores below).
+  // The tiles go out through a row-major LDS copy per wave, two column tiles (64 columns) at a
+  // time, consecutive lanes storing consecutive 16-byte pieces: 256 bytes of each kept row,
+  // whole lines (pieces of two lanes per row and tile reached 3.1 TB/s at 25088 -> 4096, batch
+  // 64).  Misaligned rows, columns past K and the integer debug output take element stores.
   if constexpr (!SPLIT) {
     if (!a.I_out) {
-      __shared__ float stage[DW_WAVES][32 * 32];
+      constexpr int SC = 64, SP = SC + 4;     // staged columns, and their pitch in floats
+      static_assert(CT % 2 == 0, "pairs of column tiles");
+      __shared__ __align__(16) float stage[DW_WAVES][32 * SP];
       float *st = stage[wave];
+      const bool vec = (a.K & 3) == 0 && (reinterpret_cast<uintptr_t>(a.dW) & 15) == 0;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const int qrow = int(qsum[rt] + lane_xor<32>(qsum[rt])) + (B8 ? 128 * int(a.Rp) : 0);
@@ -546,7 +550,7 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) qv[v] = __shfl(qrow, acc_row(v, g));
         const uint32_t jt = j0 + 32 * rt;
-        // The rows' scales and offsets and this lane's store row, loaded once per row tile,
+        // The rows' scales and offsets and this lane's store rows, loaded once per row tile,
         // all at once (inside the column-tile loop they would follow each tile's dW stores,
         // which the compiler cannot move them across: a dependent round trip per tile).
         float2 szv[16];
@@ -557,37 +561,46 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
           if (int(j) < count)
             szv[v] = a.slot_sz ? a.slot_sz[j] : make_float2(a.scale[a.kept[j]], a.offset[a.kept[j]]);
         }
-        const uint32_t jrow = jt + uint32_t(lane >> 1);
-        const size_t drow = jrow < a.D ? size_t(a.kept[jrow]) : 0;
+        uint32_t drow[8];                     // row 4 k + lane / 16 of the tile
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          const int T = int(tcnt[ct]);
+        for (int k = 0; k < 8; ++k) {
+          const uint32_t j = jt + 4 * k + uint32_t(lane >> 4);
+          drow[k] = j < a.D ? uint32_t(a.kept[j]) : 0;
+        }
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const uint32_t j = jt + uint32_t(acc_row(v, g));
-            float out = 0.0f;
-            if (int(j) < count) {
-              const int I = 2 * (acc[rt][ct][v] + (B8 ? 128 * T : 0)) - qv[v];
-              out = rescale(szv[v].x, I, szv[v].y, float(2 * T - int(a.R)));
+        for (int cp = 0; cp < CT; cp += 2) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int T = int(tcnt[cp + h]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              const uint32_t j = jt + uint32_t(acc_row(v, g));
+              float out = 0.0f;
+              if (int(j) < count) {
+                const int I = 2 * (acc[rt][cp + h][v] + (B8 ? 128 * T : 0)) - qv[v];
+                out = rescale(szv[v].x, I, szv[v].y, float(2 * T - int(a.R)));
+              }
+              st[acc_row(v, g) * SP + 32 * h + i] = out;
             }
-            st[acc_row(v, g) * 32 + i] = out;
           }
           __builtin_amdgcn_wave_barrier();    // LDS operations of a wave run in order
-          const uint32_t j = jrow;
-          const uint32_t c0 = k0 + 32 * ct + 16 * uint32_t(lane & 1);
-          if (j < a.D && c0 < a.K) {
-            const float *src = st + (lane >> 1) * 32 + 16 * (lane & 1);
-            float *dst = a.dW + drow * a.K + c0;
-            if (c0 + 16 <= a.K && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
-              const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
-              uint4 *d4 = reinterpret_cast<uint4 *>(dst);
+          const uint32_t col = k0 + 32 * cp + 4 * uint32_t(lane & 15);
 #pragma unroll
-              for (int k = 0; k < 4; ++k) d4[k] = s4[k];
+          for (int k = 0; k < 8; ++k) {
+            const int row = 4 * k + (lane >> 4);
+            if (jt + row >= a.D || col >= a.K) continue;
+            const float4 f = *reinterpret_cast<const float4 *>(st + row * SP + 4 * (lane & 15));
+            float *dst = a.dW + size_t(drow[k]) * a.K + col;
+            if (vec) {
+              *reinterpret_cast<float4 *>(dst) = f;
             } else {
-              for (uint32_t e = 0; e < 16 && c0 + e < a.K; ++e) dst[e] = src[e];
+              dst[0] = f.x;
+              if (col + 1 < a.K) dst[1] = f.y;
+              if (col + 2 < a.K) dst[2] = f.z;
+              if (col + 3 < a.K) dst[3] = f.w;
             }
           }
-          __builtin_amdgcn_wave_barrier();    // the next tile's copy waits for these reads
+          __builtin_amdgcn_wave_barrier();    // the next tiles' copy waits for these reads
         }
       }
       return;
@@ -1274,6 +1287,192 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
   }
 }
 
+// Linear layers of at most DXR_ROWS rows with large W: the product is bound by reading W, so W is
+// read once, as it is (no byte copy of its signs).  A block takes 64 channels, its waves every
+// DXR_WAVES-th chunk of 32 output channels d; lane (i = lane % 32, g = lane / 32) loads channels
+// 2 i, 2 i + 1 of rows d = 16 g .. 16 g + 15 (256 contiguous bytes per row) and packs their
+// signs to the 16 bytes it feeds as column i of two MFMA tiles (even and odd channels).  The
+// codes' rows are the MFMA's rows, so that output lanes run along the channels.  Line sums of
+// the signs come from v_dot4 on the same bytes.  Rows of pruned samples are zeroed.
+struct DxRowsArgs {
+  const void *w;                 // [D][C]
+  const uint8_t *codes;          // PSQ codes [Dp/32][N][32]
+  const int32_t *kept, *count;
+  const float2 *slot_sz;
+  void *dX;                      // [N][C]
+  const float *ste;
+  int dx_t;
+  uint32_t N, C, D, chunks, codes_bytes;   // chunks = ceil(D / 32)
+};
+constexpr int DXR_WAVES = 8, DXR_THREADS = 64 * DXR_WAVES;
+constexpr uint32_t DXR_ROWS = 128;
+constexpr int64_t DXR_MIN_W_BYTES = int64_t(4) << 20;
+
+template <bool B8, int NT, int WDT>
+__global__ __launch_bounds__(DXR_THREADS) void k_dx_rows(DxRowsArgs a) {
+  constexpr int ES = WDT == FQT_BF16 ? 2 : 4;
+  __shared__ int32_t red[DXR_WAVES][2][16][64];
+  const int lane = threadIdx.x & 63, i = lane & 31, g = lane >> 5;
+  const uint32_t wave = wave_id();
+  const int count = *a.count;
+  const uint32_t c0 = blockIdx.x * 64, c = c0 + 2 * uint32_t(i);      // (C is even)
+  const __amdgpu_buffer_rsrc_t crs = buffer_of(a.codes, a.codes_bytes);
+  uint32_t aoff[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const uint32_t j = 32 * t + uint32_t(i);
+    aoff[t] = int(j) < count ? j * 32 + 16 * g : BUF_NONE;
+  }
+  const uint32_t live = (uint32_t(count) + 31) / 32;                  // row tiles in use
+  v16i acc[NT][2];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t][0] = acc[t][1] = v16i{0};
+  int csum[2] = {0, 0};
+  constexpr bool TWO = NT <= 2;                // two register sets of loads, where they fit
+  uint64_t wv[TWO ? 2 : 1][16];
+  auto issue = [&](uint32_t ch, uint64_t (&v)[16]) {
+    const uint32_t d = ch * 32, rows = min(32u, a.D - d);
+    const __amdgpu_buffer_rsrc_t wrs =
+        buffer_of(static_cast<const char *>(a.w) + size_t(d) * a.C * ES, rows * a.C * ES);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const uint32_t off = c < a.C && uint32_t(16 * g + m) < rows
+                               ? (uint32_t(16 * g + m) * a.C + c) * ES : BUF_NONE;
+      if (ES == 4) v[m] = load8(wrs, off, 0);
+      else v[m] = uint64_t(__builtin_amdgcn_raw_buffer_load_b32(wrs, off, 0, 0));
+    }
+  };
+  auto consume = [&](uint32_t ch, uint64_t (&v)[16], v4i (&A)[NT]) {
+    v4i b[2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t lo = 0, hi = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint64_t w = v[4 * q + e];
+        const float x = __uint_as_float(ES == 4 ? uint32_t(w) : uint32_t(w) << 16);
+        const float y = __uint_as_float(ES == 4 ? uint32_t(w >> 32) : uint32_t(w) & 0xFFFF0000u);
+        lo |= x > 0.0f ? 0x01u << (8 * e) : 0xFFu << (8 * e);
+        hi |= y > 0.0f ? 0x01u << (8 * e) : 0xFFu << (8 * e);
+      }
+      b[0][q] = int(lo);
+      b[1][q] = int(hi);
+      csum[0] = __builtin_amdgcn_sdot4(int(lo), 0x01010101, csum[0], false);
+      csum[1] = __builtin_amdgcn_sdot4(int(hi), 0x01010101, csum[1], false);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (uint32_t(t) >= live) break;
+      const v4i q = B8 ? bias128(A[t]) : A[t];
+      acc[t][0] = mfma_i8(q, b[0], acc[t][0]);
+      acc[t][1] = mfma_i8(q, b[1], acc[t][1]);
+    }
+  };
+  auto codes = [&](uint32_t ch, v4i (&A)[NT]) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) A[t] = load16(crs, aoff[t], ch * a.N * 32);
+  };
+  if (wave < a.chunks) {
+    if constexpr (TWO) {
+      // Double-buffered: chunk k + 1's loads issue before chunk k's products (past the end,
+      // the last chunk again).
+      const uint32_t last = wave + (a.chunks - 1 - wave) / DXR_WAVES * DXR_WAVES;
+      v4i Aa[NT], Ab[NT];
+      uint32_t ch = wave;
+      issue(ch, wv[0]);
+      codes(ch, Aa);
+      for (;;) {
+        issue(min(ch + DXR_WAVES, last), wv[1]);
+        codes(min(ch + DXR_WAVES, last), Ab);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(ch, wv[0], Aa);
+        ch += DXR_WAVES;
+        if (ch >= a.chunks) break;
+        issue(min(ch + DXR_WAVES, last), wv[0]);
+        codes(min(ch + DXR_WAVES, last), Aa);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(ch, wv[1], Ab);
+        ch += DXR_WAVES;
+        if (ch >= a.chunks) break;
+      }
+    } else {
+      for (uint32_t ch = wave; ch < a.chunks; ch += DXR_WAVES) {
+        v4i A[NT];
+        issue(ch, wv[0]);
+        codes(ch, A);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(ch, wv[0], A);
+      }
+    }
+  }
+  // Line sums over the half-waves and the waves; rows of the last chunk past D counted as -1.
+  __shared__ int32_t cs[DXR_WAVES][2][32];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int v = csum[h] + int(lane_xor<32>(uint32_t(csum[h])));
+    if (g == 0) cs[wave][h][i] = v;
+  }
+  __syncthreads();
+  int call[2] = {0, 0};
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int w = 0; w < DXR_WAVES; ++w) call[h] += cs[w][h][i];
+  const int pad = int(a.chunks * 32 - a.D);
+  auto store2 = [&](size_t o, float x, float y) {       // channels c, c + 1 of row o / C
+    if (a.ste) {
+      x = __builtin_fabsf(a.ste[o]) <= 1.0f ? x : 0.0f;
+      y = __builtin_fabsf(a.ste[o + 1]) <= 1.0f ? y : 0.0f;
+    }
+    if (a.dx_t == FQT_BF16) {
+      uint16_t *d = static_cast<uint16_t *>(a.dX) + o;
+      if ((reinterpret_cast<uintptr_t>(d) & 3) == 0) {
+        *reinterpret_cast<uint32_t *>(d) = f32_to_bf16(x) | (uint32_t(f32_to_bf16(y)) << 16);
+      } else {
+        d[0] = f32_to_bf16(x);
+        d[1] = f32_to_bf16(y);
+      }
+    } else {
+      float *d = static_cast<float *>(a.dX) + o;
+      if ((reinterpret_cast<uintptr_t>(d) & 7) == 0) {
+        *reinterpret_cast<float2 *>(d) = make_float2(x, y);
+      } else {
+        d[0] = x;
+        d[1] = y;
+      }
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if (uint32_t(t) >= live) break;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[wave][h][v][lane] = acc[t][h][v];
+    __syncthreads();
+    // Wave w finishes accumulators 2 w, 2 w + 1 of both tiles.
+#pragma unroll
+    for (int u = 0; u < 16 / DXR_WAVES; ++u) {
+      const int v = (16 / DXR_WAVES) * int(wave) + u;
+      const uint32_t j = 32 * t + uint32_t(acc_row(v, g));
+      int I[2] = {0, 0};
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int w = 0; w < DXR_WAVES; ++w) I[h] += red[w][h][v][lane];
+      if (int(j) < count && c < a.C) {
+        const float2 sz = a.slot_sz[j];
+        const float x = rescale(sz.x, I[0] + (B8 ? 128 * call[0] : 0), sz.y, float(call[0] + pad));
+        const float y = rescale(sz.x, I[1] + (B8 ? 128 * call[1] : 0), sz.y, float(call[1] + pad));
+        store2(size_t(a.kept[j]) * a.C + c, x, y);
+      }
+    }
+    __syncthreads();
+  }
+  for (uint32_t j = uint32_t(count) + 2 * wave + uint32_t(g); j < a.N; j += 2 * DXR_WAVES)
+    if (c < a.C) store2(size_t(a.kept[j]) * a.C + c, 0.0f, 0.0f);
+}
+
 // WT: 0 for the split form, CT (1 or 2 channel tiles per wave) for the register-tile form.
 template <int WT>
 using DxLdsOf = std::conditional_t<WT != 0, DxTileLds<WT == 0 ? 1 : WT>, DxLds>;
@@ -1518,6 +1717,15 @@ void launch_dw_finish(const Layer &L, const DwArgs &a, hipStream_t s) {
 
 }  // namespace
 
+// The linear layers k_dx_rows takes: few rows, W of 4 MB and more (below, the product shares its
+// launch with dW and packing W hides beside the selection), pairs of channels on 4-byte
+// addresses, 32 rows of W in one buffer.
+bool dx_rows_form(const Layer &L, const void *W) {
+  const int64_t es = L.w_t == FQT_BF16 ? 2 : 4;
+  return L.kind == FQT_LINEAR && L.N <= int64_t(DXR_ROWS) && L.D * L.C * es >= DXR_MIN_W_BYTES &&
+         L.C % 2 == 0 && aligned(W, 4) && 32 * L.C * es < (int64_t(1) << 31);
+}
+
 int launch_gemm_dw(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                    const uint64_t *xsign, float *dW, int32_t *I_out, void *ws, hipStream_t s) {
   const DwArgs a = make_dw_args(L, cfg, q, xsign, dW, I_out, ws);
@@ -1570,7 +1778,8 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
 int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
-                    hipStream_t s, const TrainJob *train, const TapsPlan *taps, char *arena) {
+                    hipStream_t s, const TrainJob *train, const TapsPlan *taps, char *arena,
+                    const void *wrows) {
   if (L.kh * L.kw > DX_MAX_TAPS) return FQT_E_SHAPE;
   DwArgs dwa = make_dw_args(L, cfg, q, xsign, dW, nullptr, dw_ws);
   DxArgs dxa = make_dx_args(L, q, wsb, wlsum, dX, nullptr);
@@ -1594,6 +1803,27 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
   }
   const uint32_t ndw = (big || split_big) ? 0u
                       : kred ? dw_kred_blocks(L, dwa) : dw_part_blocks(L, dwa);
+  if (wrows) {
+    DxRowsArgs r;
+    r.w = wrows; r.codes = q.psq_codes; r.kept = q.psq_kept; r.count = q.psq_count;
+    r.slot_sz = sslot; r.dX = dX; r.ste = train ? train->X : nullptr; r.dx_t = L.dx_t;
+    r.N = uint32_t(L.N); r.C = uint32_t(L.C); r.D = uint32_t(L.D);
+    r.chunks = uint32_t((L.D + 31) / 32); r.codes_bytes = dxa.codes_bytes;
+    const dim3 rgrid(unsigned((L.C + 63) / 64));
+    auto go = [&]<bool B8, int WDT>() {
+      if (L.N <= 32) hipLaunchKernelGGL((k_dx_rows<B8, 1, WDT>), rgrid, dim3(DXR_THREADS), 0, s, r);
+      else if (L.N <= 64)
+        hipLaunchKernelGGL((k_dx_rows<B8, 2, WDT>), rgrid, dim3(DXR_THREADS), 0, s, r);
+      else hipLaunchKernelGGL((k_dx_rows<B8, 4, WDT>), rgrid, dim3(DXR_THREADS), 0, s, r);
+    };
+    dispatch_dtype(L.w_t, [&]<int WDT>() {
+      if (cfg.bits == 8) go.template operator()<true, WDT>();
+      else go.template operator()<false, WDT>();
+    });
+    if (last_launch_status() != FQT_OK) return FQT_E_HIP;
+    dxa.nblocks = 0;                      // the products launch holds what is left
+    if (ndw == 0 && !train) return FQT_OK;
+  }
   DgArgs dg{};
   if (train) {
     dxa.ste = train->X;

@@ -115,6 +115,7 @@ struct SignJob {
   int8_t *wsb;           // sign(W) bytes
   int32_t *wlsum;
   bool done;
+  bool no_w;             // W is not packed (the dX product reads it)
   const TapsPlan *taps;  // the sign plane of the tap form instead of xsign, at `arena`
   char *arena;
 };
@@ -152,7 +153,10 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
                     hipStream_t s, const TrainJob *train = nullptr,
-                    const TapsPlan *taps = nullptr, char *arena = nullptr);
+                    const TapsPlan *taps = nullptr, char *arena = nullptr,
+                    const void *wrows = nullptr);
+// Linear layers whose dX product reads W itself (launch_products' wrows).
+bool dx_rows_form(const Layer &L, const void *W);
 
 // The dW product from the code planes and line-major sign bits (popcount or fp4 engine).
 size_t engine_ws_bytes(const Layer &L, const fqt_quant_cfg &cfg, int engine);

@@ -588,8 +588,8 @@ __device__ __forceinline__ uint64_t sort_key(uint64_t w, int i) {
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  if constexpr (sizeof(T) == 8) return T(wave_total_u64(uint64_t(v)));
+  else return __builtin_amdgcn_readlane(wave_scan_i32(v, 0, [](int a, int b) { return a + b; }), 63);
 }
 
 template <int NT, typename T>
@@ -606,7 +606,7 @@ __device__ T block_sum(T v, T *scratch) {
 
 template <int NT>
 __device__ float block_max_f(float v, float *scratch) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+  v = __int_as_float(wave_max_all(__float_as_int(v)));     // (ranges: non-negative)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) scratch[wave] = v;
   __syncthreads();
@@ -635,11 +635,9 @@ __device__ uint64_t block_max_u64(uint64_t v, uint64_t *scratch) {
 template <int NT, typename T>
 __device__ T block_exscan(T v, T *scratch, T &total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  T x = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    const T y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
+  T x;
+  if constexpr (sizeof(T) == 8) x = T(wave_scan_add_u64(uint64_t(v)));
+  else x = wave_scan_i32(v, 0, [](int a, int b) { return a + b; });
   if (lane == 63) scratch[wave] = x;
   __syncthreads();
   T off = 0, tot = 0;
@@ -744,8 +742,24 @@ __global__ __launch_bounds__(NT) void k_select(SelectArgs a) {
           ++rc;
         }
       }
-      const int32_t cnt = block_sum<NT, int32_t>(rc, scr_i);
-      const uint64_t sum = block_sum<NT, uint64_t>(rs, scr_u);
+      // The round's count and weight together: one barrier, buffers in turn.
+      __shared__ uint64_t rsum[2][NT / 64];
+      __shared__ int32_t rcnt[2][NT / 64];
+      const int buf = round & 1;
+      const uint64_t ws = wave_sum(rs);
+      const int32_t wc = wave_sum(rc);
+      if ((t & 63) == 0) {
+        rsum[buf][t >> 6] = ws;
+        rcnt[buf][t >> 6] = wc;
+      }
+      __syncthreads();
+      uint64_t sum = 0;
+      int32_t cnt = 0;
+#pragma unroll
+      for (int w = 0; w < NT / 64; ++w) {
+        sum += rsum[buf][w];
+        cnt += rcnt[buf][w];
+      }
       if (cnt == 0) {
         done = true;
         break;
@@ -1994,7 +2008,7 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
     SignArgs sg{};
     sg.x = signs->X; sg.xsign = signs->xsign;
     sg.w = signs->W; sg.pg = pack_w_geom(L); sg.wsb = signs->wsb; sg.wlsum = signs->wlsum;
-    sg.npw = pack_w_blocks(L);
+    sg.npw = signs->no_w ? 0 : pack_w_blocks(L);
     uint32_t xblocks;
     if (with_plane) {
       const TapsPlan &tp = *signs->taps;

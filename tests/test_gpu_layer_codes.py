@@ -34,6 +34,14 @@ CASES = [
     (_conv(13, 70, 200, 64, 64, 3, 1, 1), 1, 2, "bf16", 1.0),
     (_conv(13, 65, 150, 64, 64, 3, 1, 1), 3, 2, "f32", 1.0),
     (_conv(800, 3, 80, 1, 64, 3, 1, 1), 5, 0, "f32", 1.0),
+    # Linear layers of few rows and large W (dX from W itself, dW bound by its stores): one, two
+    # and four row tiles, ragged D and C, b = 8, the many-group selection.
+    (LayerShape("fc", "linear", 20, 2050, 1030), 3, 0, "f32", 1.5),
+    (LayerShape("fc", "linear", 64, 4096, 2600), 2, 0, "bf16", 1.5),
+    (LayerShape("fc", "linear", 128, 1026, 2050), 8, 0, "f32", 1.0),
+    (LayerShape("fc", "linear", 65, 6000, 1000), 1, 2, "f32", 1.0),
+    (LayerShape("fc", "linear", 64, 2051, 2100), 4, 0, "f32", 1.5),
+    (LayerShape("fc", "linear", 33, 3000, 1500), 4, 1, "bf16", 3.0),
 ]
 
 
