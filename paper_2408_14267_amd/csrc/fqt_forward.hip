@@ -200,6 +200,7 @@ struct FwdArgs {
   int kh, kw, sh, sw, ph, pw;
   uint32_t steps, taps, Cw;      // steps = Cw * taps, taps fastest
   uint32_t dblocks, nblocks;
+  uint32_t stream;               // Y by non-temporal stores (STREAM_BYTES)
   uint32_t xf_bytes, wf_bytes;   // below 2^31 (not BIG)
   uint64_t xstride, wstride;     // bytes per chunk of X and per step of W
   FastDiv divP, divWo, divDb;
@@ -236,24 +237,31 @@ __device__ __forceinline__ void store_tile(const FwdArgs &a, const int32_t *st, 
     pq[k] = (e & (qs - 1)) + qs * (e >> (qsh + 5));
     gm[k] = d0 + dd[k] < a.D ? a.gamma[d0 + dd[k]] : 0.0f;
   }
+  auto put = [&](auto store4, auto store2) {
 #pragma unroll
-  for (int k = 0; k < PIECES; ++k) {
-    const uint32_t d = d0 + dd[k], r = r0 + 4 * pq[k];
-    if (d >= a.D || r >= a.R) continue;
-    const uint32_t n = fdiv(r, a.divP), p = r - n * a.P;
-    const size_t o = (size_t(n) * a.D + d) * a.P + p;
-    const int4 I = *reinterpret_cast<const int4 *>(st + dd[k] * st_pitch(RT) + 4 * pq[k]);
-    const float y0 = __fmul_rn(gm[k], float(I.x)), y1 = __fmul_rn(gm[k], float(I.y));
-    const float y2 = __fmul_rn(gm[k], float(I.z)), y3 = __fmul_rn(gm[k], float(I.w));
-    if (a.y_t == FQT_BF16) {
-      const uint32_t lo = f32_to_bf16(y0) | (uint32_t(f32_to_bf16(y1)) << 16);
-      const uint32_t hi = f32_to_bf16(y2) | (uint32_t(f32_to_bf16(y3)) << 16);
-      *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(a.Y) + o) = make_uint2(lo, hi);
-    } else {
-      *reinterpret_cast<float4 *>(static_cast<float *>(a.Y) + o) = make_float4(y0, y1, y2, y3);
+    for (int k = 0; k < PIECES; ++k) {
+      const uint32_t d = d0 + dd[k], r = r0 + 4 * pq[k];
+      if (d >= a.D || r >= a.R) continue;
+      const uint32_t n = fdiv(r, a.divP), p = r - n * a.P;
+      const size_t o = (size_t(n) * a.D + d) * a.P + p;
+      const int4 I = *reinterpret_cast<const int4 *>(st + dd[k] * st_pitch(RT) + 4 * pq[k]);
+      const float y0 = __fmul_rn(gm[k], float(I.x)), y1 = __fmul_rn(gm[k], float(I.y));
+      const float y2 = __fmul_rn(gm[k], float(I.z)), y3 = __fmul_rn(gm[k], float(I.w));
+      if (a.y_t == FQT_BF16)
+        store2(reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(a.Y) + o),
+               u32x2{f32_to_bf16(y0) | (uint32_t(f32_to_bf16(y1)) << 16),
+                     f32_to_bf16(y2) | (uint32_t(f32_to_bf16(y3)) << 16)});
+      else
+        store4(reinterpret_cast<u32x4 *>(static_cast<float *>(a.Y) + o),
+               u32x4{__float_as_uint(y0), __float_as_uint(y1), __float_as_uint(y2),
+                     __float_as_uint(y3)});
+      if (a.I_out) *reinterpret_cast<int4 *>(a.I_out + o) = I;
     }
-    if (a.I_out) *reinterpret_cast<int4 *>(a.I_out + o) = I;
-  }
+  };
+  if (a.stream)
+    put([](u32x4 *p, u32x4 v) { stream_fence(); __builtin_nontemporal_store(v, p); stream_fence(); },
+        [](u32x2 *p, u32x2 v) { stream_fence(); __builtin_nontemporal_store(v, p); stream_fence(); });
+  else put([](u32x4 *p, u32x4 v) { *p = v; }, [](u32x2 *p, u32x2 v) { *p = v; });
 }
 
 // One output element.
@@ -691,6 +699,7 @@ int launch_forward(const Layer &L, const void *X, const void *W, const float *ga
   a.xf_bytes = big ? 0 : uint32_t(z.xbytes); a.wf_bytes = big ? 0 : uint32_t(z.wbytes);
   a.divP = make_fastdiv(a.P); a.divWo = make_fastdiv(a.Wo);
   const size_t es = L.dy_t == FQT_BF16 ? 2 : 4;
+  a.stream = size_t(L.R) * L.D * es >= STREAM_BYTES ? 1u : 0u;
   const uint32_t vec = L.P % 4 == 0 && aligned(Y, 4 * es) && (!I_out || aligned(I_out, 16)) ? 1 : 0;
   const bool lin = L.P == 1;
   // Wave tiles of 64 pixels x 64 channels, each wave its own, while they give every SIMD two

@@ -95,7 +95,8 @@ __device__ __forceinline__ int acc_row(int v, int g) { return 8 * (v >> 2) + 4 *
 // Zero `count` elements of `esize` bytes starting at element `first` of `base`, by the
 // `nthr` threads of a block: 16-byte stores where the run is 16-byte aligned, bytes of
 // the ragged ends one element at a time.
-__device__ void zero_run(void *base, size_t first, size_t count, int esize, int tid, int nthr) {
+__device__ void zero_run(void *base, size_t first, size_t count, int esize, int tid, int nthr,
+                         bool stream) {
   char *p = static_cast<char *>(base) + first * esize;
   const size_t bytes = count * esize;
   const size_t head = (16 - (reinterpret_cast<uintptr_t>(p) & 15)) & 15;
@@ -106,7 +107,15 @@ __device__ void zero_run(void *base, size_t first, size_t count, int esize, int 
     else reinterpret_cast<uint16_t *>(p)[e] = 0;
   }
   uint4 *v = reinterpret_cast<uint4 *>(p + lead);
-  for (size_t e = tid; e < nvec; e += nthr) v[e] = make_uint4(0u, 0u, 0u, 0u);
+  if (stream) {
+    for (size_t e = tid; e < nvec; e += nthr) {
+      stream_fence();
+      __builtin_nontemporal_store(u32x4{0u, 0u, 0u, 0u}, reinterpret_cast<u32x4 *>(v + e));
+      stream_fence();
+    }
+  } else {
+    for (size_t e = tid; e < nvec; e += nthr) v[e] = make_uint4(0u, 0u, 0u, 0u);
+  }
   char *tail = p + lead + nvec * 16;
   const size_t rest = bytes - lead - nvec * 16;
   for (size_t e = tid; e * esize < rest; e += nthr) {
@@ -440,7 +449,7 @@ __device__ __forceinline__ void dwb_consume(const DwBigBatch<RT, CT> &b, const u
 // writing the slice's partial sums (in the split kernel's form, sum over the slice of
 // A_r s_r with A_r the MFMA code byte: 2 sum A b - sum A) and its set-bit counts for the
 // finish pass.  Grid: S slices (fastest) x slot blocks x column groups.
-template <bool B8, int RT, int CT, int ST, bool SPLIT = false>
+template <bool B8, int RT, int CT, int ST, bool SPLIT = false, bool STREAM = false>
 __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = wave_id();
@@ -589,15 +598,16 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
           for (int k = 0; k < 8; ++k) {
             const int row = 4 * k + (lane >> 4);
             if (jt + row >= a.D || col >= a.K) continue;
-            const float4 f = *reinterpret_cast<const float4 *>(st + row * SP + 4 * (lane & 15));
+            const u32x4 f = *reinterpret_cast<const u32x4 *>(st + row * SP + 4 * (lane & 15));
             float *dst = a.dW + size_t(drow[k]) * a.K + col;
             if (vec) {
-              *reinterpret_cast<float4 *>(dst) = f;
+              if constexpr (STREAM) __builtin_nontemporal_store(f, reinterpret_cast<u32x4 *>(dst));
+              else *reinterpret_cast<u32x4 *>(dst) = f;
             } else {
-              dst[0] = f.x;
-              if (col + 1 < a.K) dst[1] = f.y;
-              if (col + 2 < a.K) dst[2] = f.z;
-              if (col + 3 < a.K) dst[3] = f.w;
+              dst[0] = __uint_as_float(f[0]);
+              if (col + 1 < a.K) dst[1] = __uint_as_float(f[1]);
+              if (col + 2 < a.K) dst[2] = __uint_as_float(f[2]);
+              if (col + 3 < a.K) dst[3] = __uint_as_float(f[3]);
             }
           }
           __builtin_amdgcn_wave_barrier();    // the next tiles' copy waits for these reads
@@ -656,14 +666,14 @@ uint32_t dw_split_blocks(const DwArgs &a, int rt) {
 
 // Long contractions: two waves per SIMD (the accumulators and the word ring fit 256
 // registers).
-template <bool B8>
+template <bool B8, bool STREAM>
 __global__ __launch_bounds__(DW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mfma_dw_big(DwArgs a) {
-  dw_big_body<B8, 2, 4, 4>(a, blockIdx.x);
+  dw_big_body<B8, 2, 4, 4, false, STREAM>(a, blockIdx.x);
 }
 // Short contractions: three waves per SIMD, for the stores.
-template <bool B8>
+template <bool B8, bool STREAM>
 __global__ __launch_bounds__(DW_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_mfma_dw_short(DwArgs a) {
-  dw_big_body<B8, 2, 2, 2>(a, blockIdx.x);
+  dw_big_body<B8, 2, 2, 2, false, STREAM>(a, blockIdx.x);
 }
 
 template <bool B8, bool DIRECT>
@@ -819,6 +829,7 @@ struct DxArgs {
   uint32_t wide;                 // 0: split form; CT >= 1: register tiles, CT channel tiles
   uint32_t cblocks;              // register-tile form: channel blocks of 32 CT channels
   FastDiv divCb;
+  uint32_t stream;               // dX by non-temporal stores (STREAM_BYTES)
   const float *ste;              // training: X; dX (float32) is 0 where |X| <= 1 does not hold
 };
 
@@ -869,8 +880,8 @@ __device__ __forceinline__ void dx_zero_pool(const DxArgs &a, uint32_t zb, uint3
     const size_t n = size_t(a.kept[uint32_t(count) + slot]);
     const size_t first = size_t(piece) * DX_ZCHUNK;
     const size_t len = min(size_t(DX_ZCHUNK), size_t(a.CHW) - first);
-    zero_run(a.dX, n * a.CHW + first, len, a.dx_t == FQT_BF16 ? 2 : 4, t, DX_THREADS);
-    if (a.I_out) zero_run(a.I_out, n * a.CHW + first, len, 4, t, DX_THREADS);
+    zero_run(a.dX, n * a.CHW + first, len, a.dx_t == FQT_BF16 ? 2 : 4, t, DX_THREADS, a.stream);
+    if (a.I_out) zero_run(a.I_out, n * a.CHW + first, len, 4, t, DX_THREADS, false);
   }
 }
 
@@ -1090,19 +1101,23 @@ __device__ __forceinline__ void dx_store_tile(const DxArgs &a, const int32_t *pi
         float4 x[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) x[k] = x4[k];
+        uint4 o[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const uint4 v = s4[k];
-          d4[k] = make_uint4(__builtin_fabsf(x[k].x) <= 1.0f ? v.x : 0u,
-                             __builtin_fabsf(x[k].y) <= 1.0f ? v.y : 0u,
-                             __builtin_fabsf(x[k].z) <= 1.0f ? v.z : 0u,
-                             __builtin_fabsf(x[k].w) <= 1.0f ? v.w : 0u);
+          o[k] = make_uint4(__builtin_fabsf(x[k].x) <= 1.0f ? v.x : 0u,
+                            __builtin_fabsf(x[k].y) <= 1.0f ? v.y : 0u,
+                            __builtin_fabsf(x[k].z) <= 1.0f ? v.z : 0u,
+                            __builtin_fabsf(x[k].w) <= 1.0f ? v.w : 0u);
         }
+        store16s(d4, 1, o, a.stream);
         return;
       }
     }
+    uint4 o[16 / PER16];
 #pragma unroll
-    for (int k = 0; k < 16 / PER16; ++k) d4[k] = s4[k];
+    for (int k = 0; k < 16 / PER16; ++k) o[k] = s4[k];
+    store16s(d4, 1, o, a.stream);
   } else {
     for (int j = 0; j < 16; ++j) {
       const int o = pix_out[pb + j];
@@ -1628,6 +1643,7 @@ DxArgs make_dx_args(const Layer &L, const fqt_qgrad &q, const int8_t *wsb,
   a.codes = q.psq_codes; a.kept = q.psq_kept; a.count = q.psq_count;
   a.scale = q.psq_scale; a.offset = q.psq_offset; a.slot_sz = nullptr; a.wsb = wsb;
   a.wlsum = wlsum; a.ste = nullptr;
+  a.stream = size_t(L.N) * L.C * L.HW * (L.dx_t == FQT_BF16 ? 2 : 4) >= STREAM_BYTES ? 1u : 0u;
   a.dX = dX; a.I_out = I_out; a.dx_t = L.dx_t;
   a.N = uint32_t(L.N); a.C = uint32_t(L.C); a.H = uint32_t(L.H); a.W = uint32_t(L.W);
   a.HW = uint32_t(L.HW); a.Ho = uint32_t(L.Ho); a.Wo = uint32_t(L.Wo); a.P = uint32_t(L.P);
@@ -1696,12 +1712,16 @@ void launch_dw_split(const DwArgs &a, int rt, hipStream_t s) {
 
 template <bool B8>
 void launch_dw_big(const DwArgs &a, hipStream_t s) {
-  if (a.Wr >= uint32_t(DWB_LONG_WORDS))
-    hipLaunchKernelGGL(k_mfma_dw_big<B8>, dim3(dw_big_blocks(a.D, a.K, 2, 4)), dim3(DW_THREADS),
-                       0, s, a);
-  else
-    hipLaunchKernelGGL(k_mfma_dw_short<B8>, dim3(dw_big_blocks(a.D, a.K, 2, 2)), dim3(DW_THREADS),
-                       0, s, a);
+  auto go = [&]<bool STREAM>() {
+    if (a.Wr >= uint32_t(DWB_LONG_WORDS))
+      hipLaunchKernelGGL((k_mfma_dw_big<B8, STREAM>), dim3(dw_big_blocks(a.D, a.K, 2, 4)),
+                         dim3(DW_THREADS), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_mfma_dw_short<B8, STREAM>), dim3(dw_big_blocks(a.D, a.K, 2, 2)),
+                         dim3(DW_THREADS), 0, s, a);
+  };
+  if (size_t(a.D) * a.K * 4 >= STREAM_BYTES) go.template operator()<true>();
+  else go.template operator()<false>();
 }
 
 template <bool B8>

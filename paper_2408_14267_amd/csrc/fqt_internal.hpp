@@ -295,6 +295,32 @@ __device__ __forceinline__ void load_oct(const void *p, int64_t i, float out[8])
   }
 }
 
+// Outputs of STREAM_BYTES and more go out with non-temporal stores: they do not fit beside
+// anything else in the 256 MB last-level cache, so no reader finds them there, and their dirty
+// lines would be written back under the next kernel's reads (dX of 411 MB: the next read of
+// 411 MB took 126 us instead of 74; dW of 411 MB: the pass 263 -> 206 us).
+constexpr size_t STREAM_BYTES = size_t(128) << 20;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// Keeps the compiler from merging the stores of a streaming branch with those of the other one
+// (which drops the hint): before and after them.
+__device__ __forceinline__ void stream_fence() { asm volatile("; stream"); }
+// N values to p[0], p[step], ... (the branch outside the stores, so that they issue together).
+template <int N>
+__device__ __forceinline__ void store16s(uint4 *p, size_t step, const uint4 (&v)[N], bool stream) {
+  if (stream) {
+    stream_fence();
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      __builtin_nontemporal_store(u32x4{v[k].x, v[k].y, v[k].z, v[k].w},
+                                  reinterpret_cast<u32x4 *>(p + k * step));
+    stream_fence();
+  } else {
+#pragma unroll
+    for (int k = 0; k < N; ++k) p[k * step] = v[k];
+  }
+}
+
 // Calls F.template operator()<DT>() with DT the compile-time dtype code of `dt`.
 template <typename F>
 __host__ void dispatch_dtype(int dt, F &&f) {
