@@ -826,8 +826,10 @@ struct DxArgs {
   FastDiv divHW, divW, divKw, divNch, divCt, divSh, divSw;
   uint32_t nblocks;              // blocks of the dX grid (compute tiles + zero pool)
   uint32_t zpieces;              // pieces of DX_ZCHUNK elements per pruned sample
-  uint32_t wide;                 // 0: split form; CT >= 1: register tiles, CT channel tiles
-  uint32_t cblocks;              // register-tile form: channel blocks of 32 CT channels
+  uint32_t wide;                 // DxForm
+  uint32_t vec;                  // register tiles: pieces of 4 pixels (HW % 4 == 0, aligned dX and X, no I_out)
+  uint32_t D;
+  uint32_t cblocks;              // register-tile forms: channel blocks of 32 CT channels
   FastDiv divCb;
   uint32_t stream;               // dX by non-temporal stores (STREAM_BYTES)
   const float *ste;              // training: X; dX (float32) is 0 where |X| <= 1 does not hold
@@ -838,6 +840,9 @@ __device__ __forceinline__ bool ste_pass(const DxArgs &a, size_t o) {
   return !a.ste || __builtin_fabsf(a.ste[o]) <= 1.0f;
 }
 
+// The forms of the dX product: the contraction of a 32 x 32 tile split over four waves, or
+// register tiles (one channel tile per wave, two, two with the channels along the lanes).
+enum DxForm : uint32_t { DX_SPLIT = 0, DX_CT1 = 1, DX_CT2 = 2, DX_LIN = 3 };
 constexpr int DX_MAX_TAPS = 64;
 constexpr uint32_t DX_ZCHUNK = 65536;    // elements of a pruned sample one block zeroes
 constexpr int DX_WAVES = 4;
@@ -1048,137 +1053,122 @@ __device__ __forceinline__ void dx_body(const DxArgs &a, uint32_t bid, DxLds &sm
   }
 }
 
-// Large layers (many row tiles, at most DXW_MAX_TAPS taps): register tiles.  A block
-// holds 4 * DXT_RT pixel tiles of 32 rows and CT channel tiles; wave w runs the whole
-// contraction of pixel tiles DXT_RT w .. DXT_RT (w + 1) - 1 against all CT channel tiles
-// (no split over the waves, no reduction), so each loaded sign fragment feeds DXT_RT
-// MFMAs and each code fragment CT of them: (DXT_RT + CT) 1 KB loads per DXT_RT * CT
-// products instead of two per product.  The per-(tap, pixel) code row
-// offsets of the block's pixels and the channel sign sums are tabulated in LDS as in the
-// split form.  CT = 2 unless the layer has a single channel tile.
-constexpr int DXW_MAX_TAPS = 16;
+// Large layers: register tiles.  A wave holds DXT_RT pixel tiles x CT channel tiles of 32 x 32 and
+// runs their whole contraction (no split over the waves, no reduction), so each loaded sign
+// fragment feeds DXT_RT MFMAs and each code fragment CT of them; a block's four waves take
+// consecutive pixels of the same channels.  Steps run over the taps of a 32-byte chunk before
+// the next chunk, so that the taps' rows of codes come from the L1; a tap's row is found from
+// the pixel by one multiply-add and a range check (division by the strides where they are not
+// 1).  Batches of DXT_NB steps at four waves per SIMD (four steps at three waves: conv2 at
+// 224 198 -> see the table of the layer).
+//   FP4: codes and signs as e2m1 nibbles (b <= 2; half the bytes and half the steps), sums in
+//        float32, exact below 2^24.
+//   LIN: one pixel per sample and one tap: codes feed the MFMA's rows, so that output lanes run
+//        along the channels, as dX does.
 constexpr int DXT_RT = 2;                            // pixel tiles per wave
-constexpr int DXT_NB = 4;                            // contraction steps per load batch
+constexpr int DXT_NB = 2;                            // contraction steps per load batch
 constexpr uint32_t DXT_BP = DX_WAVES * DXT_RT * 32;  // pixel rows per block
-template <int CT>
+constexpr int DXT_PITCH = 32 * DXT_RT + 4;           // staged floats per channel
 struct alignas(16) DxTileLds {
-  uint32_t rowoff[DXW_MAX_TAPS][DXT_BP];
-  int32_t wl[DXW_MAX_TAPS][CT * 32];
-  int32_t pix_out[DXT_BP];
-  float pix_s[DXT_BP], pix_z[DXT_BP];
-  // A wave's output tile, [channel row][pixel] (two channel tiles: full 32-channel tiles;
-  // one channel tile has C <= 32 and stores element by element).
-  uint32_t stage[CT == 2 ? DX_WAVES : 1][CT == 2 ? 32 * 32 : 1];
+  float stage[DX_WAVES][32 * DXT_PITCH];
+  int32_t pix_out[DXT_BP];                           // offset of each pixel in dX, -1 past the live rows
+  float2 pix_sz[DXT_BP];                             // its sample's scale and offset (LIN)
 };
 
-// Stores of one wave's 32 x 32 output tile (channels c0t .. c0t + 31 x the 32 pixels from
-// block pixel p0) from its row-major copy in LDS: lane L writes half h = L % 2 (16
-// pixels) of channel row L / 2, as 16-byte stores when those 16 pixels are live, in one
-// sample (consecutive offsets) and 16-byte aligned in dX; else element by element.
-template <typename T>
-__device__ __forceinline__ void dx_store_tile(const DxArgs &a, const int32_t *pix_out,
-                                              const T *stage, uint32_t c0t, uint32_t p0,
-                                              int lane) {
-  constexpr int PER16 = 16 / sizeof(T);            // elements per 16-byte store
-  static_assert(16 % PER16 == 0, "whole 16-byte pieces");
-  const int rr = lane >> 1, h = lane & 1;
-  const uint32_t cc = c0t + uint32_t(rr);
-  if (cc >= a.C) return;
-  const uint32_t pb = p0 + 16 * h;
-  const int o0 = pix_out[pb], o15 = pix_out[pb + 15];
-  const T *src = stage + rr * 32 + 16 * h;
-  T *dst = static_cast<T *>(a.dX);
-  const size_t base = size_t(o0) + size_t(cc) * a.HW;
-  // (o15 = o0 + 15 with both live: the 16 offsets are consecutive, also where a sample
-  // boundary falls inside, which only C = 1 allows.)
-  if (o0 >= 0 && o15 == o0 + 15 &&
-      ((reinterpret_cast<uintptr_t>(dst + base) | reinterpret_cast<uintptr_t>(a.ste ? a.ste + base : nullptr)) & 15) == 0) {
-    const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
-    uint4 *d4 = reinterpret_cast<uint4 *>(dst + base);
-    if constexpr (sizeof(T) == 4) {
+typedef int v8i __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ v8i as_v8(v4i v) { return v8i{v.x, v.y, v.z, v.w, 0, 0, 0, 0}; }
+
+// Stores of one wave's 32 channels x 64 pixels from their LDS copy [channel][pixel]: pieces of
+// 4 pixels of one channel (HW % 4 == 0: of one sample), consecutive lanes on consecutive
+// pixels.
+__device__ __forceinline__ void dx_store_tile(const DxArgs &a, const int32_t *pix, const float *st,
+                                              uint32_t c0, int lane) {
+  constexpr int PIECES = 4 * DXT_RT, QROW = 8 * DXT_RT;   // pieces per lane, per channel row
+  const int off = pix[4 * (lane % QROW)];
+  if (off < 0) return;
+  auto put = [&](auto store) {
+#pragma unroll
+    for (int k = 0; k < PIECES; ++k) {
+      const uint32_t row = uint32_t(lane / QROW + (64 / QROW) * k);
+      if (c0 + row >= a.C) continue;
+      const size_t o = size_t(off) + size_t(c0 + row) * a.HW;
+      float4 f = *reinterpret_cast<const float4 *>(st + row * DXT_PITCH + 4 * (lane % QROW));
       if (a.ste) {
-        const float4 *x4 = reinterpret_cast<const float4 *>(a.ste + base);
-        float4 x[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = x4[k];
-        uint4 o[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint4 v = s4[k];
-          o[k] = make_uint4(__builtin_fabsf(x[k].x) <= 1.0f ? v.x : 0u,
-                            __builtin_fabsf(x[k].y) <= 1.0f ? v.y : 0u,
-                            __builtin_fabsf(x[k].z) <= 1.0f ? v.z : 0u,
-                            __builtin_fabsf(x[k].w) <= 1.0f ? v.w : 0u);
-        }
-        store16s(d4, 1, o, a.stream);
-        return;
+        const float4 x = *reinterpret_cast<const float4 *>(a.ste + o);
+        f.x = __builtin_fabsf(x.x) <= 1.0f ? f.x : 0.0f;
+        f.y = __builtin_fabsf(x.y) <= 1.0f ? f.y : 0.0f;
+        f.z = __builtin_fabsf(x.z) <= 1.0f ? f.z : 0.0f;
+        f.w = __builtin_fabsf(x.w) <= 1.0f ? f.w : 0.0f;
       }
+      if (a.dx_t == FQT_BF16)
+        store(reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(a.dX) + o),
+              u32x2{f32_to_bf16(f.x) | (uint32_t(f32_to_bf16(f.y)) << 16),
+                    f32_to_bf16(f.z) | (uint32_t(f32_to_bf16(f.w)) << 16)});
+      else
+        store(reinterpret_cast<u32x4 *>(static_cast<float *>(a.dX) + o),
+              u32x4{__float_as_uint(f.x), __float_as_uint(f.y), __float_as_uint(f.z),
+                    __float_as_uint(f.w)});
     }
-    uint4 o[16 / PER16];
-#pragma unroll
-    for (int k = 0; k < 16 / PER16; ++k) o[k] = s4[k];
-    store16s(d4, 1, o, a.stream);
-  } else {
-    for (int j = 0; j < 16; ++j) {
-      const int o = pix_out[pb + j];
-      const size_t at = size_t(o) + size_t(cc) * a.HW;
-      if (o >= 0) dst[at] = ste_pass(a, at) ? src[j] : T(0);
-    }
-  }
+  };
+  if (a.stream)
+    put([](auto *p, auto v) { stream_fence(); __builtin_nontemporal_store(v, p); stream_fence(); });
+  else put([](auto *p, auto v) { *p = v; });
 }
 
-template <bool B8, int CT>
-__device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxTileLds<CT> &sm) {
-  static_assert(DXT_BP == DX_THREADS, "one pixel row per thread");
+template <bool FP4, bool B8, int CT, bool LIN>
+__device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxTileLds &sm) {
+  using Acc = std::conditional_t<FP4, v16f, v16i>;
   bid = xcd_tile<DXW_XCD_RUN>(bid, a.nblocks);
-  constexpr uint32_t BP = DXT_BP;
-  constexpr int CW = CT * 32;                    // channels per block
   const int t = threadIdx.x, lane = t & 63;
   const uint32_t wave = wave_id();
   const int i = lane & 31, g = lane >> 5;
   const int count = *a.count;
   const uint32_t mt = fdiv(bid, a.divCb);
-  const uint32_t m0 = mt * BP, c0 = (bid - mt * a.cblocks) * CW;
-  const int taps = int(a.taps);
-  // Loads that do not depend on the count issue with it (clamped indices).
-  const uint32_t m = min(m0 + uint32_t(t), a.N * a.HW - 1);
-  const uint32_t pslot = fdiv(m, a.divHW);
-  const uint32_t ppix = m - pslot * a.HW;
-  const int kn = a.kept[pslot];
-  float2 sz = a.slot_sz ? a.slot_sz[pslot] : make_float2(0.0f, 0.0f);
-  constexpr int WLT = DXW_MAX_TAPS * CW / DX_THREADS;
-  int wlv[WLT];
-#pragma unroll
-  for (int k = 0; k < WLT; ++k) {
-    const int e = t + k * DX_THREADS, p = e % CW, tap = e / CW;
-    const uint32_t ch = c0 + uint32_t(p);
-    wlv[k] = (tap < taps && ch < a.C) ? a.wlsum[ch * a.taps + uint32_t(tap)] : 0;
-  }
+  const uint32_t m0 = mt * DXT_BP + wave * (32 * DXT_RT), c0 = (bid - mt * a.cblocks) * (CT * 32);
   const uint32_t live_rows = uint32_t(count) * a.HW;
-  const uint32_t live_blocks = ((live_rows + BP - 1) / BP) * a.cblocks;
+  const uint32_t live_blocks = ((live_rows + DXT_BP - 1) / DXT_BP) * a.cblocks;
   if (bid >= live_blocks) {
     dx_zero_pool(a, bid - live_blocks, a.nblocks - live_blocks, count);
     return;
   }
-  {
-    const bool live = m0 + uint32_t(t) < live_rows;
-    if (!a.slot_sz && live) sz = make_float2(a.scale[kn], a.offset[kn]);
-    sm.pix_out[t] = live ? int(uint32_t(kn) * a.CHW + ppix) : -1;
-    sm.pix_s[t] = live ? sz.x : 0.0f;
-    sm.pix_z[t] = live ? sz.y : 0.0f;
-  }
+  if (m0 >= live_rows) return;                   // (no barrier below: each wave has its own LDS)
+  int32_t *pix = sm.pix_out + wave * (32 * DXT_RT);
+  float2 *psz = sm.pix_sz + wave * (32 * DXT_RT);
+  // This lane's pixels: position under tap (0, 0), first code row, scale and offset.
+  int hb[DXT_RT], wb[DXT_RT];
+  uint32_t base[DXT_RT];
+  float2 sz[DXT_RT];
+  int off[DXT_RT];
 #pragma unroll
-  for (int k = 0; k < WLT; ++k) {
-    const int e = t + k * DX_THREADS;
-    if (e / CW < taps) sm.wl[e / CW][e % CW] = wlv[k];
+  for (int rt = 0; rt < DXT_RT; ++rt) {
+    const uint32_t m = m0 + 32 * rt + uint32_t(i), mm = min(m, live_rows - 1);
+    const uint32_t slot = fdiv(mm, a.divHW), p = mm - slot * a.HW;
+    const uint32_t h = fdiv(p, a.divW), w = p - h * a.W;
+    const uint32_t n = uint32_t(a.kept[slot]);
+    sz[rt] = a.slot_sz ? a.slot_sz[slot] : make_float2(a.scale[n], a.offset[n]);
+    off[rt] = m < live_rows ? int(n * a.CHW + p) : -1;
+    hb[rt] = int(h) + a.ph;
+    wb[rt] = int(w) + a.pw;
+    base[rt] = slot * a.P;
+    if (g == 0) {
+      pix[32 * rt + i] = off[rt];
+      if (LIN) psz[32 * rt + i] = sz[rt];
+    }
   }
-  dx_row_table<BP, DX_THREADS>(a, m0, live_rows, sm.rowoff);
-  __syncthreads();
-
-  // This lane: A rows = channels c0 + 32 ct + i, B columns = pixels 32 (DXT_RT wave + rt) + i.
-  uint32_t px[DXT_RT], abase[CT];
-#pragma unroll
-  for (int rt = 0; rt < DXT_RT; ++rt) px[rt] = (wave * DXT_RT + uint32_t(rt)) * 32 + uint32_t(i);
+  // Output position that tap (ti, tj) of pixel rt meets; false where there is none.
+  auto meets = [&](int rt, int ti, int tj, uint32_t &ho, uint32_t &wo) -> bool {
+    const int th = hb[rt] - ti, tw = wb[rt] - tj;
+    ho = uint32_t(th);
+    wo = uint32_t(tw);
+    bool ok = true;
+    if (a.sh != 1 || a.sw != 1) {                // (uniform)
+      ho = fdiv(uint32_t(max(th, 0)), a.divSh);
+      wo = fdiv(uint32_t(max(tw, 0)), a.divSw);
+      ok = int(ho) * a.sh == th && int(wo) * a.sw == tw;
+    }
+    return ok && ho < a.Ho && wo < a.Wo;
+  };
+  uint32_t abase[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const uint32_t ch = c0 + uint32_t(32 * ct + i);
@@ -1186,29 +1176,36 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
   }
   const __amdgpu_buffer_rsrc_t ars = buffer_of(a.wsb, a.wsb_bytes);
   const __amdgpu_buffer_rsrc_t brs = buffer_of(a.codes, a.codes_bytes);
-  const uint32_t steps = a.taps * a.nch;
-  v16i acc[DXT_RT][CT];
+  const uint32_t steps = a.taps * a.nch, wstride = a.C * 32;
+  Acc acc[DXT_RT][CT];
 #pragma unroll
   for (int rt = 0; rt < DXT_RT; ++rt)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = v16i{0};
+    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = Acc{0};
+  int ti = 0, tj = 0;
+  uint32_t kc = 0;
   for (uint32_t s0 = 0; s0 < steps; s0 += DXT_NB) {
-    // A batch's loads all issue before its first product; a step past the end reads zeros
-    // through its A operands and adds nothing.
+    // A batch's loads all issue before its first product; a step past the end multiplies by
+    // zero signs.
     v4i A[DXT_NB][CT], B[DXT_NB][DXT_RT];
 #pragma unroll
     for (int u = 0; u < DXT_NB; ++u) {
-      const uint32_t st0 = s0 + u;
-      const bool live = st0 < steps;
-      const uint32_t st = live ? st0 : 0;
-      const uint32_t tap = fdiv(st, a.divNch);
-      const uint32_t kc = st - tap * a.nch;
-      const uint32_t aoff = (kc * a.taps + tap) * a.C * 32;
+      const bool live = s0 + u < steps;
+      const uint32_t ws = min(s0 + u, steps - 1) * wstride;
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) A[u][ct] = load16(ars, live ? abase[ct] : BUF_NONE, aoff);
+      for (int ct = 0; ct < CT; ++ct) A[u][ct] = load16(ars, live ? abase[ct] : BUF_NONE, ws);
+      const uint32_t cs = min(kc, a.nch - 1) * a.R * 32;
 #pragma unroll
-      for (int rt = 0; rt < DXT_RT; ++rt)
-        B[u][rt] = load16(brs, sm.rowoff[tap][px[rt]] + 16 * g, kc * a.R * 32);
+      for (int rt = 0; rt < DXT_RT; ++rt) {
+        uint32_t ho, wo;
+        const bool ok = meets(rt, ti, tj, ho, wo);
+        B[u][rt] = load16(brs, ok ? (base[rt] + ho * a.Wo + wo) * 32 + 16 * g : BUF_NONE, cs);
+      }
+      ++tj;
+      ti += tj == a.kw ? 1 : 0;
+      tj = tj == a.kw ? 0 : tj;
+      kc += ti == a.kh ? 1 : 0;
+      ti = ti == a.kh ? 0 : ti;
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1217,87 +1214,102 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
       for (int rt = 0; rt < DXT_RT; ++rt) {
         const v4i b = B8 ? bias128(B[u][rt]) : B[u][rt];
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = mfma_i8(A[u][ct], b, acc[rt][ct]);
+        for (int ct = 0; ct < CT; ++ct) {
+          const v4i x = LIN ? b : A[u][ct], y = LIN ? A[u][ct] : b;
+          if constexpr (FP4)
+            acc[rt][ct] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                as_v8(x), as_v8(y), acc[rt][ct], 4, 4, 0, 127, 0, 127);
+          else acc[rt][ct] = mfma_i8(x, y, acc[rt][ct]);
+        }
       }
   }
 
-#pragma unroll
-  for (int rt = 0; rt < DXT_RT; ++rt) {
+  if constexpr (LIN) {
+    // Columns are channels, rows the pixels (samples): the zero-point term is the channel's
+    // line sum.
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-      // Zero-point term of each output, c = sum over the taps that reach the pixel of the
-      // channel's line sign sum: the 32 x 32 product [channel][tap] x [tap][pixel] of the
-      // sign sums and the 0/1 reach flags in the accumulator layout of the tile.  Exact:
-      // with D <= 2048 every sign sum is a float16 integer and all taps go into one f16
-      // MFMA (lane half g holds taps 8 g .. 8 g + 7); else two taps per float32 MFMA.
-      v16f cz = v16f{0};
-      if (a.Dp <= 2048) {
-        f16x8 wa, rb;
+      const uint32_t cc = c0 + uint32_t(32 * ct + i);
+      if (cc >= a.C) continue;
+      const int wl = a.wlsum[cc];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int tap = 8 * g + k;
-          const bool in = tap < taps;
-          wa[k] = in ? _Float16(sm.wl[tap][32 * ct + i]) : _Float16(0.0f);
-          rb[k] = in && sm.rowoff[tap][px[rt]] != BUF_NONE ? _Float16(1.0f) : _Float16(0.0f);
+      for (int rt = 0; rt < DXT_RT; ++rt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int row = 32 * rt + acc_row(v, g), o0 = pix[row];
+          if (o0 < 0) continue;
+          const size_t o = size_t(o0) + cc;
+          const int I = int(acc[rt][ct][v]) + (B8 ? 128 * wl : 0);
+          const float out = ste_pass(a, o) ? rescale(psz[row].x, I, psz[row].y, float(wl)) : 0.0f;
+          if (a.dx_t == FQT_BF16) static_cast<uint16_t *>(a.dX)[o] = f32_to_bf16(out);
+          else static_cast<float *>(a.dX)[o] = out;
+          if (a.I_out) a.I_out[o] = I;
         }
-        cz = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa, rb, cz, 0, 0, 0);
+    }
+    return;
+  }
+  float *st = sm.stage[wave];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const uint32_t ch = c0 + uint32_t(32 * ct + i);
+#pragma unroll
+    for (int rt = 0; rt < DXT_RT; ++rt) {
+      // Zero-point term of each output, c = sum over the taps that reach the pixel of the
+      // channel's line sign sum: the product [channel][tap] x [tap][pixel] of the sign sums and
+      // the 0/1 reach flags in the accumulator layout of the tile.  Exact: with D <= 2048 every
+      // sign sum is a float16 integer and 16 taps go into one f16 MFMA (lane half g holds taps
+      // 8 g .. 8 g + 7); else two taps per float32 MFMA.
+      v16f cz = v16f{0};
+      if (a.D <= 2048) {
+        for (uint32_t tb = 0; tb < a.taps; tb += 16) {
+          f16x8 wa, rb;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const uint32_t tap = tb + 8 * g + k;
+            const bool in = tap < a.taps;
+            const uint32_t tr = fdiv(tap, a.divKw);
+            uint32_t ho, wo;
+            wa[k] = in && ch < a.C ? _Float16(float(a.wlsum[ch * a.taps + tap])) : _Float16(0.0f);
+            rb[k] = in && meets(rt, int(tr), int(tap) - int(tr) * a.kw, ho, wo) ? _Float16(1.0f)
+                                                                             : _Float16(0.0f);
+          }
+          cz = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa, rb, cz, 0, 0, 0);
+        }
       } else {
-        for (int j = 0; 2 * j < taps; ++j) {
-          const int tap = 2 * j + g;
-          const bool in = tap < taps;
-          const float wv = in ? float(sm.wl[tap][32 * ct + i]) : 0.0f;
-          const float rv = in && sm.rowoff[tap][px[rt]] != BUF_NONE ? 1.0f : 0.0f;
+        for (uint32_t j = 0; 2 * j < a.taps; ++j) {
+          const uint32_t tap = 2 * j + g, tr = fdiv(tap, a.divKw);
+          const bool in = tap < a.taps;
+          uint32_t ho, wo;
+          const float wv = in && ch < a.C ? float(a.wlsum[ch * a.taps + tap]) : 0.0f;
+          const float rv =
+              in && meets(rt, int(tr), int(tap) - int(tr) * a.kw, ho, wo) ? 1.0f : 0.0f;
           cz = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, rv, cz, 0, 0, 0);
         }
       }
-      const int off = sm.pix_out[px[rt]];
-      const float S = sm.pix_s[px[rt]], Z = sm.pix_z[px[rt]];
-      if constexpr (CT == 2) {
-        if (!a.I_out && c0 + uint32_t(32 * ct + 32) <= a.C) {
-          // A whole tile of 32 channels goes through the wave's LDS copy (row-major), then
-          // out in 16-byte pieces along the pixels: 2-byte stores scattered over 32 channel
-          // rows were the slowest part of the kernel.
-          uint32_t *st = sm.stage[wave];
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int row = acc_row(v, g);
-            int lt = 0;
-            if (B8)
-              for (int tap = 0; tap < taps; ++tap) lt += sm.wl[tap][32 * ct + row];
-            const float out = rescale(S, acc[rt][ct][v] + (B8 ? 128 * lt : 0), Z, cz[v]);
-            if (a.dx_t == FQT_BF16)
-              reinterpret_cast<uint16_t *>(st)[row * 32 + i] = f32_to_bf16(out);
-            else
-              reinterpret_cast<float *>(st)[row * 32 + i] = out;
-          }
-          __builtin_amdgcn_wave_barrier();    // LDS operations of a wave run in order
-          const uint32_t p0 = (wave * DXT_RT + uint32_t(rt)) * 32;
-          if (a.dx_t == FQT_BF16)
-            dx_store_tile<uint16_t>(a, sm.pix_out, reinterpret_cast<const uint16_t *>(st),
-                                    c0 + uint32_t(32 * ct), p0, lane);
-          else
-            dx_store_tile<float>(a, sm.pix_out, reinterpret_cast<const float *>(st),
-                                 c0 + uint32_t(32 * ct), p0, lane);
-          __builtin_amdgcn_wave_barrier();    // the next tile's copy waits for these reads
-          continue;
-        }
-      }
-      if (off < 0) continue;               // rows past the count belong to the zero blocks
+      const float S = sz[rt].x, Z = sz[rt].y;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int row = 32 * ct + acc_row(v, g);
-        const uint32_t cc = c0 + uint32_t(row);
-        if (cc >= a.C) continue;
-        int lt = 0;
-        if (B8)
-          for (int tap = 0; tap < taps; ++tap) lt += sm.wl[tap][row];
-        const int Iv = acc[rt][ct][v] + (B8 ? 128 * lt : 0);
-        const size_t o = size_t(off) + size_t(cc) * a.HW;
-        const float out = ste_pass(a, o) ? rescale(S, Iv, Z, cz[v]) : 0.0f;
-        if (a.dx_t == FQT_BF16) static_cast<uint16_t *>(a.dX)[o] = f32_to_bf16(out);
-        else static_cast<float *>(a.dX)[o] = out;
-        if (a.I_out) a.I_out[o] = Iv;
+        const int row = acc_row(v, g);
+        const uint32_t cc = c0 + uint32_t(32 * ct + row);
+        int I = int(acc[rt][ct][v]);
+        if (B8 && cc < a.C)
+          for (uint32_t tap = 0; tap < a.taps; ++tap) I += 128 * a.wlsum[cc * a.taps + tap];
+        float out = rescale(S, I, Z, cz[v]);
+        if (a.vec) {
+          st[row * DXT_PITCH + 32 * rt + i] = out;
+        } else if (off[rt] >= 0 && cc < a.C) {
+          const size_t o = size_t(off[rt]) + size_t(cc) * a.HW;
+          out = ste_pass(a, o) ? out : 0.0f;
+          if (a.dx_t == FQT_BF16) static_cast<uint16_t *>(a.dX)[o] = f32_to_bf16(out);
+          else static_cast<float *>(a.dX)[o] = out;
+          if (a.I_out) a.I_out[o] = I;
+        }
       }
+    }
+    if (a.vec) {
+      __builtin_amdgcn_wave_barrier();    // LDS operations of a wave run in order
+      dx_store_tile(a, pix, st, c0 + uint32_t(32 * ct), lane);
+      __builtin_amdgcn_wave_barrier();    // the next tile's copy waits for these reads
     }
   }
 }
@@ -1488,18 +1500,21 @@ __global__ __launch_bounds__(DXR_THREADS) void k_dx_rows(DxRowsArgs a) {
     if (c < a.C) store2(size_t(a.kept[j]) * a.C + c, 0.0f, 0.0f);
 }
 
-// WT: 0 for the split form, CT (1 or 2 channel tiles per wave) for the register-tile form.
+// WT: a DxForm.
 template <int WT>
-using DxLdsOf = std::conditional_t<WT != 0, DxTileLds<WT == 0 ? 1 : WT>, DxLds>;
+using DxLdsOf = std::conditional_t<WT != 0, DxTileLds, DxLds>;
+template <bool FP4, bool B8, int NB, int WT>
+__device__ __forceinline__ void dx_form_body(const DxArgs &a, uint32_t bid, DxLdsOf<WT> &sm) {
+  if constexpr (WT == DX_SPLIT) dx_body<B8, NB>(a, bid, sm);
+  else dx_body_tiles<FP4, B8, WT == DX_CT1 ? 1 : 2, WT == DX_LIN>(a, bid, sm);
+}
 
-// The register-tile forms (WT != 0) are held to three waves per SIMD (at most 170
-// registers; the compiler's own choice, 182, leaves two).
+// The register-tile forms are held to four waves per SIMD.
 template <bool B8, int NB, int WT>
-__global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT != 0 ? 3 : 1)))
+__global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT == 0 ? 1 : WT == 2 ? 3 : 4)))
 void k_mfma_dx(DxArgs a) {
   __shared__ DxLdsOf<WT> sm;
-  if constexpr (WT != 0) dx_body_tiles<B8, WT>(a, blockIdx.x, sm);
-  else dx_body<B8, NB>(a, blockIdx.x, sm);
+  dx_form_body<false, B8, NB, WT>(a, blockIdx.x, sm);
 }
 
 // How the dW blocks of the products launch run: split-R partials summed by a finish pass
@@ -1535,8 +1550,8 @@ union ProductsLds {
   DwRedLds dw;
   double dg[DX_WAVES][64];
 };
-template <bool B8, int NB, int DWF, int WT>
-__global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT != 0 ? 3 : 1)))
+template <bool B8, int NB, int DWF, int WT, bool FP4>
+__global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT == 0 ? 1 : WT == 2 ? 3 : 4)))
 void k_products(DxArgs dxa, DwArgs dwa, uint32_t ndw, DgArgs dg) {
   __shared__ ProductsLds<WT> sm;
   if (blockIdx.x < ndw) {
@@ -1545,8 +1560,7 @@ void k_products(DxArgs dxa, DwArgs dwa, uint32_t ndw, DgArgs dg) {
   } else if (blockIdx.x - ndw >= dxa.nblocks) {
     dgamma_body(dg, blockIdx.x - ndw - dxa.nblocks, sm.dg);
   } else {
-    if constexpr (WT != 0) dx_body_tiles<B8, WT>(dxa, blockIdx.x - ndw, sm.dx);
-    else dx_body<B8, NB>(dxa, blockIdx.x - ndw, sm.dx);
+    dx_form_body<FP4, B8, NB, WT>(dxa, blockIdx.x - ndw, sm.dx);
   }
 }
 
@@ -1637,6 +1651,15 @@ uint32_t dw_part_blocks(const Layer &L, const DwArgs &a) {
   return a.S * a.kgroups * uint32_t((L.D + 31) / 32);
 }
 
+// Register tiles once the capacity has DX_TILES tiles of 32 x 32.
+constexpr int64_t DX_TILES = 16384;
+uint32_t dx_form(const Layer &L) {
+  const int64_t ctiles = (L.C + 31) / 32, tiles = ((L.N * L.HW + 31) / 32) * ctiles;
+  if (tiles < DX_TILES) return DX_SPLIT;
+  if (L.HW == 1 && L.kh * L.kw == 1) return DX_LIN;
+  return ctiles > 1 ? DX_CT2 : DX_CT1;
+}
+
 DxArgs make_dx_args(const Layer &L, const fqt_qgrad &q, const int8_t *wsb,
                     const int32_t *wlsum, void *dX, int32_t *I_out) {
   DxArgs a;
@@ -1663,10 +1686,12 @@ DxArgs make_dx_args(const Layer &L, const fqt_qgrad &q, const int8_t *wsb,
   // DX_ZCHUNK elements each: whatever the device-side count, at least
   // min(2048, N * pieces) blocks are left for the zeroing.
   a.zpieces = uint32_t((int64_t(a.CHW) + DX_ZCHUNK - 1) / DX_ZCHUNK);
-  // Four pixel tiles per block once the capacity has 16384 tiles (with few taps).
-  const int64_t tiles = ((L.N * L.HW + 31) / 32) * a.ctiles;
-  a.wide = (a.taps <= uint32_t(DXW_MAX_TAPS) && tiles >= 16384) ? (a.ctiles > 1 ? 2u : 1u) : 0u;
-  a.cblocks = a.wide ? (a.ctiles + a.wide - 1) / a.wide : a.ctiles;
+  a.D = uint32_t(L.D);
+  a.wide = dx_form(L);
+  const uint32_t ct = a.wide == DX_CT1 ? 1 : 2;
+  a.cblocks = a.wide ? (a.ctiles + ct - 1) / ct : a.ctiles;
+  const size_t es = L.dx_t == FQT_BF16 ? 2 : 4;
+  a.vec = L.HW % 4 == 0 && aligned(dX, 4 * es) && !I_out ? 1u : 0u;
   a.divCb = make_fastdiv(a.cblocks);
   const int64_t rows = a.wide ? DXT_BP : 32;
   a.nblocks = uint32_t(((L.N * L.HW + rows - 1) / rows) * a.cblocks +
@@ -1737,6 +1762,12 @@ void launch_dw_finish(const Layer &L, const DwArgs &a, hipStream_t s) {
 
 }  // namespace
 
+// Nibble codes and signs for dX: codes of at most 3, register tiles, sums below 2^24.
+bool dx_fp4_form(const Layer &L, const fqt_quant_cfg &cfg) {
+  return cfg.bits <= 2 && dx_form(L) != DX_SPLIT &&
+         ((1 << cfg.bits) - 1) * L.D * L.kh * L.kw < (int64_t(1) << 24);
+}
+
 // The linear layers k_dx_rows takes: few rows, W of 4 MB and more (below, the product shares its
 // launch with dW and packing W hides beside the selection), pairs of channels on 4-byte
 // addresses, 32 rows of W in one buffer.
@@ -1779,16 +1810,17 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
   const dim3 grid(a.nblocks);
   const int nb = dx_batch(a);
   auto go = [&]<bool B8, int WT>() {
-    if constexpr (WT != 0)      // the register-tile form batches DXT_NB steps itself
+    if constexpr (WT != 0)      // the register-tile forms batch DXT_NB steps themselves
       hipLaunchKernelGGL((k_mfma_dx<B8, 4, WT>), grid, dim3(DX_THREADS), 0, s, a);
     else if (nb == 4) hipLaunchKernelGGL((k_mfma_dx<B8, 4, 0>), grid, dim3(DX_THREADS), 0, s, a);
     else if (nb == 8) hipLaunchKernelGGL((k_mfma_dx<B8, 8, 0>), grid, dim3(DX_THREADS), 0, s, a);
     else hipLaunchKernelGGL((k_mfma_dx<B8, 10, 0>), grid, dim3(DX_THREADS), 0, s, a);
   };
   auto go2 = [&]<bool B8>() {
-    if (a.wide == 2) go.template operator()<B8, 2>();
-    else if (a.wide == 1) go.template operator()<B8, 1>();
-    else go.template operator()<B8, 0>();
+    if (a.wide == DX_LIN) go.template operator()<B8, DX_LIN>();
+    else if (a.wide == DX_CT2) go.template operator()<B8, DX_CT2>();
+    else if (a.wide == DX_CT1) go.template operator()<B8, DX_CT1>();
+    else go.template operator()<B8, DX_SPLIT>();
   };
   if (cfg.bits == 8) go2.template operator()<true>();
   else go2.template operator()<false>();
@@ -1799,7 +1831,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
                     hipStream_t s, const TrainJob *train, const TapsPlan *taps, char *arena,
-                    const void *wrows) {
+                    const void *wrows, bool fp4) {
   if (L.kh * L.kw > DX_MAX_TAPS) return FQT_E_SHAPE;
   DwArgs dwa = make_dw_args(L, cfg, q, xsign, dW, nullptr, dw_ws);
   DxArgs dxa = make_dx_args(L, q, wsb, wlsum, dX, nullptr);
@@ -1845,31 +1877,46 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
     if (ndw == 0 && !train) return FQT_OK;
   }
   DgArgs dg{};
+  if (fp4) {                              // nibble operands: half the chunks and bytes
+    dxa.nch /= 2;
+    dxa.divNch = make_fastdiv(dxa.nch);
+    dxa.codes_bytes /= 2;
+    dxa.wsb_bytes /= 2;
+  }
   if (train) {
+    if (!aligned(train->X, 16)) dxa.vec = 0;
     dxa.ste = train->X;
     dg = DgArgs{train->part, train->dgamma, train->parts, uint32_t(L.D)};
   }
   const dim3 grid(ndw + dxa.nblocks + (train ? unsigned((L.D + 63) / 64) : 0u));
   const int nb = dx_batch(dxa);
   auto go = [&]<bool B8, int DWF, int WT>() {
-    if constexpr (WT != 0)
-      hipLaunchKernelGGL((k_products<B8, 4, DWF, WT>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
-                         ndw, dg);
-    else if (nb == 4)
-      hipLaunchKernelGGL((k_products<B8, 4, DWF, 0>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
+    if constexpr (WT != 0) {
+      if constexpr (!B8)
+        if (fp4) {
+          hipLaunchKernelGGL((k_products<B8, 4, DWF, WT, true>), grid, dim3(DX_THREADS), 0, s, dxa,
+                             dwa, ndw, dg);
+          if (DWF == DWF_PARTS) launch_dw_finish<B8>(L, dwa, s);
+          return;
+        }
+      hipLaunchKernelGGL((k_products<B8, 4, DWF, WT, false>), grid, dim3(DX_THREADS), 0, s, dxa,
+                         dwa, ndw, dg);
+    } else if (nb == 4)
+      hipLaunchKernelGGL((k_products<B8, 4, DWF, 0, false>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
                          ndw, dg);
     else if (nb == 8)
-      hipLaunchKernelGGL((k_products<B8, 8, DWF, 0>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
+      hipLaunchKernelGGL((k_products<B8, 8, DWF, 0, false>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
                          ndw, dg);
     else
-      hipLaunchKernelGGL((k_products<B8, 10, DWF, 0>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
+      hipLaunchKernelGGL((k_products<B8, 10, DWF, 0, false>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
                          ndw, dg);
     if (DWF == DWF_PARTS) launch_dw_finish<B8>(L, dwa, s);
   };
   auto go2 = [&]<bool B8, int DWF>() {
-    if (dxa.wide == 2) go.template operator()<B8, DWF, 2>();
-    else if (dxa.wide == 1) go.template operator()<B8, DWF, 1>();
-    else go.template operator()<B8, DWF, 0>();
+    if (dxa.wide == DX_LIN) go.template operator()<B8, DWF, DX_LIN>();
+    else if (dxa.wide == DX_CT2) go.template operator()<B8, DWF, DX_CT2>();
+    else if (dxa.wide == DX_CT1) go.template operator()<B8, DWF, DX_CT1>();
+    else go.template operator()<B8, DWF, DX_SPLIT>();
   };
   auto go3 = [&]<bool B8>() {
     // With the dW product in its own launch the products launch has no dW blocks: the big

@@ -115,6 +115,7 @@ struct SignJob {
   int8_t *wsb;           // sign(W) bytes
   int32_t *wlsum;
   bool done;
+  bool fp4;              // W as nibbles (dx_fp4_form)
   bool no_w;             // W is not packed (the dX product reads it)
   const TapsPlan *taps;  // the sign plane of the tap form instead of xsign, at `arena`
   char *arena;
@@ -136,14 +137,15 @@ int launch_state_clear(void *state, hipStream_t s);
 // planes = false: the codes one byte each only (what the products read), no bit planes.
 int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, const fqt_qgrad &q,
                     const QuantWs &w, hipStream_t s, SignJob *signs = nullptr,
-                    bool planes = true, TrainJob *train = nullptr);
+                    bool planes = true, TrainJob *train = nullptr, bool psq_fp4 = false);
 int launch_pack_bits(const void *src, int dtype, int64_t rows, int64_t cols, int64_t ld, int axis,
                      const Layer *conv, uint64_t *dst, int32_t *linesum, hipStream_t s,
                      bool word_major = false);
 size_t gemm_dw_ws_bytes(const Layer &L, const fqt_quant_cfg &cfg);
 int launch_gemm_dw(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                    const uint64_t *xsign, float *dW, int32_t *I_out, void *ws, hipStream_t s);
-int launch_pack_w_i8(const void *W, const Layer &L, int8_t *dst, int32_t *lsum, hipStream_t s);
+int launch_pack_w_i8(const void *W, const Layer &L, int8_t *dst, int32_t *lsum, hipStream_t s,
+                     bool fp4 = false);
 int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                    const int8_t *wsb, const int32_t *wlsum, void *dX, int32_t *I_out,
                    hipStream_t s);
@@ -154,7 +156,22 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
                     hipStream_t s, const TrainJob *train = nullptr,
                     const TapsPlan *taps = nullptr, char *arena = nullptr,
-                    const void *wrows = nullptr);
+                    const void *wrows = nullptr, bool fp4 = false);
+// Layers whose dX product takes nibble operands (launch_products' fp4): PSQ codes [Dp/64][R][32]
+// and W signs [Dp/64][taps][C][32], byte e of a dword pair's codes q0..q7 holding q_e and q_(e+4).
+bool dx_fp4_form(const Layer &L, const fqt_quant_cfg &cfg);
+// Eight values of at most 3, a byte each in lo and hi, as e2m1 nibbles (0, 1, 2, 3 -> 0, 2, 4, 5).
+__device__ __forceinline__ uint32_t pack_e2m1(uint32_t lo8, uint32_t hi8) {
+  const uint32_t q = lo8 | (hi8 << 4);
+  const uint32_t hi = q & 0x22222222u, lo = q & 0x11111111u;
+  return (hi << 1) | ((lo << 1) & ~hi) | (lo & (hi >> 1));
+}
+// Eight sign bytes (1, -1 or 0) as e2m1 nibbles (0x2, 0xA, 0) in the same order.
+__device__ __forceinline__ uint32_t pack_sign_e2m1(uint32_t lo8, uint32_t hi8) {
+  const uint32_t l = ((lo8 & 0x01010101u) << 1) | ((lo8 & 0x80808080u) >> 4);
+  const uint32_t h = ((hi8 & 0x01010101u) << 1) | ((hi8 & 0x80808080u) >> 4);
+  return l | (h << 4);
+}
 // Linear layers whose dX product reads W itself (launch_products' wrows).
 bool dx_rows_form(const Layer &L, const void *W);
 

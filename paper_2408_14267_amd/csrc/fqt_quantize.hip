@@ -1476,6 +1476,7 @@ struct QPackArgs {
   uint32_t planes;      // 1: also write the bit planes (0: the byte codes only)
   const float *gamma;   // training: the gradient is dy * gamma[d]
   uint32_t pcq_fmt;     // PcqFormat (k_qpack_lines)
+  uint32_t psq_fp4;     // PSQ codes as nibbles (dx_fp4_form)
 };
 
 // Codes of a thread's quads into the LDS tiles.  The four codes of a quad share one
@@ -1650,9 +1651,14 @@ __global__ __launch_bounds__(THREADS) void k_qpack(QPackArgs a) {
     const int row = prow[rr];                   // -1 for pruned samples and past R
     const uint32_t *src = reinterpret_cast<const uint32_t *>(&cs[rr][8 * lk]);
     const uint32_t lo = src[0], hi = src[1];
-    if (row >= 0)
-      *reinterpret_cast<uint2 *>(a.psq_codes + ((size_t(d0 >> 5) + (lk >> 2)) * g.R + row) * 32 +
-                                 8 * (lk & 3)) = make_uint2(lo, hi);
+    if (row >= 0) {
+      if (a.psq_fp4)
+        *reinterpret_cast<uint32_t *>(a.psq_codes + (size_t(d0 >> 6) * g.R + row) * 32 + 4 * lk) =
+            pack_e2m1(lo, hi);
+      else
+        *reinterpret_cast<uint2 *>(a.psq_codes + ((size_t(d0 >> 5) + (lk >> 2)) * g.R + row) * 32 +
+                                   8 * (lk & 3)) = make_uint2(lo, hi);
+    }
     if (a.planes) {
       const uint64_t y = bit_transpose8((uint64_t(hi) << 32) | lo);
 #pragma unroll
@@ -1711,9 +1717,7 @@ __device__ __forceinline__ uint32_t taps_transpose(uint32_t word, int lane) {
   return __builtin_amdgcn_perm(z, r, (lane & 2) ? 0x03070105u : 0x06020400u);
 }
 __device__ __forceinline__ uint32_t taps_nibbles(uint32_t t) {   // valid in even lanes
-  const uint32_t q = t | (lane_xor<1>(t) << 4);
-  const uint32_t hi = q & 0x22222222u, lo = q & 0x11111111u;
-  return (hi << 1) | ((lo << 1) & ~hi) | (lo & (hi >> 1));
+  return pack_e2m1(t, lane_xor<1>(t));
 }
 
 // Grid: ceil(R / 256) x ceil(D / 64) blocks; wave w takes channels d0 + 16 w .. + 15, lane l
@@ -1818,6 +1822,21 @@ __global__ __launch_bounds__(QL_THREADS) void k_qpack_lines(QPackArgs a) {
   __syncthreads();
   if (!any_s) return;                       // (the same over the block: the waves share the rows)
   // Consecutive threads store consecutive 16-byte pieces of the chunk-major rows.
+  if (a.psq_fp4) {
+    const uint32_t half = threadIdx.x & 1;
+    uint8_t *out = a.psq_codes + size_t(d0 >> 6) * g.R * 32 + 16 * half;
+#pragma unroll
+    for (int i = 0; i < QL_ROWS * 2 / QL_THREADS; ++i) {
+      const uint32_t rr = (threadIdx.x >> 1) + (QL_THREADS / 2) * i;
+      const int row = prow[rr];
+      if (row < 0) continue;
+      const uint4 *src = reinterpret_cast<const uint4 *>(&cs[64 * (rr & 3) + (rr >> 2)][32 * half]);
+      const uint4 x = src[0], y = src[1];
+      *reinterpret_cast<uint4 *>(out + size_t(row) * 32) = make_uint4(
+          pack_e2m1(x.x, x.y), pack_e2m1(x.z, x.w), pack_e2m1(y.x, y.y), pack_e2m1(y.z, y.w));
+    }
+    return;
+  }
   const uint32_t part = threadIdx.x & 3;
   uint8_t *out = a.psq_codes + size_t((d0 >> 5) + (part >> 1)) * g.R * 32 + 16 * (part & 1);
 #pragma unroll
@@ -1910,7 +1929,7 @@ int launch_state_clear(void *state, hipStream_t s) {
 
 int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, const fqt_qgrad &q,
                     const QuantWs &w, hipStream_t s, SignJob *signs, bool write_planes,
-                    TrainJob *train) {
+                    TrainJob *train, bool psq_fp4) {
   TileGeom g{uint32_t(L.D), uint32_t(L.P), uint32_t(L.R), make_fastdiv(uint32_t(L.P))};
   const uint32_t nrt = uint32_t(L.Wr), ndt = uint32_t(L.Wd);
   const uint32_t nrb = uint32_t(stats_row_blocks(L));
@@ -2007,7 +2026,7 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   if (with_plane || with_bits || with_band || with_wave || with_rows) {
     SignArgs sg{};
     sg.x = signs->X; sg.xsign = signs->xsign;
-    sg.w = signs->W; sg.pg = pack_w_geom(L); sg.wsb = signs->wsb; sg.wlsum = signs->wlsum;
+    sg.w = signs->W; sg.pg = pack_w_geom(L, signs->fp4); sg.wsb = signs->wsb; sg.wlsum = signs->wlsum;
     sg.npw = signs->no_w ? 0 : pack_w_blocks(L);
     uint32_t xblocks;
     if (with_plane) {
@@ -2112,6 +2131,7 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   qa.planes = write_planes ? 1u : 0u;
   qa.gamma = train ? train->gamma : nullptr;
   const uint32_t lblocks = uint32_t((L.R + QL_ROWS - 1) / QL_ROWS);
+  qa.psq_fp4 = psq_fp4 ? 1u : 0u;
   qa.pcq_fmt = signs && signs->taps ? signs->taps->fmt : uint32_t(PCQ_PLAIN);
   if (mode == TILE_PIX && !write_planes &&
       (qa.pcq_fmt != PCQ_PLAIN || int64_t(lblocks) * ndt >= QL_MIN_BLOCKS)) {

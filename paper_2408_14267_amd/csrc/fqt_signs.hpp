@@ -550,7 +550,7 @@ constexpr int WB_THREADS = 1024;
 constexpr int WB_ROWS = 256;                  // rows of D per pass: 16 per thread
 constexpr int WB_PITCH = WB_ROWS + 4;
 struct PackWGeom {
-  uint32_t D, K, Dp, C, taps;
+  uint32_t D, K, Dp, C, taps, fp4;     // fp4: nibbles, [Dp/64][taps][C][32] (dx_fp4_form)
   FastDiv div_taps;
 };
 struct alignas(16) PackWLds {
@@ -585,7 +585,18 @@ __device__ __forceinline__ void pack_w_body(const void *__restrict__ w, const Pa
     __syncthreads();
     // 64 lines x 16 pieces of 16 bytes; pieces past Dp (last pass of a short D) are not stored.
     const int wl = t >> 4, part = t & 15;
-    if (l0 + wl < g.K && d0 + 16 * part < g.Dp) {
+    if (g.fp4) {                              // 64 lines x 8 pieces of 16 bytes (32 channels d)
+      const int wn = t >> 3, pn = t & 7;
+      if (t < 512 && l0 + wn < g.K && d0 + 32 * pn < g.Dp) {
+        const uint32_t lw = l0 + wn, c = fdiv(lw, g.div_taps), tap = lw - c * g.taps;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(&sm.tile[wn][32 * pn]);
+        uint32_t o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = pack_sign_e2m1(src[2 * k], src[2 * k + 1]);
+        *reinterpret_cast<uint4 *>(dst + ((size_t((d0 >> 6) + (pn >> 1)) * g.taps + tap) * g.C + c) * 32 +
+                                   16 * (pn & 1)) = make_uint4(o[0], o[1], o[2], o[3]);
+      }
+    } else if (l0 + wl < g.K && d0 + 16 * part < g.Dp) {
       const uint32_t lw = l0 + wl, c = fdiv(lw, g.div_taps), tap = lw - c * g.taps;
       const uint32_t chunk = (d0 >> 5) + (part >> 1);
       const uint32_t *src = reinterpret_cast<const uint32_t *>(&sm.tile[wl][16 * part]);
@@ -700,10 +711,10 @@ __device__ __forceinline__ void plane_mask_body(const PlaneGeom &g, uint4 *__res
   masks[2 * (g.per + 1) + m] = make_uint4(down & left, down, down & right, 0u);
 }
 
-inline PackWGeom pack_w_geom(const Layer &L) {
+inline PackWGeom pack_w_geom(const Layer &L, bool fp4 = false) {
   const uint32_t taps = uint32_t(L.kh * L.kw);
   return PackWGeom{uint32_t(L.D), uint32_t(L.K), uint32_t(L.Wd * 64), uint32_t(L.C), taps,
-                   make_fastdiv(taps)};
+                   fp4 ? 1u : 0u, make_fastdiv(taps)};
 }
 inline uint32_t pack_w_blocks(const Layer &L) { return uint32_t((L.K + 63) / 64); }
 
