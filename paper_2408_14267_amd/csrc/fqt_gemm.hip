@@ -1059,8 +1059,7 @@ __device__ __forceinline__ void dx_body(const DxArgs &a, uint32_t bid, DxLds &sm
 // consecutive pixels of the same channels.  Steps run over the taps of a 32-byte chunk before
 // the next chunk, so that the taps' rows of codes come from the L1; a tap's row is found from
 // the pixel by one multiply-add and a range check (division by the strides where they are not
-// 1).  Batches of DXT_NB steps at four waves per SIMD (four steps at three waves: conv2 at
-// 224 198 -> see the table of the layer).
+// 1).  Batches of DXT_NB steps are double-buffered at three waves per SIMD.
 //   FP4: codes and signs as e2m1 nibbles (b <= 2; half the bytes and half the steps), sums in
 //        float32, exact below 2^24.
 //   LIN: one pixel per sample and one tap: codes feed the MFMA's rows, so that output lanes run
@@ -1072,7 +1071,7 @@ constexpr int DXT_PITCH = 32 * DXT_RT + 4;           // staged floats per channe
 struct alignas(16) DxTileLds {
   float stage[DX_WAVES][32 * DXT_PITCH];
   int32_t pix_out[DXT_BP];                           // offset of each pixel in dX, -1 past the live rows
-  float2 pix_sz[DXT_BP];                             // its sample's scale and offset (LIN)
+  float2 pix_sz[DXT_BP];                             // its sample's scale and offset
 };
 
 typedef int v8i __attribute__((ext_vector_type(8)));
@@ -1137,22 +1136,18 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
   // This lane's pixels: position under tap (0, 0), first code row, scale and offset.
   int hb[DXT_RT], wb[DXT_RT];
   uint32_t base[DXT_RT];
-  float2 sz[DXT_RT];
-  int off[DXT_RT];
 #pragma unroll
   for (int rt = 0; rt < DXT_RT; ++rt) {
     const uint32_t m = m0 + 32 * rt + uint32_t(i), mm = min(m, live_rows - 1);
     const uint32_t slot = fdiv(mm, a.divHW), p = mm - slot * a.HW;
     const uint32_t h = fdiv(p, a.divW), w = p - h * a.W;
     const uint32_t n = uint32_t(a.kept[slot]);
-    sz[rt] = a.slot_sz ? a.slot_sz[slot] : make_float2(a.scale[n], a.offset[n]);
-    off[rt] = m < live_rows ? int(n * a.CHW + p) : -1;
     hb[rt] = int(h) + a.ph;
     wb[rt] = int(w) + a.pw;
     base[rt] = slot * a.P;
     if (g == 0) {
-      pix[32 * rt + i] = off[rt];
-      if (LIN) psz[32 * rt + i] = sz[rt];
+      pix[32 * rt + i] = m < live_rows ? int(n * a.CHW + p) : -1;
+      psz[32 * rt + i] = a.slot_sz ? a.slot_sz[slot] : make_float2(a.scale[n], a.offset[n]);
     }
   }
   // Output position that tap (ti, tj) of pixel rt meets; false where there is none.
@@ -1182,24 +1177,51 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
   for (int rt = 0; rt < DXT_RT; ++rt)
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = Acc{0};
+  // Operands of the zero-point term (below): the sign sums of 16 taps of this lane's channels and
+  // the flags of the taps that reach its pixels, loaded and formed ahead of the contraction.
+  const bool few = a.taps <= 16 && a.D <= 2048;  // one f16 MFMA per tile
+  auto line_sum = [&](uint32_t ch, uint32_t tap) {
+    return tap < a.taps && ch < a.C ? a.wlsum[ch * a.taps + tap] : 0;
+  };
+  auto reaches = [&](int rt, uint32_t tap) {
+    const uint32_t tr = fdiv(tap, a.divKw);
+    uint32_t ho, wo;
+    return tap < a.taps && meets(rt, int(tr), int(tap) - int(tr) * a.kw, ho, wo);
+  };
+  f16x8 wsum[LIN ? 1 : CT];
+  uint32_t flags[DXT_RT];
+  if (!LIN && few) {
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        wsum[ct][k] = _Float16(float(line_sum(c0 + uint32_t(32 * ct + i), 8 * g + k)));
+#pragma unroll
+    for (int rt = 0; rt < DXT_RT; ++rt) {
+      flags[rt] = 0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) flags[rt] |= reaches(rt, 8 * g + k) ? 1u << k : 0u;
+    }
+  }
   int ti = 0, tj = 0;
   uint32_t kc = 0;
-  for (uint32_t s0 = 0; s0 < steps; s0 += DXT_NB) {
-    // A batch's loads all issue before its first product; a step past the end multiplies by
-    // zero signs.
+  struct Batch {
     v4i A[DXT_NB][CT], B[DXT_NB][DXT_RT];
+  };
+  // The loads of a batch of steps (a step past the end multiplies by zero signs).
+  auto issue = [&](uint32_t s0, Batch &b) {
 #pragma unroll
     for (int u = 0; u < DXT_NB; ++u) {
       const bool live = s0 + u < steps;
       const uint32_t ws = min(s0 + u, steps - 1) * wstride;
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) A[u][ct] = load16(ars, live ? abase[ct] : BUF_NONE, ws);
+      for (int ct = 0; ct < CT; ++ct) b.A[u][ct] = load16(ars, live ? abase[ct] : BUF_NONE, ws);
       const uint32_t cs = min(kc, a.nch - 1) * a.R * 32;
 #pragma unroll
       for (int rt = 0; rt < DXT_RT; ++rt) {
         uint32_t ho, wo;
         const bool ok = meets(rt, ti, tj, ho, wo);
-        B[u][rt] = load16(brs, ok ? (base[rt] + ho * a.Wo + wo) * 32 + 16 * g : BUF_NONE, cs);
+        b.B[u][rt] = load16(brs, ok ? (base[rt] + ho * a.Wo + wo) * 32 + 16 * g : BUF_NONE, cs);
       }
       ++tj;
       ti += tj == a.kw ? 1 : 0;
@@ -1208,20 +1230,36 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
       ti = ti == a.kh ? 0 : ti;
     }
     __builtin_amdgcn_sched_barrier(0);
+  };
+  auto consume = [&](const Batch &q) {
 #pragma unroll
     for (int u = 0; u < DXT_NB; ++u)
 #pragma unroll
       for (int rt = 0; rt < DXT_RT; ++rt) {
-        const v4i b = B8 ? bias128(B[u][rt]) : B[u][rt];
+        const v4i b = B8 ? bias128(q.B[u][rt]) : q.B[u][rt];
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-          const v4i x = LIN ? b : A[u][ct], y = LIN ? A[u][ct] : b;
+          const v4i x = LIN ? b : q.A[u][ct], y = LIN ? q.A[u][ct] : b;
           if constexpr (FP4)
             acc[rt][ct] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                 as_v8(x), as_v8(y), acc[rt][ct], 4, 4, 0, 127, 0, 127);
           else acc[rt][ct] = mfma_i8(x, y, acc[rt][ct]);
         }
       }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Two batches in turn: one loads behind the other's products.
+  Batch b0, b1;
+  issue(0, b0);
+  for (uint32_t s0 = 0;;) {
+    issue(s0 + DXT_NB, b1);
+    consume(b0);
+    s0 += DXT_NB;
+    if (s0 >= steps) break;
+    issue(s0 + DXT_NB, b0);
+    consume(b1);
+    s0 += DXT_NB;
+    if (s0 >= steps) break;
   }
 
   if constexpr (LIN) {
@@ -1260,33 +1298,28 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
       // sign sum is a float16 integer and 16 taps go into one f16 MFMA (lane half g holds taps
       // 8 g .. 8 g + 7); else two taps per float32 MFMA.
       v16f cz = v16f{0};
-      if (a.D <= 2048) {
+      if (few) {
+        f16x8 rb;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) rb[k] = (flags[rt] >> k) & 1u ? _Float16(1.0f) : _Float16(0.0f);
+        cz = __builtin_amdgcn_mfma_f32_32x32x16_f16(wsum[ct], rb, cz, 0, 0, 0);
+      } else if (a.D <= 2048) {
         for (uint32_t tb = 0; tb < a.taps; tb += 16) {
           f16x8 wa, rb;
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
-            const uint32_t tap = tb + 8 * g + k;
-            const bool in = tap < a.taps;
-            const uint32_t tr = fdiv(tap, a.divKw);
-            uint32_t ho, wo;
-            wa[k] = in && ch < a.C ? _Float16(float(a.wlsum[ch * a.taps + tap])) : _Float16(0.0f);
-            rb[k] = in && meets(rt, int(tr), int(tap) - int(tr) * a.kw, ho, wo) ? _Float16(1.0f)
-                                                                             : _Float16(0.0f);
+            wa[k] = _Float16(float(line_sum(ch, tb + 8 * g + k)));
+            rb[k] = reaches(rt, tb + 8 * g + k) ? _Float16(1.0f) : _Float16(0.0f);
           }
           cz = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa, rb, cz, 0, 0, 0);
         }
       } else {
-        for (uint32_t j = 0; 2 * j < a.taps; ++j) {
-          const uint32_t tap = 2 * j + g, tr = fdiv(tap, a.divKw);
-          const bool in = tap < a.taps;
-          uint32_t ho, wo;
-          const float wv = in && ch < a.C ? float(a.wlsum[ch * a.taps + tap]) : 0.0f;
-          const float rv =
-              in && meets(rt, int(tr), int(tap) - int(tr) * a.kw, ho, wo) ? 1.0f : 0.0f;
-          cz = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, rv, cz, 0, 0, 0);
-        }
+        for (uint32_t j = 0; 2 * j < a.taps; ++j)
+          cz = __builtin_amdgcn_mfma_f32_32x32x2f32(float(line_sum(ch, 2 * j + g)),
+                                                    reaches(rt, 2 * j + g) ? 1.0f : 0.0f, cz, 0, 0, 0);
       }
-      const float S = sz[rt].x, Z = sz[rt].y;
+      const float S = psz[32 * rt + i].x, Z = psz[32 * rt + i].y;
+      const int off = pix[32 * rt + i];
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = acc_row(v, g);
@@ -1297,8 +1330,8 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
         float out = rescale(S, I, Z, cz[v]);
         if (a.vec) {
           st[row * DXT_PITCH + 32 * rt + i] = out;
-        } else if (off[rt] >= 0 && cc < a.C) {
-          const size_t o = size_t(off[rt]) + size_t(cc) * a.HW;
+        } else if (off >= 0 && cc < a.C) {
+          const size_t o = size_t(off) + size_t(cc) * a.HW;
           out = ste_pass(a, o) ? out : 0.0f;
           if (a.dx_t == FQT_BF16) static_cast<uint16_t *>(a.dX)[o] = f32_to_bf16(out);
           else static_cast<float *>(a.dX)[o] = out;
@@ -1509,9 +1542,10 @@ __device__ __forceinline__ void dx_form_body(const DxArgs &a, uint32_t bid, DxLd
   else dx_body_tiles<FP4, B8, WT == DX_CT1 ? 1 : 2, WT == DX_LIN>(a, bid, sm);
 }
 
-// The register-tile forms are held to four waves per SIMD.
+// The two-channel-tile forms are held to three waves per SIMD (two batches of loads in flight;
+// at four the epilogue spills), the one-channel-tile form to four.
 template <bool B8, int NB, int WT>
-__global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT == 0 ? 1 : WT == 2 ? 3 : 4)))
+__global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT == DX_SPLIT ? 1 : WT == DX_CT1 ? 4 : 3)))
 void k_mfma_dx(DxArgs a) {
   __shared__ DxLdsOf<WT> sm;
   dx_form_body<false, B8, NB, WT>(a, blockIdx.x, sm);
@@ -1551,7 +1585,7 @@ union ProductsLds {
   double dg[DX_WAVES][64];
 };
 template <bool B8, int NB, int DWF, int WT, bool FP4>
-__global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT == 0 ? 1 : WT == 2 ? 3 : 4)))
+__global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT == DX_SPLIT ? 1 : WT == DX_CT1 ? 4 : 3)))
 void k_products(DxArgs dxa, DwArgs dwa, uint32_t ndw, DgArgs dg) {
   __shared__ ProductsLds<WT> sm;
   if (blockIdx.x < ndw) {
@@ -1652,10 +1686,12 @@ uint32_t dw_part_blocks(const Layer &L, const DwArgs &a) {
 }
 
 // Register tiles once the capacity has DX_TILES tiles of 32 x 32.
-constexpr int64_t DX_TILES = 16384;
+constexpr int64_t DX_TILES = 8192;
 uint32_t dx_form(const Layer &L) {
   const int64_t ctiles = (L.C + 31) / 32, tiles = ((L.N * L.HW + 31) / 32) * ctiles;
-  if (tiles < DX_TILES) return DX_SPLIT;
+  // (strided layers twice as many: most of a pixel's taps meet nothing, and the split form
+  // spreads what is left over four waves; 29 against 33 us at 12544 tiles)
+  if (tiles < (L.sh * L.sw > 1 ? 2 : 1) * DX_TILES) return DX_SPLIT;
   if (L.HW == 1 && L.kh * L.kw == 1) return DX_LIN;
   return ctiles > 1 ? DX_CT2 : DX_CT1;
 }
