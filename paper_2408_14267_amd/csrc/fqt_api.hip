@@ -459,7 +459,9 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
   const TapsPlan *taps = w.taps_on ? &w.taps : nullptr;
   const bool wrows = dx_rows_form(L, W);
   const bool fp4 = dx_fp4_form(L, *cfg);
-  SignJob sj{X, W, w.xsign, w.wsb, w.wlsum, false, fp4, wrows, taps, w.arena};
+  const bool dw4 = !taps && dw_fp4_form(L, *cfg);
+  const uint32_t pcq = taps ? taps->fmt : dw4 ? PCQ_TAPS4 : PCQ_PLAIN;
+  SignJob sj{X, W, w.xsign, w.wsb, w.wlsum, false, fp4, false, wrows, pcq, taps, w.arena};
   // The products read the byte codes; the bit planes (the paper's packed form) are left to
   // fqt_agp_scq_quantize callers.
   FQT_TRY(launch_quantize(L, *cfg, dY, w.q, w.qws, s, &sj, false, train, fp4));
@@ -470,10 +472,10 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
     else
       FQT_TRY(launch_pack_bits(X, L.x_t, 0, 0, 0, FQT_PACK_IM2COL, &L, w.xsign, nullptr, s,
                                true));
-    if (!wrows) FQT_TRY(launch_pack_w_i8(W, L, w.wsb, w.wlsum, s, fp4));
+    if (!wrows) FQT_TRY(launch_pack_w_i8(W, L, w.wsb, w.wlsum, s, fp4, sj.zeroed));
   }
   return launch_products(L, *cfg, w.q, w.xsign, w.wsb, w.wlsum, dX, dW, w.dw_ws, w.qws.sslot,
-                         w.qws.cslot, s, train, taps, w.arena, wrows ? W : nullptr, fp4);
+                         w.qws.cslot, s, train, taps, w.arena, wrows ? W : nullptr, fp4, dw4);
 }
 }  // namespace
 }  // namespace fqt

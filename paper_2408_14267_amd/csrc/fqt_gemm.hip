@@ -39,6 +39,7 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef int v8i __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // The wave index as a scalar, so that per-wave loop bounds and strides stay in SGPRs.
@@ -387,26 +388,50 @@ __device__ __forceinline__ void dw_kred_body(const DwArgs &a, uint32_t bid, DwRe
 // tiles and a four-word ring at two waves per SIMD; short ones (a few words, where the
 // dW stores dominate) 2 x 2 tiles and two words at the occupancy the registers allow.
 constexpr int DWB_LONG_WORDS = 8;     // contractions of at least this many words: long form
-template <int RT, int CT>
+template <int RT, int CT, bool FP4 = false>
 struct DwBigBatch {
-  uint64_t word[CT];
-  v4i A[2][RT];                           // [half][row tile]
+  uint64_t word[CT];                      // FP4: the half-wave's 32 positions
+  v4i A[FP4 ? 1 : 2][RT];                 // [half][row tile]
 };
-template <int RT, int CT>
+template <int RT, int CT, bool FP4>
 __device__ __forceinline__ void dwb_issue(const DwArgs &a, __amdgpu_buffer_rsrc_t crs,
                                           __amdgpu_buffer_rsrc_t xrs, const uint32_t (&aoff)[RT],
                                           const uint32_t (&boff)[CT], uint32_t c,
-                                          DwBigBatch<RT, CT> &b) {
+                                          DwBigBatch<RT, CT, FP4> &b) {
   // Word offsets as scalars (kept out of any vector induction variable).
   const uint32_t xs = __builtin_amdgcn_readfirstlane(c * a.K * 8);
-  const uint32_t cs0 = __builtin_amdgcn_readfirstlane(2 * c * a.D * 32);
+  const uint32_t cs0 = __builtin_amdgcn_readfirstlane((FP4 ? c : 2 * c) * a.D * 32);
   const uint32_t cs1 = __builtin_amdgcn_readfirstlane((2 * c + 1) * a.D * 32);
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) b.word[ct] = load8(xrs, boff[ct], xs);
+  for (int ct = 0; ct < CT; ++ct)
+    b.word[ct] = FP4 ? uint32_t(__builtin_amdgcn_raw_buffer_load_b32(xrs, boff[ct], xs, 0))
+                     : load8(xrs, boff[ct], xs);
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     b.A[0][rt] = load16(crs, aoff[rt], cs0);
-    b.A[1][rt] = load16(crs, aoff[rt], cs1);
+    if constexpr (!FP4) b.A[1][rt] = load16(crs, aoff[rt], cs1);
+  }
+}
+// FP4: +-1 nibbles from 32 sign bits in the codes' order (dword q: positions 4 n + q, the bit
+// moved to the sign of a nibble 0x2), one fp4 MFMA per tile and word.
+template <int RT, int CT>
+__device__ __forceinline__ void dwb_consume4(const DwBigBatch<RT, CT, true> &b, uint32_t c88,
+                                             v16f (&acc)[RT][CT], uint32_t (&tcnt)[CT]) {
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const uint32_t n = ~uint32_t(b.word[ct]);
+    tcnt[ct] += __popc(uint32_t(b.word[ct]));
+    v4i B;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      B[q] = int(__builtin_amdgcn_bitop3_b32(n << (3 - q), c88, 0x22222222u, 0xEA));
+    const v8i B8v{B.x, B.y, B.z, B.w, 0, 0, 0, 0};
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const v4i A = b.A[0][rt];
+      acc[rt][ct] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+          v8i{A.x, A.y, A.z, A.w, 0, 0, 0, 0}, B8v, acc[rt][ct], 4, 4, 0, 127, 0, 127);
+    }
   }
 }
 // Four sign bits of `half` from bit `off` (LSB first) as four 0/1 bytes: a nibble times
@@ -449,7 +474,7 @@ __device__ __forceinline__ void dwb_consume(const DwBigBatch<RT, CT> &b, const u
 // writing the slice's partial sums (in the split kernel's form, sum over the slice of
 // A_r s_r with A_r the MFMA code byte: 2 sum A b - sum A) and its set-bit counts for the
 // finish pass.  Grid: S slices (fastest) x slot blocks x column groups.
-template <bool B8, int RT, int CT, int ST, bool SPLIT = false, bool STREAM = false>
+template <bool B8, int RT, int CT, int ST, bool SPLIT = false, bool STREAM = false, bool FP4 = false>
 __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = wave_id();
@@ -468,11 +493,11 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
   const uint32_t j0 = rb * (32 * RT);
   const uint32_t k0 = ((bid - rb * kgroups) * DW_WAVES + wave) * (32 * CT);
   if (k0 >= a.K) return;
-  v16i acc[RT][CT];
+  std::conditional_t<FP4, v16f, v16i> acc[RT][CT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = v16i{0};
+    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = std::conditional_t<FP4, v16f, v16i>{0};
   uint32_t tcnt[CT], qsum[RT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) tcnt[ct] = 0u;
@@ -490,7 +515,7 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       const uint32_t kc = k0 + 32 * ct + i;
-      boff[ct] = kc < a.K ? kc * 8 : BUF_NONE;
+      boff[ct] = kc < a.K ? kc * 8 + (FP4 ? 4 * g : 0) : BUF_NONE;
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) off[k] = uint32_t(16 * g + 4 * k);
@@ -498,7 +523,9 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
     // been used, so ST - 1 words are in flight during each word's products.  Every
     // step issues the same loads (a word past the end re-reads the last one), so the
     // waits count exactly.
-    DwBigBatch<RT, CT> bs[ST];
+    DwBigBatch<RT, CT, FP4> bs[ST];
+    uint32_t c88 = 0x88888888u;           // (in a vector register: an instruction takes one scalar)
+    asm("" : "+v"(c88));
     const uint32_t last = ce - 1;
 #pragma unroll
     for (int u = 0; u < ST; ++u) dwb_issue(a, crs, xrs, aoff, boff, min(cb + uint32_t(u), last), bs[u]);
@@ -506,13 +533,17 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
 #pragma unroll
       for (int u = 0; u < ST; ++u) {
         if (c + u >= ce) break;
-        dwb_consume<B8, RT, CT>(bs[u], off, acc, tcnt, qsum);
+        if constexpr (FP4) dwb_consume4<RT, CT>(bs[u], c88, acc, tcnt);
+        else dwb_consume<B8, RT, CT>(bs[u], off, acc, tcnt, qsum);
         __builtin_amdgcn_sched_barrier(0);
         dwb_issue(a, crs, xrs, aoff, boff, min(c + u + ST, last), bs[u]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
+  if constexpr (FP4)                      // each half-wave counted its own positions
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) tcnt[ct] += lane_xor<32>(tcnt[ct]);
   // Lane i (and i + 32) holds half of the code sum of row i of each row tile; the
   // accumulator rows of a lane are acc_row(v, g), fetched from their lanes.
   if (SPLIT) {
@@ -535,7 +566,7 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int row = acc_row(v, g);
-          if (int(j0) + 32 * rt + row < count) out[size_t(row) * a.Kp] = 2 * acc[rt][ct][v] - qv[v];
+          if (int(j0) + 32 * rt + row < count) out[size_t(row) * a.Kp] = 2 * int(acc[rt][ct][v]) - qv[v];
         }
       }
     }
@@ -586,7 +617,8 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
               const uint32_t j = jt + uint32_t(acc_row(v, g));
               float out = 0.0f;
               if (int(j) < count) {
-                const int I = 2 * (acc[rt][cp + h][v] + (B8 ? 128 * T : 0)) - qv[v];
+                const int I = FP4 ? int(acc[rt][cp + h][v])
+                                  : 2 * (int(acc[rt][cp + h][v]) + (B8 ? 128 * T : 0)) - qv[v];
                 out = rescale(szv[v].x, I, szv[v].y, float(2 * T - int(a.R)));
               }
               st[acc_row(v, g) * SP + 32 * h + i] = out;
@@ -638,7 +670,7 @@ __device__ __forceinline__ void dw_big_body(const DwArgs &a, uint32_t bid) {
         float out = 0.0f;
         if (int(j) < count) {
           const float2 sz = a.slot_sz ? a.slot_sz[j] : make_float2(a.scale[d], a.offset[d]);
-          I = 2 * (acc[rt][ct][v] + (B8 ? 128 * T : 0)) - qv[v];
+          I = FP4 ? int(acc[rt][ct][v]) : 2 * (int(acc[rt][ct][v]) + (B8 ? 128 * T : 0)) - qv[v];
           out = rescale(sz.x, I, sz.y, float(2 * T - int(a.R)));
         }
         a.dW[d * a.K + kc] = out;
@@ -669,6 +701,12 @@ uint32_t dw_split_blocks(const DwArgs &a, int rt) {
 template <bool B8, bool STREAM>
 __global__ __launch_bounds__(DW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mfma_dw_big(DwArgs a) {
   dw_big_body<B8, 2, 4, 4, false, STREAM>(a, blockIdx.x);
+}
+// The same from nibble codes (b <= 2, the layer backward): 8 expansion operations per 64
+// positions of a column instead of 24, half the matrix steps and code bytes.
+template <bool STREAM>
+__global__ __launch_bounds__(DW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mfma_dw_big4(DwArgs a) {
+  dw_big_body<false, 2, 4, 4, false, STREAM, true>(a, blockIdx.x);
 }
 // Short contractions: three waves per SIMD, for the stores.
 template <bool B8, bool STREAM>
@@ -1074,7 +1112,6 @@ struct alignas(16) DxTileLds {
   float2 pix_sz[DXT_BP];                             // its sample's scale and offset
 };
 
-typedef int v8i __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ v8i as_v8(v4i v) { return v8i{v.x, v.y, v.z, v.w, 0, 0, 0, 0}; }
 
 // Stores of one wave's 32 channels x 64 pixels from their LDS copy [channel][pixel]: pieces of
@@ -1772,9 +1809,12 @@ void launch_dw_split(const DwArgs &a, int rt, hipStream_t s) {
 }
 
 template <bool B8>
-void launch_dw_big(const DwArgs &a, hipStream_t s) {
+void launch_dw_big(const DwArgs &a, bool fp4, hipStream_t s) {
   auto go = [&]<bool STREAM>() {
-    if (a.Wr >= uint32_t(DWB_LONG_WORDS))
+    if (!B8 && fp4)
+      hipLaunchKernelGGL(k_mfma_dw_big4<STREAM>, dim3(dw_big_blocks(a.D, a.K, 2, 4)),
+                         dim3(DW_THREADS), 0, s, a);
+    else if (a.Wr >= uint32_t(DWB_LONG_WORDS))
       hipLaunchKernelGGL((k_mfma_dw_big<B8, STREAM>), dim3(dw_big_blocks(a.D, a.K, 2, 4)),
                          dim3(DW_THREADS), 0, s, a);
     else
@@ -1798,6 +1838,15 @@ void launch_dw_finish(const Layer &L, const DwArgs &a, hipStream_t s) {
 
 }  // namespace
 
+// Nibble PCQ codes for dW: codes of at most 3, the long one-split form, sums below 2^24.
+bool dw_fp4_form(const Layer &L, const fqt_quant_cfg &cfg) {
+  if (cfg.bits > 2 || L.Wr < DWB_LONG_WORDS || ((1 << cfg.bits) - 1) * L.R >= (int64_t(1) << 24))
+    return false;
+  DwArgs a;
+  a.S = uint32_t(gemm_dw_splits(L, cfg));
+  return dw_big(L, a);
+}
+
 // Nibble codes and signs for dX: codes of at most 3, register tiles, sums below 2^24.
 bool dx_fp4_form(const Layer &L, const fqt_quant_cfg &cfg) {
   return cfg.bits <= 2 && dx_form(L) != DX_SPLIT &&
@@ -1819,7 +1868,7 @@ int launch_gemm_dw(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
   const dim3 grid(dw_part_blocks(L, a));
   auto go = [&]<bool B8>() {
     if (dw_big(L, a)) {
-      launch_dw_big<B8>(a, s);
+      launch_dw_big<B8>(a, false, s);
     } else if (dw_kred_form(L, a.S) && !dw_split_big(L, a)) {
       hipLaunchKernelGGL(k_mfma_dw_kred<B8>, dim3(dw_kred_blocks(L, a)), dim3(DW_THREADS), 0, s,
                          a);
@@ -1867,7 +1916,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
                     hipStream_t s, const TrainJob *train, const TapsPlan *taps, char *arena,
-                    const void *wrows, bool fp4) {
+                    const void *wrows, bool fp4, bool dw4) {
   if (L.kh * L.kw > DX_MAX_TAPS) return FQT_E_SHAPE;
   DwArgs dwa = make_dw_args(L, cfg, q, xsign, dW, nullptr, dw_ws);
   DxArgs dxa = make_dx_args(L, q, wsb, wlsum, dX, nullptr);
@@ -1876,6 +1925,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
   // A large one-split dW runs as its own launch in the 2 x 2-tile form; the products
   // launch then holds only dX blocks.
   // Long split-R contractions likewise run their partials as their own launch.
+  if (dw4) dwa.codes_bytes /= 2;
   const bool big = taps || dw_big(L, dwa);
   const bool split_big = !big && dw_split_big(L, dwa);
   const bool kred = !big && !split_big && dw_kred_form(L, dwa.S);
@@ -1883,8 +1933,8 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
     const int st = launch_dw_taps(L, cfg, *taps, q, arena, cslot, dW, s);
     if (st != FQT_OK) return st;
   } else if (big) {
-    if (cfg.bits == 8) launch_dw_big<true>(dwa, s);
-    else launch_dw_big<false>(dwa, s);
+    if (cfg.bits == 8) launch_dw_big<true>(dwa, false, s);
+    else launch_dw_big<false>(dwa, dw4, s);
   } else if (split_big) {
     if (cfg.bits == 8) launch_dw_split<true>(dwa, dw_split_rt(L, cfg), s);
     else launch_dw_split<false>(dwa, dw_split_rt(L, cfg), s);

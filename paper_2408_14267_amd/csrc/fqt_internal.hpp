@@ -116,7 +116,9 @@ struct SignJob {
   int32_t *wlsum;
   bool done;
   bool fp4;              // W as nibbles (dx_fp4_form)
+  bool zeroed;           // set where the line sums were zeroed instead (large group sets)
   bool no_w;             // W is not packed (the dX product reads it)
+  uint32_t pcq_fmt;      // PcqFormat of the dW product
   const TapsPlan *taps;  // the sign plane of the tap form instead of xsign, at `arena`
   char *arena;
 };
@@ -144,8 +146,10 @@ int launch_pack_bits(const void *src, int dtype, int64_t rows, int64_t cols, int
 size_t gemm_dw_ws_bytes(const Layer &L, const fqt_quant_cfg &cfg);
 int launch_gemm_dw(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                    const uint64_t *xsign, float *dW, int32_t *I_out, void *ws, hipStream_t s);
+// split: blocks of 64 lines x 256 rows that add to line sums already zero (a block per 64 lines
+// left 64 blocks for 4096 x 4096: 40 us).
 int launch_pack_w_i8(const void *W, const Layer &L, int8_t *dst, int32_t *lsum, hipStream_t s,
-                     bool fp4 = false);
+                     bool fp4 = false, bool split = false);
 int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                    const int8_t *wsb, const int32_t *wlsum, void *dX, int32_t *I_out,
                    hipStream_t s);
@@ -156,7 +160,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
                     hipStream_t s, const TrainJob *train = nullptr,
                     const TapsPlan *taps = nullptr, char *arena = nullptr,
-                    const void *wrows = nullptr, bool fp4 = false);
+                    const void *wrows = nullptr, bool fp4 = false, bool dw4 = false);
 // Layers whose dX product takes nibble operands (launch_products' fp4): PSQ codes [Dp/64][R][32]
 // and W signs [Dp/64][taps][C][32], byte e of a dword pair's codes q0..q7 holding q_e and q_(e+4).
 bool dx_fp4_form(const Layer &L, const fqt_quant_cfg &cfg);
@@ -172,6 +176,8 @@ __device__ __forceinline__ uint32_t pack_sign_e2m1(uint32_t lo8, uint32_t hi8) {
   const uint32_t h = ((hi8 & 0x01010101u) << 1) | ((hi8 & 0x80808080u) >> 4);
   return l | (h << 4);
 }
+// Layers whose one-split dW product takes PCQ codes as nibbles (PCQ_TAPS4; launch_products' dw4).
+bool dw_fp4_form(const Layer &L, const fqt_quant_cfg &cfg);
 // Linear layers whose dX product reads W itself (launch_products' wrows).
 bool dx_rows_form(const Layer &L, const void *W);
 

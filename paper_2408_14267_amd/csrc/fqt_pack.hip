@@ -118,10 +118,12 @@ __global__ __launch_bounds__(WB_THREADS) void k_pack_w_i8(const void *__restrict
 }  // namespace
 
 int launch_pack_w_i8(const void *W, const Layer &L, int8_t *dst, int32_t *lsum, hipStream_t s,
-                     bool fp4) {
-  const PackWGeom g = pack_w_geom(L, fp4);
+                     bool fp4, bool split) {
+  PackWGeom g = pack_w_geom(L, fp4);
+  g.split = split ? 1u : 0u;
+  const unsigned blocks = pack_w_blocks(L) * (split ? unsigned((L.Wd * 64 + WB_ROWS - 1) / WB_ROWS) : 1u);
   dispatch_dtype(L.w_t, [&]<int DT>() {
-    hipLaunchKernelGGL(k_pack_w_i8<DT>, dim3(pack_w_blocks(L)), dim3(WB_THREADS), 0, s, W, g, dst,
+    hipLaunchKernelGGL(k_pack_w_i8<DT>, dim3(blocks), dim3(WB_THREADS), 0, s, W, g, dst,
                        lsum);
   });
   return last_launch_status();

@@ -490,7 +490,12 @@ __global__ __launch_bounds__(RED_THREADS) void k_stats_reduce(const int2 *__rest
                                                           StatsGeom sg, uint32_t nrb,
                                                           uint32_t ndt,
                                                           int2 *__restrict__ skey,
-                                                          int2 *__restrict__ ckey) {
+                                                          int2 *__restrict__ ckey,
+                                                          int32_t *__restrict__ zero,
+                                                          uint32_t nzero) {
+  // (line sums that a later launch adds to)
+  for (uint32_t e = blockIdx.x * RED_THREADS + threadIdx.x; e < nzero; e += gridDim.x * RED_THREADS)
+    zero[e] = 0;
   __shared__ int32_t smn[RED_THREADS / 64], smx[RED_THREADS / 64];
   const TileGeom &g = sg.g;
   const uint32_t b = blockIdx.x;
@@ -1475,7 +1480,7 @@ struct QPackArgs {
   uint32_t chan_fast;   // grid x walks the channel tiles (rows of dY read as long runs)
   uint32_t planes;      // 1: also write the bit planes (0: the byte codes only)
   const float *gamma;   // training: the gradient is dy * gamma[d]
-  uint32_t pcq_fmt;     // PcqFormat (k_qpack_lines)
+  uint32_t pcq_fmt;     // PcqFormat (k_qpack: PCQ_PLAIN or PCQ_TAPS4)
   uint32_t psq_fp4;     // PSQ codes as nibbles (dx_fp4_form)
 };
 
@@ -1631,9 +1636,20 @@ __global__ __launch_bounds__(THREADS) void k_qpack(QPackArgs a) {
     const int rank = cpar[dd].rank;             // -1 for pruned channels and past D
     const uint32_t *src = reinterpret_cast<const uint32_t *>(&cc[dd][8 * lk]);
     const uint32_t lo = src[0], hi = src[1];
-    if (rank >= 0)
+    if (a.pcq_fmt == PCQ_TAPS4) {
+      // Byte lk % 4 of dword j of a 32-position half: positions 8 (lk % 4) + j and + 4.  The four
+      // lanes' bytes transposed as a 4 x 4 matrix give lane b of them dword b.
+      const uint32_t x = pack_e2m1(lo, hi);
+      const uint32_t y = lane_xor<2>(x);
+      const uint32_t r = __builtin_amdgcn_perm(y, x, (lane & 2) ? 0x03020706u : 0x05040100u);
+      const uint32_t z = lane_xor<1>(r);
+      const uint32_t w = __builtin_amdgcn_perm(z, r, (lane & 1) ? 0x03070105u : 0x06020400u);
+      if (rank >= 0)
+        *reinterpret_cast<uint32_t *>(a.pcq_codes + (size_t(r0 >> 6) * g.D + rank) * 32 + 4 * lk) = w;
+    } else if (rank >= 0) {
       *reinterpret_cast<uint2 *>(a.pcq_codes + ((size_t(r0 >> 5) + (lk >> 2)) * g.D + rank) * 32 +
                                  8 * (lk & 3)) = make_uint2(lo, hi);
+    }
     if (a.planes) {
       const uint64_t y = bit_transpose8((uint64_t(hi) << 32) | lo);
 #pragma unroll
@@ -2000,7 +2016,7 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   int st;
   if (gmax <= 1024 && many_partials) {
     hipLaunchKernelGGL(k_stats_reduce, dim3(unsigned(L.N + L.D)), dim3(RED_THREADS), 0, s,
-                       w.part_c, w.part_s, sg, nrb, ndt, w.skey, w.ckey);
+                       w.part_c, w.part_s, sg, nrb, ndt, w.skey, w.ckey, nullptr, 0u);
     if (last_launch_status() != FQT_OK) return FQT_E_HIP;
     sa.set[0].slots = 2;          // the selection reads the reduced keys
     sa.set[1].slots = 2;
@@ -2100,8 +2116,10 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
     st = last_launch_status();
   } else {
     hipLaunchKernelGGL(k_stats_reduce, dim3(unsigned(L.N + L.D)), dim3(RED_THREADS), 0, s,
-                       w.part_c, w.part_s, sg, nrb, ndt, w.skey, w.ckey);
+                       w.part_c, w.part_s, sg, nrb, ndt, w.skey, w.ckey,
+                       signs ? signs->wlsum : nullptr, signs ? uint32_t(L.K) : 0u);
     if (last_launch_status() != FQT_OK) return FQT_E_HIP;
+    if (signs) signs->zeroed = true;
     if (cfg.agp_mode == FQT_AGP_OFF) {
       hipLaunchKernelGGL(k_select_off, dim3(unsigned((gmax + 255) / 256), 2), dim3(256), 0, s, sa);
       st = last_launch_status();
@@ -2132,9 +2150,9 @@ int launch_quantize(const Layer &L, const fqt_quant_cfg &cfg, const void *dY, co
   qa.gamma = train ? train->gamma : nullptr;
   const uint32_t lblocks = uint32_t((L.R + QL_ROWS - 1) / QL_ROWS);
   qa.psq_fp4 = psq_fp4 ? 1u : 0u;
-  qa.pcq_fmt = signs && signs->taps ? signs->taps->fmt : uint32_t(PCQ_PLAIN);
+  qa.pcq_fmt = signs ? signs->pcq_fmt : uint32_t(PCQ_PLAIN);
   if (mode == TILE_PIX && !write_planes &&
-      (qa.pcq_fmt != PCQ_PLAIN || int64_t(lblocks) * ndt >= QL_MIN_BLOCKS)) {
+      ((signs && signs->taps) || int64_t(lblocks) * ndt >= QL_MIN_BLOCKS)) {
     const dim3 lgrid(lblocks, ndt);
     by_type([&]<int DT, bool TR>() {
       if (cfg.bits == 1)

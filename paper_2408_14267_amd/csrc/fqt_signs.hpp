@@ -551,7 +551,9 @@ constexpr int WB_ROWS = 256;                  // rows of D per pass: 16 per thre
 constexpr int WB_PITCH = WB_ROWS + 4;
 struct PackWGeom {
   uint32_t D, K, Dp, C, taps, fp4;     // fp4: nibbles, [Dp/64][taps][C][32] (dx_fp4_form)
-  FastDiv div_taps;
+  uint32_t split;                      // 1: a block takes one pass of WB_ROWS rows (its index / the
+                                       //    line blocks) and adds to line sums that start at 0
+  FastDiv div_taps, div_lines;         // div_lines: blocks of 64 lines
 };
 struct alignas(16) PackWLds {
   int8_t tile[64][WB_PITCH];
@@ -564,10 +566,13 @@ __device__ __forceinline__ void pack_w_body(const void *__restrict__ w, const Pa
                                             uint32_t bid, PackWLds &sm) {
   constexpr int Q = WB_THREADS / 64;          // row phases per pass
   const int t = threadIdx.x, line = t & 63, q = t >> 6;
+  const uint32_t pass = g.split ? fdiv(bid, g.div_lines) : 0;
+  if (g.split) bid -= pass * g.div_lines.d;
   const uint32_t l0 = bid * 64, l = l0 + line;
   if (t < 64) sm.pos[t] = 0;
   int mine = 0;
-  for (uint32_t d0 = 0; d0 < g.Dp; d0 += WB_ROWS) {
+  const uint32_t d_end = g.split ? min(g.Dp, (pass + 1) * WB_ROWS) : g.Dp;
+  for (uint32_t d0 = pass * WB_ROWS; d0 < d_end; d0 += WB_ROWS) {
     float v[WB_ROWS / Q];
 #pragma unroll
     for (int k = 0; k < WB_ROWS / Q; ++k) {   // unconditional loads (element 0 outside) issue back to back
@@ -607,7 +612,10 @@ __device__ __forceinline__ void pack_w_body(const void *__restrict__ w, const Pa
   }
   atomicAdd(&sm.pos[line], mine);
   __syncthreads();
-  if (t < 64 && l0 + t < g.K) lsum[l0 + t] = 2 * sm.pos[t] - int(g.D);
+  if (t < 64 && l0 + t < g.K) {
+    if (!g.split) lsum[l0 + t] = 2 * sm.pos[t] - int(g.D);
+    else atomicAdd(lsum + l0 + t, 2 * sm.pos[t] - int(min(g.D, d_end) - min(g.D, pass * WB_ROWS)));
+  }
 }
 
 // ----------------------------------------------------------------------------- sign plane
@@ -714,7 +722,7 @@ __device__ __forceinline__ void plane_mask_body(const PlaneGeom &g, uint4 *__res
 inline PackWGeom pack_w_geom(const Layer &L, bool fp4 = false) {
   const uint32_t taps = uint32_t(L.kh * L.kw);
   return PackWGeom{uint32_t(L.D), uint32_t(L.K), uint32_t(L.Wd * 64), uint32_t(L.C), taps,
-                   fp4 ? 1u : 0u, make_fastdiv(taps)};
+                   fp4 ? 1u : 0u, 0u, make_fastdiv(taps), make_fastdiv(uint32_t((L.K + 63) / 64))};
 }
 inline uint32_t pack_w_blocks(const Layer &L) { return uint32_t((L.K + 63) / 64); }
 

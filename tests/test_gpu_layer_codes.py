@@ -42,6 +42,18 @@ CASES = [
     (LayerShape("fc", "linear", 65, 6000, 1000), 1, 2, "f32", 1.0),
     (LayerShape("fc", "linear", 64, 2051, 2100), 4, 0, "f32", 1.5),
     (LayerShape("fc", "linear", 33, 3000, 1500), 4, 1, "bf16", 3.0),
+    # Large linear layers: dX with the channels along the lanes and nibble operands, dW from
+    # nibble codes (b <= 2) over ragged words, W packed by row passes.
+    (LayerShape("fc", "linear", 4100, 4100, 1100), 1, 2, "f32", 1.0),
+    (LayerShape("fc", "linear", 2050, 8196, 2050), 2, 0, "bf16", 1.5),
+    (LayerShape("fc", "linear", 2600, 6500, 1026), 4, 0, "f32", 1.5),
+    (LayerShape("fc", "linear", 530, 2048, 2052), 2, 0, "f32", 1.5),
+    (LayerShape("fc", "linear", 513, 2050, 2051), 1, 2, "f32", 1.0),
+    # Register-tile dX of convolutions: 25 taps, D above 2048, stride 2, one channel tile.
+    (_conv(50, 40, 16, 60, 60, 5, 1, 2), 2, 2, "f32", 1.0),
+    (_conv(300, 40, 2112, 16, 16, 3, 1, 1), 2, 0, "f32", 1.0),
+    (_conv(90, 40, 20, 75, 75, 3, 2, 1), 1, 2, "bf16", 1.0),
+    (_conv(90, 20, 70, 57, 57, 3, 1, 1), 8, 0, "f32", 1.0),
 ]
 
 
