@@ -323,8 +323,8 @@ int fqt_layer_backward_noalloc(const fqt_layer_desc *desc, const fqt_quant_cfg *
  * X: x_dtype [N][C][H][W] (linear [N][C]); W: w_dtype [D][C][kh][kw] ([D][C]); gamma:
  * float32 [D]; Y: dy_dtype, the layout of dY ([N][D][Ho][Wo], linear [N][D]); I_out
  * (optional, NULL to skip): int32 in Y's layout.  ws: >= fqt_workspace_size(FQT_WS_FORWARD)
- * bytes, 256-byte aligned, no initialisation needed (it holds the packed operands:
- * sign(X_u) bits and sign(W) bytes).  All pointers are device pointers; stream-ordered on
+ * bytes, 256-byte aligned, no initialisation needed (it holds the packed operands,
+ * sign(X) and sign(W)).  All pointers are device pointers; stream-ordered on
  * hip_stream; returns FQT_E_SHAPE when an operand exceeds 2 GiB. */
 int fqt_binary_forward(const fqt_layer_desc *desc, const void *X, const void *W,
                        const float *gamma, void *Y, int32_t *I_out, void *ws, size_t ws_bytes,

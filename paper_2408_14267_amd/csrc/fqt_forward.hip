@@ -606,7 +606,14 @@ size_t forward_ws_bytes(const Layer &L) {
   // (the packed rows of k_fwd_rows, 64 bytes per row and 128 channels, fit the X area)
   const uint64_t few = uint64_t((L.C + 127) / 128) * 16 * few_rows_tiles(L) * 64;
   const uint64_t x = L.kind == FQT_LINEAR && L.N <= FEW_ROWS ? std::max(z.xbytes, few) : z.xbytes;
-  return align256(x) + align256(z.wbytes);
+  const uint64_t need = align256(x) + align256(z.wbytes);
+  // The reported size is never below that of unfolded sign bits, once per word and once per
+  // row block, beside sign bytes of W (K and D rounded up to 64): callers that reserve by that
+  // formula, and those that reserve by the reported size, are both served.
+  const uint64_t Kp = uint64_t((L.K + 63) / 64 * 64);
+  const uint64_t unfolded = align256(uint64_t(L.Wr) * L.K * 8) + align256(Kp / 64 * L.Wr * 512) +
+                            align256(z.Dp * Kp);
+  return std::max(need, unfolded);
 }
 
 namespace {
