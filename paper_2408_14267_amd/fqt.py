@@ -110,13 +110,14 @@ _lib = _load()
 # ----------------------------------------------------------------------------- marshalling helpers
 
 def _ptr(t):
-    return None if t is None else c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()      # (ctypes takes an int as a c_void_p)
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        # The raw handle of torch's current stream, without a Stream object around it.
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(status, where):
@@ -161,6 +162,27 @@ def _need(where, *specs):
     for t, _, _, name, *opt in specs:
         if t is not None and not t.is_cuda:
             raise ValueError(f"{where}: {name}: expected a device tensor, got one on {t.device}")
+
+
+def _fits(*specs):
+    """Whether _need(specs) would pass: specs are (tensor, dtype, elements).  The calls of a
+    training step test this first (about half a microsecond per tensor) and leave the error
+    to _need."""
+    for t, dtype, numel in specs:
+        if t is None or t.dtype is not dtype or not t.is_cuda or t.numel() < numel \
+                or not t.is_contiguous():
+            return False
+    return True
+
+
+def _extents(desc):
+    """Elements of X, W and dY."""
+    n, c, d = desc.N, desc.C, desc.D
+    if desc.kind == FQT_LINEAR:
+        return n * c, d * c, n * d
+    h, w, kh, kw = desc.H, desc.W, desc.kh, desc.kw
+    p = ((h + 2 * desc.ph - kh) // desc.sh + 1) * ((w + 2 * desc.pw - kw) // desc.sw + 1)
+    return n * c * h * w, d * c * kh * kw, n * d * p
 
 
 def dtype_code(dt):
@@ -292,16 +314,18 @@ def fqt_binary_products(desc, cfg, qgrad, xsign, wsign, wsign_linesum, dX, dW, w
 
 
 def fqt_layer_backward(desc, cfg, X, W, dY, dX, dW, ws, stream=None):
-    z = _sizes(desc)
-    _need("fqt_layer_backward",
-          (X, _TORCH_OF.get(desc.x_dtype), z["X"], "X"),
-          (W, _TORCH_OF.get(desc.w_dtype), z["W"], "W"),
-          (dY, _TORCH_OF.get(desc.dy_dtype), z["dY"], "dY"),
-          (dX, _TORCH_OF.get(desc.dx_dtype), z["X"], "dX"),
-          (dW, torch.float32, z["W"], "dW"))
-    _check(_lib.fqt_layer_backward(desc, cfg, _ptr(X), _ptr(W), _ptr(dY), _ptr(dX), _ptr(dW),
-                                   _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)),
-           "fqt_layer_backward")
+    x_t, w_t, dy_t, dx_t = (_TORCH_OF.get(t) for t in (desc.x_dtype, desc.w_dtype,
+                                                       desc.dy_dtype, desc.dx_dtype))
+    nx, nw, ny = _extents(desc)
+    if not _fits((X, x_t, nx), (W, w_t, nw), (dY, dy_t, ny), (dX, dx_t, nx),
+                 (dW, torch.float32, nw)):
+        _need("fqt_layer_backward", (X, x_t, nx, "X"), (W, w_t, nw, "W"), (dY, dy_t, ny, "dY"),
+              (dX, dx_t, nx, "dX"), (dW, torch.float32, nw, "dW"))
+    st = _lib.fqt_layer_backward(desc, cfg, X.data_ptr(), W.data_ptr(), dY.data_ptr(),
+                                 dX.data_ptr(), dW.data_ptr(), _ptr(ws),
+                                 ws.numel() * ws.element_size(), _stream(stream))
+    if st:
+        _check(st, "fqt_layer_backward")
 
 
 def fqt_layer_backward_noalloc(desc, cfg, X, W, dY, dX, dW, stream=None):
@@ -318,16 +342,18 @@ def fqt_layer_backward_noalloc(desc, cfg, X, W, dY, dX, dW, stream=None):
 
 
 def fqt_binary_forward(desc, X, W, gamma, Y, I_out, ws, stream=None):
-    z = _sizes(desc)
-    _need("fqt_binary_forward",
-          (X, _TORCH_OF.get(desc.x_dtype), z["X"], "X"),
-          (W, _TORCH_OF.get(desc.w_dtype), z["W"], "W"),
-          (gamma, torch.float32, desc.D, "gamma"),
-          (Y, _TORCH_OF.get(desc.dy_dtype), z["dY"], "Y"),
-          (I_out, torch.int32, z["dY"], "I_out", True))
-    _check(_lib.fqt_binary_forward(desc, _ptr(X), _ptr(W), _ptr(gamma), _ptr(Y), _ptr(I_out),
-                                   _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)),
-           "fqt_binary_forward")
+    x_t, w_t, y_t = (_TORCH_OF.get(t) for t in (desc.x_dtype, desc.w_dtype, desc.dy_dtype))
+    nx, nw, ny = _extents(desc)
+    if not (_fits((X, x_t, nx), (W, w_t, nw), (gamma, torch.float32, desc.D), (Y, y_t, ny)) and
+            (I_out is None or _fits((I_out, torch.int32, ny)))):
+        _need("fqt_binary_forward", (X, x_t, nx, "X"), (W, w_t, nw, "W"),
+              (gamma, torch.float32, desc.D, "gamma"), (Y, y_t, ny, "Y"),
+              (I_out, torch.int32, ny, "I_out", True))
+    st = _lib.fqt_binary_forward(desc, X.data_ptr(), W.data_ptr(), gamma.data_ptr(), Y.data_ptr(),
+                                 _ptr(I_out), _ptr(ws), ws.numel() * ws.element_size(),
+                                 _stream(stream))
+    if st:
+        _check(st, "fqt_binary_forward")
 
 
 def fqt_train_workspace_size(desc, cfg):
@@ -337,16 +363,19 @@ def fqt_train_workspace_size(desc, cfg):
 
 
 def fqt_train_backward(desc, cfg, X, W, gamma, I, dH, dX, dW, dgamma, ws, stream=None):
-    z = _sizes(desc)
-    _need("fqt_train_backward",
-          (X, torch.float32, z["X"], "X"), (W, torch.float32, z["W"], "W"),
-          (gamma, torch.float32, desc.D, "gamma"), (I, torch.int32, z["dY"], "I"),
-          (dH, torch.float32, z["dY"], "dH"), (dX, torch.float32, z["X"], "dX"),
-          (dW, torch.float32, z["W"], "dW"), (dgamma, torch.float32, desc.D, "dgamma"))
-    _check(_lib.fqt_train_backward(desc, cfg, _ptr(X), _ptr(W), _ptr(gamma), _ptr(I), _ptr(dH),
-                                   _ptr(dX), _ptr(dW), _ptr(dgamma), _ptr(ws),
-                                   ws.numel() * ws.element_size(), _stream(stream)),
-           "fqt_train_backward")
+    f32, d = torch.float32, desc.D
+    nx, nw, ny = _extents(desc)
+    if not _fits((X, f32, nx), (W, f32, nw), (gamma, f32, d), (I, torch.int32, ny), (dH, f32, ny),
+                 (dX, f32, nx), (dW, f32, nw), (dgamma, f32, d)):
+        _need("fqt_train_backward", (X, f32, nx, "X"), (W, f32, nw, "W"), (gamma, f32, d, "gamma"),
+              (I, torch.int32, ny, "I"), (dH, f32, ny, "dH"), (dX, f32, nx, "dX"),
+              (dW, f32, nw, "dW"), (dgamma, f32, d, "dgamma"))
+    st = _lib.fqt_train_backward(desc, cfg, X.data_ptr(), W.data_ptr(), gamma.data_ptr(),
+                                 I.data_ptr(), dH.data_ptr(), dX.data_ptr(), dW.data_ptr(),
+                                 dgamma.data_ptr(), _ptr(ws), ws.numel() * ws.element_size(),
+                                 _stream(stream))
+    if st:
+        _check(st, "fqt_train_backward")
 
 
 # ----------------------------------------------------------------------------- buffers

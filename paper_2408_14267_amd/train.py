@@ -35,16 +35,15 @@ class _BinaryLayerFn(torch.autograd.Function):
         i = torch.empty(y.shape, dtype=torch.int32, device=x.device)
         fqt.fqt_binary_forward(desc, x, w, gamma, y, i, layer.ws_forward(desc))
         ctx.save_for_backward(x, w, gamma, i)
-        ctx.layer = layer
+        ctx.layer, ctx.desc = layer, desc
         return y
 
     @staticmethod
     def backward(ctx, dy):
         x, w, gamma, i = ctx.saved_tensors
-        layer = ctx.layer
+        layer, desc = ctx.layer, ctx.desc
         dx = torch.empty_like(x)
         dw = torch.empty_like(w)
-        desc = layer.desc(x.shape)
         cfg = fqt.quant_cfg(layer.bits, layer.agp_mode, layer.seed, layer.step, layer.layer_id)
         ws = layer.ws_backward(desc, cfg)
         if torch.is_grad_enabled():
