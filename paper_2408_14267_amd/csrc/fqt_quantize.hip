@@ -1,9 +1,10 @@
 // AGP + SCQ quantization of the output gradient dY on gfx950.
 //
 //   k_stats         one pass over dY in 64 (channel) x 64 (unfolded row r = n*P + pixel)
-//                   tiles: per-tile min/max of every channel row and every r column,
-//                   written as partials (no atomics: same-address atomics from the
-//                   eight XCDs serialise at the memory side)
+//                   tiles: min/max of every channel row and every r column, merged into the
+//                   group keys by atomics over eight replicas, or written as partials where
+//                   a group has many
+//   k_stats_lines   the same for maps of 256 pixels and more, along lines of one channel
 //   k_select_fused  (N, D <= 1024) one workgroup per group set: min/max of each group's
 //                   partials (Section 3.2 range and zero point; Section 5.2 / 5.3
 //                   groups), then AGP keep probabilities, Bernoulli masks, kept-id
@@ -14,6 +15,7 @@
 //                   kept sample / kept channel, bit-plane split and packing, and the
 //                   byte codes the MFMA products read
 //                   (Section 3.2 SR; Section 5.2 decomposition; Appendix C encoders)
+//   k_qpack_lines   the byte or nibble codes of larger layers along lines of one channel
 //
 // A tile holds whole 64-bit words of both packings: a PSQ word runs along the 64
 // channels of one row r, a PCQ word along the 64 rows of one channel.

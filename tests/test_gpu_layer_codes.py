@@ -54,6 +54,11 @@ CASES = [
     (_conv(300, 40, 2112, 16, 16, 3, 1, 1), 2, 0, "f32", 1.0),
     (_conv(90, 40, 20, 75, 75, 3, 2, 1), 1, 2, "bf16", 1.0),
     (_conv(90, 20, 70, 57, 57, 3, 1, 1), 8, 0, "f32", 1.0),
+    # More dW blocks of pruned slots than the chip holds (they follow the dX blocks): the in-block
+    # reduction and the split partials, and a set where every channel may be kept.
+    (_conv(40, 512, 300, 7, 7, 3, 1, 1), 8, 0, "f32", 1.5),
+    (_conv(40, 64, 300, 28, 28, 3, 1, 1), 8, 0, "bf16", 1.5),
+    (_conv(40, 512, 300, 7, 7, 3, 1, 1), 4, 2, "f32", 1.0),
 ]
 
 
@@ -95,3 +100,44 @@ def test_layer_matches_the_entries(layer, bits, agp, dtype, spread):
         assert torch.equal(dx2, dx), "dX"
         assert torch.equal(dw2, dw), "dW"
     assert torch.count_nonzero(dw).item() > 0
+
+
+@pytest.mark.parametrize("layer,bits,agp", [
+    (_conv(13, 40, 70, 64, 64, 3, 1, 1), 2, 0),                  # dW by taps
+    (LayerShape("fc", "linear", 64, 4096, 1030), 4, 0),          # few rows
+    (LayerShape("fc", "linear", 2050, 8196, 1030), 1, 2),        # W by row passes, nibble codes
+])
+def test_captured_calls_replay(layer, bits, agp):
+    """Backward and forward captured in one HIP graph and replayed with eager work between the
+    replays equal the eager calls bit for bit."""
+    from paper_2408_14267_amd import fqt
+    print(f"[layer codes] replay {layer} b={bits}", file=sys.stderr, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda shape: torch.randn(shape, device="cuda", generator=gen)
+    x, w, dy, gamma = rnd(layer.x_shape), rnd(layer.w_shape), rnd(layer.dy_shape), rnd((layer.D,))
+    desc, cfg = fqt.layer_desc(layer), fqt.quant_cfg(bits, agp, 3, 0, 1)
+    ws, wf = fqt.workspace(desc, cfg), fqt.workspace(desc, None, fqt.FQT_WS_FORWARD)
+
+    def calls(dx, dw, y, stream=None):
+        fqt.fqt_layer_backward(desc, cfg, x, w, dy, dx, dw, ws, stream)
+        fqt.fqt_binary_forward(desc, x, w, gamma, y, None, wf, stream)
+
+    want = torch.empty_like(x), torch.empty_like(w), torch.empty_like(dy)
+    got = torch.empty_like(x), torch.empty_like(w), torch.empty_like(dy)
+    calls(*want)
+    torch.cuda.synchronize()
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side), torch.cuda.graph(g, stream=side):
+        calls(*got, side)
+    torch.cuda.synchronize()
+    other = torch.empty_like(x), torch.empty_like(w), torch.empty_like(dy)
+    for r in range(3):
+        for t in got:
+            t.fill_(7.0)
+        g.replay()
+        torch.cuda.synchronize()
+        for name, a, b in zip(("dx", "dw", "y"), got, want):
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32)), f"replay {r} {name}"
+        calls(*other)                                             # eager work between
+        torch.cuda.synchronize()
