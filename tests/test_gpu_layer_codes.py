@@ -30,10 +30,11 @@ CASES = [
     # is not a multiple of 32, a ragged last word, one to three channel and slot blocks.
     (_conv(65, 40, 70, 30, 26, 3, 1, 1), 2, 0, "bf16", 1.5),
     (_conv(13, 33, 40, 66, 62, 3, 1, 1), 8, 2, "f32", 1.0),
-    (_conv(2, 5, 20, 224, 224, 3, 1, 1), 2, 2, "f32", 1.0),
+    (_conv(2, 29, 20, 224, 224, 3, 1, 1), 2, 2, "f32", 1.0),
     (_conv(13, 70, 200, 64, 64, 3, 1, 1), 1, 2, "bf16", 1.0),
     (_conv(13, 65, 150, 64, 64, 3, 1, 1), 3, 2, "f32", 1.0),
-    (_conv(800, 3, 80, 1, 64, 3, 1, 1), 5, 0, "f32", 1.0),
+    (_conv(800, 27, 80, 1, 64, 3, 1, 1), 5, 0, "f32", 1.0),
+    (_conv(2, 23, 20, 224, 224, 3, 1, 1), 2, 2, "f32", 1.0),     # (too few channels for it)
     # Linear layers of few rows and large W (dX from W itself, dW bound by its stores): one, two
     # and four row tiles, ragged D and C, b = 8, the many-group selection.
     (LayerShape("fc", "linear", 20, 2050, 1030), 3, 0, "f32", 1.5),
