@@ -1624,17 +1624,26 @@ union ProductsLds {
   DwRedLds dw;
   double dg[DX_WAVES][64];
 };
-template <bool B8, int NB, int DWF, int WT, bool FP4>
+// TR: a training step (the straight-through mask, dgamma's blocks); a template parameter because
+// the tests alone cost small layers a microsecond (256 -> 256 on 2x2 maps, N = 128: layer 23.3 us
+// with them, 22.3 without).
+template <bool B8, int NB, int DWF, int WT, bool FP4, bool TR>
 __global__ __launch_bounds__(DX_THREADS) __attribute__((amdgpu_waves_per_eu(WT == DX_SPLIT ? 1 : WT == DX_CT1 ? 4 : 3)))
 void k_products(DxArgs dxa, DwArgs dwa, uint32_t nfront, uint32_t ndw, DgArgs dg) {
   __shared__ ProductsLds<WT> sm;
   const uint32_t b = blockIdx.x;
+  if constexpr (!TR) dxa.ste = nullptr;
+  if constexpr (!TR && DWF == DWF_DIRECT) {     // (never reordered: fewer dW blocks than that)
+    if (b < ndw) dw_part_body<B8, true>(dwa, b);
+    else dx_form_body<FP4, B8, NB, WT>(dxa, b - ndw, sm.dx);
+    return;
+  }
   if (b >= nfront && b - nfront < dxa.nblocks) {
     dx_form_body<FP4, B8, NB, WT>(dxa, b - nfront, sm.dx);
     return;
   }
   const uint32_t wb = b < nfront ? b : b - dxa.nblocks;
-  if (wb >= ndw) dgamma_body(dg, wb - ndw, sm.dg);
+  if (TR && wb >= ndw) dgamma_body(dg, wb - ndw, sm.dg);
   else if constexpr (DWF == DWF_KRED) dw_kred_body<B8>(dwa, wb, sm.dw);
   else dw_part_body<B8, DWF == DWF_DIRECT>(dwa, wb);
 }
@@ -1989,30 +1998,34 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
   const uint32_t keep = uint32_t(
       cfg.agp_mode == FQT_AGP_OFF ? stiles : ((L.D + cfg.bits - 1) / cfg.bits + 31) / 32);
   uint32_t nfront = ndw / stiles * keep;
-  if (ndw - nfront < PRODUCTS_RESIDENT) nfront = ndw;
+  if (ndw - nfront < PRODUCTS_RESIDENT || dwa.S == 1) nfront = ndw;
   const dim3 grid(ndw + dxa.nblocks + (train ? unsigned((L.D + 63) / 64) : 0u));
   const int nb = dx_batch(dxa);
-  auto go = [&]<bool B8, int DWF, int WT>() {
+  auto go_tr = [&]<bool B8, int DWF, int WT, bool TR>() {
     if constexpr (WT != 0) {
       if constexpr (!B8)
         if (fp4) {
-          hipLaunchKernelGGL((k_products<B8, 4, DWF, WT, true>), grid, dim3(DX_THREADS), 0, s, dxa,
+          hipLaunchKernelGGL((k_products<B8, 4, DWF, WT, true, TR>), grid, dim3(DX_THREADS), 0, s, dxa,
                              dwa, nfront, ndw, dg);
           if (DWF == DWF_PARTS) launch_dw_finish<B8>(L, dwa, s);
           return;
         }
-      hipLaunchKernelGGL((k_products<B8, 4, DWF, WT, false>), grid, dim3(DX_THREADS), 0, s, dxa,
+      hipLaunchKernelGGL((k_products<B8, 4, DWF, WT, false, TR>), grid, dim3(DX_THREADS), 0, s, dxa,
                          dwa, nfront, ndw, dg);
     } else if (nb == 4)
-      hipLaunchKernelGGL((k_products<B8, 4, DWF, 0, false>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
+      hipLaunchKernelGGL((k_products<B8, 4, DWF, 0, false, TR>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
                          nfront, ndw, dg);
     else if (nb == 8)
-      hipLaunchKernelGGL((k_products<B8, 8, DWF, 0, false>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
+      hipLaunchKernelGGL((k_products<B8, 8, DWF, 0, false, TR>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
                          nfront, ndw, dg);
     else
-      hipLaunchKernelGGL((k_products<B8, 10, DWF, 0, false>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
+      hipLaunchKernelGGL((k_products<B8, 10, DWF, 0, false, TR>), grid, dim3(DX_THREADS), 0, s, dxa, dwa,
                          nfront, ndw, dg);
     if (DWF == DWF_PARTS) launch_dw_finish<B8>(L, dwa, s);
+  };
+  auto go = [&]<bool B8, int DWF, int WT>() {
+    if (train) go_tr.template operator()<B8, DWF, WT, true>();
+    else go_tr.template operator()<B8, DWF, WT, false>();
   };
   auto go2 = [&]<bool B8, int DWF>() {
     if (dxa.wide == DX_LIN) go.template operator()<B8, DWF, DX_LIN>();
