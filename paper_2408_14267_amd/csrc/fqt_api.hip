@@ -458,7 +458,7 @@ int layer_backward_run(const Layer &L, const fqt_quant_cfg &cfg_, const void *X,
   // layer allows), the quantizer, both products.
   const TapsPlan *taps = w.taps_on ? &w.taps : nullptr;
   const bool wrows = dx_rows_form(L, W);
-  const bool fp4 = dx_fp4_form(L, *cfg);
+  const bool fp4 = !wrows && dx_fp4_form(L, *cfg);    // (the rows form reads byte codes)
   const bool dw4 = !taps && dw_fp4_form(L, *cfg);
   const uint32_t pcq = taps ? taps->fmt : dw4 ? PCQ_TAPS4 : PCQ_PLAIN;
   SignJob sj{X, W, w.xsign, w.wsb, w.wlsum, false, fp4, false, wrows, pcq, taps, w.arena};

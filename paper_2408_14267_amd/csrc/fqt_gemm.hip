@@ -1936,7 +1936,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
                     float *dW, void *dw_ws, const float2 *sslot, const float2 *cslot,
                     hipStream_t s, const TrainJob *train, const TapsPlan *taps, char *arena,
                     const void *wrows, bool fp4, bool dw4) {
-  if (L.kh * L.kw > DX_MAX_TAPS) return FQT_E_SHAPE;
+  if (L.kh * L.kw > DX_MAX_TAPS || (wrows && fp4)) return FQT_E_SHAPE;
   DwArgs dwa = make_dw_args(L, cfg, q, xsign, dW, nullptr, dw_ws);
   DxArgs dxa = make_dx_args(L, q, wsb, wlsum, dX, nullptr);
   dwa.slot_sz = cslot;

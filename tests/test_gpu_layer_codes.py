@@ -43,6 +43,12 @@ CASES = [
     (LayerShape("fc", "linear", 65, 6000, 1000), 1, 2, "f32", 1.0),
     (LayerShape("fc", "linear", 64, 2051, 2100), 4, 0, "f32", 1.5),
     (LayerShape("fc", "linear", 33, 3000, 1500), 4, 1, "bf16", 3.0),
+    # Few rows and as many outputs as the register tiles take (8192 tiles of 32 x 32; the first
+    # case has eight fewer): dX from W itself reads byte codes also for b <= 2.
+    (LayerShape("fc", "linear", 128, 65472, 18), 2, 0, "f32", 1.5),
+    (LayerShape("fc", "linear", 128, 65536, 18), 2, 0, "f32", 1.5),
+    (LayerShape("fc", "linear", 100, 65536, 70), 1, 2, "bf16", 1.0),
+    (LayerShape("fc", "linear", 64, 131072, 16), 2, 0, "f32", 1.5),
     # Large linear layers: dX with the channels along the lanes and nibble operands, dW from
     # nibble codes (b <= 2) over ragged words, W packed by row passes.
     (LayerShape("fc", "linear", 4100, 4100, 1100), 1, 2, "f32", 1.0),
