@@ -1100,7 +1100,7 @@ __device__ __forceinline__ void dx_body(const DxArgs &a, uint32_t bid, DxLds &sm
 // 1).  Batches of DXT_NB steps are double-buffered at three waves per SIMD.
 //   FP4: codes and signs as e2m1 nibbles (b <= 2; half the bytes and half the steps), sums in
 //        float32, exact below 2^24.
-//   LIN: one pixel per sample and one tap: codes feed the MFMA's rows, so that output lanes run
+//   LIN: one pixel per sample and one tap, no padding (every sample is reached): codes feed the MFMA's rows, so that output lanes run
 //        along the channels, as dX does.
 constexpr int DXT_RT = 2;                            // pixel tiles per wave
 constexpr int DXT_NB = 2;                            // contraction steps per load batch
@@ -1742,7 +1742,9 @@ uint32_t dx_form(const Layer &L) {
   // (strided layers twice as many: most of a pixel's taps meet nothing, and the split form
   // spreads what is left over four waves; 29 against 33 us at 12544 tiles)
   if (tiles < (L.sh * L.sw > 1 ? 2 : 1) * DX_TILES) return DX_SPLIT;
-  if (L.HW == 1 && L.kh * L.kw == 1) return DX_LIN;
+  // (padding puts output pixels where the one tap does not reach the map, and a stride may leave
+  // only such pixels: those need the reach flags of the other forms)
+  if (L.HW == 1 && L.kh * L.kw == 1 && L.ph == 0 && L.pw == 0) return DX_LIN;
   return ctiles > 1 ? DX_CT2 : DX_CT1;
 }
 

@@ -109,6 +109,41 @@ def test_layer_matches_the_entries(layer, bits, agp, dtype, spread):
     assert torch.count_nonzero(dw).item() > 0
 
 
+@pytest.mark.parametrize("stride,pad", [(2, 1), (3, 1), (1, 1), (2, 2)])
+@pytest.mark.parametrize("bits", [2, 4])
+def test_padded_one_tap_on_one_pixel_maps(stride, pad, bits):
+    """A padded 1 x 1 convolution on 1 x 1 maps, large enough for register tiles: output pixel p meets
+    the input pixel where p * stride = pad, and where no p does dX is 0 (its zero-point term too)."""
+    from paper_2408_14267_amd import fqt
+    layer = _conv(1024, 16400, 12, 1, 1, 1, stride, pad)
+    print(f"[gpu layer codes] {layer} b={bits}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x, w = (torch.randn(s, generator=g, device="cuda") for s in (layer.x_shape, layer.w_shape))
+    dy = torch.randn(layer.dy_shape, generator=g, device="cuda") + 3.0
+    desc, cfg = fqt.layer_desc(layer), fqt.quant_cfg(bits, 0, 17, 3, 2)
+    q = fqt.QGrad(desc, cfg)
+    fqt.fqt_agp_scq_quantize(desc, cfg, dy, q, fqt.workspace(desc, cfg, fqt.FQT_WS_QUANTIZE))
+    wsb = torch.empty(layer.C * 64, dtype=torch.int8, device="cuda")
+    wsum = torch.empty(layer.C, dtype=torch.int32, device="cuda")
+    fqt.fqt_pack_weight_signs(desc, w, wsb, wsum)
+    # The rescale of exact integers from the byte codes of the pixel that the tap meets.
+    want = torch.zeros(layer.N, layer.C, device="cuda")
+    kept = q.psq_kept[:int(q.psq_count)].long()
+    if pad % stride == 0:
+        P = layer.Ho * layer.Wo
+        rows = torch.arange(len(kept), device="cuda") * P + pad // stride * (layer.Wo + 1)
+        codes = q.psq_codes.view(2, layer.N * P, 32)[0, rows, :layer.D].float()
+        signs = torch.where(w.view(layer.D, layer.C) > 0, 1.0, -1.0)
+        want[kept] = q.psq_scale[kept, None] * (codes @ signs) + q.psq_offset[kept, None] * signs.sum(0)
+    dx, dx2, dw = torch.full_like(x, 7.0), torch.full_like(x, 7.0), torch.empty_like(w)
+    fqt.fqt_binary_gemm_dx(desc, cfg, q, wsb, wsum, dx)
+    fqt.fqt_layer_backward(desc, cfg, x, w, dy, dx2, dw, fqt.workspace(desc, cfg))
+    torch.cuda.synchronize()
+    assert len(kept) > 0
+    assert torch.equal(dx.view_as(want), want), "dX of the entry"
+    assert torch.equal(dx2.view_as(want), want), "dX of the layer"
+
+
 @pytest.mark.parametrize("layer,bits,agp", [
     (_conv(13, 40, 70, 64, 64, 3, 1, 1), 2, 0),                  # dW by taps
     (LayerShape("fc", "linear", 64, 4096, 1030), 4, 0),          # few rows
