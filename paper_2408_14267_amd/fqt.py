@@ -113,10 +113,21 @@ def _ptr(t):
     return None if t is None else t.data_ptr()      # (ctypes takes an int as a c_void_p)
 
 
+# The raw handle of torch's current stream without a Stream object around it, where this torch
+# has that (an undocumented name).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def current_stream():
+    """The handle of torch's current stream on the current device."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
 def _stream(stream):
     if stream is None:
-        # The raw handle of torch's current stream, without a Stream object around it.
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

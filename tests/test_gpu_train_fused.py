@@ -89,3 +89,14 @@ def test_module_gradients_of_any_layout_and_create_graph():
     assert torch.allclose(dgamma.detach(), plain[2], rtol=1e-5, atol=1e-4)
     second, = torch.autograd.grad(dgamma.sum(), dy)
     assert torch.equal(second, torch.round(y.detach() / mod.gamma.detach().view(1, -1, 1, 1)))
+
+
+def test_current_stream_with_and_without_the_raw_handle(monkeypatch):
+    from paper_2408_14267_amd import fqt
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.default_stream(), side):
+        with torch.cuda.stream(stream):
+            assert fqt.current_stream() == stream.cuda_stream
+            with monkeypatch.context() as m:
+                m.setattr(fqt, "_raw_stream", None)
+                assert fqt.current_stream() == stream.cuda_stream
