@@ -71,7 +71,8 @@ def _aligned(t):
 
 
 class _BinaryBase(nn.Module):
-    """Latent float32 weight, Gamma, quantizer settings and per-shape workspaces."""
+    """Latent float32 weight, Gamma, quantizer settings, and workspaces per shape, quantizer settings
+    and stream."""
 
     def __init__(self, weight_shape, out_features, bits, agp_mode, layer_id, seed):
         super().__init__()
@@ -83,9 +84,18 @@ class _BinaryBase(nn.Module):
         self._ws = {}
 
     def _workspace(self, key, make):
-        ws = self._ws.get(key)
+        # A workspace serves one call at a time, and calls on different streams may overlap.  A capture
+        # takes one that is there (a new one's preparation would only be recorded); whoever replays the
+        # graph orders it with other calls, as for all that a graph writes.
+        by_stream = self._ws.setdefault(key, {})
+        stream = torch.cuda.current_device(), fqt.current_stream()
+        ws = by_stream.get(stream)
         if ws is None:
-            ws = self._ws[key] = make()
+            if by_stream and torch.cuda.is_current_stream_capturing():
+                for (device, _), ws in by_stream.items():
+                    if device == stream[0]:
+                        return ws
+            ws = by_stream[stream] = make()
         return ws
 
     def ws_forward(self, desc):
@@ -93,8 +103,9 @@ class _BinaryBase(nn.Module):
             desc, None, fqt.FQT_WS_FORWARD, device=self.weight.device))
 
     def ws_backward(self, desc, cfg):
-        return self._workspace(("b", desc.N, desc.H, desc.W), lambda: fqt.train_workspace(
-            desc, cfg, device=self.weight.device))
+        # (the size depends on the code width and, through the expected kept groups, on the pruning)
+        key = "b", desc.N, desc.H, desc.W, cfg.bits, cfg.agp_mode
+        return self._workspace(key, lambda: fqt.train_workspace(desc, cfg, device=self.weight.device))
 
     def forward(self, x):
         return _BinaryLayerFn.apply(x.contiguous(), self.weight, self.gamma, self)

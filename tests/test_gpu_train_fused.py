@@ -100,3 +100,60 @@ def test_current_stream_with_and_without_the_raw_handle(monkeypatch):
             with monkeypatch.context() as m:
                 m.setattr(fqt, "_raw_stream", None)
                 assert fqt.current_stream() == stream.cuda_stream
+
+
+def test_module_bits_and_agp_change_between_steps():
+    """Workspace sizes follow the code width and the pruning mode: a module whose settings change takes
+    a workspace of the new size (and the old one again when they change back)."""
+    from paper_2408_14267_amd import fqt, train
+    print("[gpu train fused] module settings change", flush=True)
+    torch.manual_seed(2)
+    mod = train.BinaryConv2d(64, 64, 3, 1, 1, bits=1, agp_mode=fqt.FQT_AGP_OFF).cuda()
+    x = torch.randn(64, 64, 32, 32, device="cuda", requires_grad=True)
+    dy = torch.randn(64, 64, 32, 32, device="cuda")
+
+    def grads(m):
+        m.step = 5
+        return torch.autograd.grad(m(x), (x, m.weight, m.gamma), dy)
+
+    for bits, agp in ((1, 2), (8, 2), (8, 0), (1, 2)):
+        mod.bits, mod.agp_mode = bits, agp
+        fresh = train.BinaryConv2d(64, 64, 3, 1, 1, bits=bits, agp_mode=agp).cuda()
+        fresh.load_state_dict(mod.state_dict())
+        for a, b in zip(grads(mod), grads(fresh)):
+            assert torch.equal(a, b), (bits, agp)
+
+
+def test_module_workspaces_are_one_per_stream():
+    """Two streams may run one module at a time each: they take workspaces of their own.  A capture
+    takes one that is there, whatever stream it came from."""
+    from paper_2408_14267_amd import fqt, train
+    print("[gpu train fused] module workspaces", flush=True)
+    mod = train.BinaryLinear(40, 24, bits=2).cuda()
+    desc, cfg = mod.desc((16, 40)), fqt.quant_cfg(2)
+    side = torch.cuda.Stream()
+    first = mod.ws_forward(desc), mod.ws_backward(desc, cfg)
+    with torch.cuda.stream(side):
+        other = mod.ws_forward(desc), mod.ws_backward(desc, cfg)
+        again = mod.ws_forward(desc), mod.ws_backward(desc, cfg)
+    assert all(a.data_ptr() != b.data_ptr() for a, b in zip(first, other))
+    assert all(a is b for a, b in zip(other, again))
+    assert all(a is b for a, b in zip(first, (mod.ws_forward(desc), mod.ws_backward(desc, cfg))))
+    x = torch.randn(16, 40, device="cuda", requires_grad=True)
+    dy = torch.randn(16, 24, device="cuda")
+    step = lambda: torch.autograd.grad(mod(x), (x, mod.weight, mod.gamma), dy)
+    mod.step = 0
+    want = [t.clone() for t in step()]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    mod.step = 0
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        got = step()
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+        step()                                  # eager work between the replays
+        torch.cuda.synchronize()
+    assert len(mod._ws) == 2 and all(len(v) == 2 for v in mod._ws.values())
