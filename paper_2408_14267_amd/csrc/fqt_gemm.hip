@@ -1095,29 +1095,34 @@ __device__ __forceinline__ void dx_body(const DxArgs &a, uint32_t bid, DxLds &sm
 // runs their whole contraction (no split over the waves, no reduction), so each loaded sign
 // fragment feeds DXT_RT MFMAs and each code fragment CT of them; a block's four waves take
 // consecutive pixels of the same channels.  Steps run over the taps of a 32-byte chunk before
-// the next chunk, so that the taps' rows of codes come from the L1; a tap's row is found from
-// the pixel by one multiply-add and a range check (division by the strides where they are not
-// 1).  Batches of DXT_NB steps are double-buffered at three waves per SIMD.
+// the next chunk, so that the taps' rows of codes come from the L1.  A wave tabulates its pixels'
+// code rows in LDS, tap by tap, a lane per pixel (found in the loop from the pixel, with
+// divisions under a stride, they took the VALU longer than the products take the matrix cores:
+// 512 -> 512 on 28 x 28, b = 2: 67 us of the launch against 54; 4 -> 223, 3 x 3 / 2 on 147 x 147,
+// b = 3: 80 against 50).  Batches of DXT_NB steps are double-buffered.
 //   FP4: codes and signs as e2m1 nibbles (b <= 2; half the bytes and half the steps), sums in
 //        float32, exact below 2^24.
-//   LIN: one pixel per sample and one tap, no padding (every sample is reached): codes feed the MFMA's rows, so that output lanes run
-//        along the channels, as dX does.
+//   LIN: one pixel per sample and one tap, no padding (every sample is reached): codes feed the
+//        MFMA's rows, so that output lanes run along the channels, as dX does.
 constexpr int DXT_RT = 2;                            // pixel tiles per wave
 constexpr int DXT_NB = 2;                            // contraction steps per load batch
 constexpr uint32_t DXT_BP = DX_WAVES * DXT_RT * 32;  // pixel rows per block
 constexpr int DXT_PITCH = 32 * DXT_RT + 4;           // staged floats per channel
 struct alignas(16) DxTileLds {
-  float stage[DX_WAVES][32 * DXT_PITCH];
+  uint32_t lds[DX_WAVES][32 * DXT_PITCH];            // code rows [tap][pixel], then the output tile
   int32_t pix_out[DXT_BP];                           // offset of each pixel in dX, -1 past the live rows
   float2 pix_sz[DXT_BP];                             // its sample's scale and offset
+  uint64_t reach[DXT_BP];                            // the taps that meet an output pixel
 };
+constexpr int DXT_TAPS = 32;                         // taps tabulated at once
+static_assert(DXT_TAPS * 32 * DXT_RT <= 32 * DXT_PITCH && 32 * DXT_RT == 64, "code rows in the tile's place");
 
 __device__ __forceinline__ v8i as_v8(v4i v) { return v8i{v.x, v.y, v.z, v.w, 0, 0, 0, 0}; }
 
 // Stores of one wave's 32 channels x 64 pixels from their LDS copy [channel][pixel]: pieces of
 // 4 pixels of one channel (HW % 4 == 0: of one sample), consecutive lanes on consecutive
 // pixels.
-__device__ __forceinline__ void dx_store_tile(const DxArgs &a, const int32_t *pix, const float *st,
+__device__ __forceinline__ void dx_store_tile(const DxArgs &a, const int32_t *pix, const uint32_t *st,
                                               uint32_t c0, int lane) {
   constexpr int PIECES = 4 * DXT_RT, QROW = 8 * DXT_RT;   // pieces per lane, per channel row
   const int off = pix[4 * (lane % QROW)];
@@ -1128,7 +1133,9 @@ __device__ __forceinline__ void dx_store_tile(const DxArgs &a, const int32_t *pi
       const uint32_t row = uint32_t(lane / QROW + (64 / QROW) * k);
       if (c0 + row >= a.C) continue;
       const size_t o = size_t(off) + size_t(c0 + row) * a.HW;
-      float4 f = *reinterpret_cast<const float4 *>(st + row * DXT_PITCH + 4 * (lane % QROW));
+      const uint4 q = *reinterpret_cast<const uint4 *>(st + row * DXT_PITCH + 4 * (lane % QROW));
+      float4 f = make_float4(__uint_as_float(q.x), __uint_as_float(q.y), __uint_as_float(q.z),
+                             __uint_as_float(q.w));
       if (a.ste) {
         const float4 x = *reinterpret_cast<const float4 *>(a.ste + o);
         f.x = __builtin_fabsf(x.x) <= 1.0f ? f.x : 0.0f;
@@ -1151,6 +1158,10 @@ __device__ __forceinline__ void dx_store_tile(const DxArgs &a, const int32_t *pi
   else put([](auto *p, auto v) { *p = v; });
 }
 
+// A pixel's or a tap's remainders under the strides as one word: a tap's are below DX_MAX_TAPS (as
+// are kh and kw), so a pixel's may be clamped to it.
+__device__ __forceinline__ uint32_t tap_rem(uint32_t h, uint32_t w) { return h << 16 | w; }
+
 template <bool FP4, bool B8, int CT, bool LIN>
 __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxTileLds &sm) {
   using Acc = std::conditional_t<FP4, v16f, v16i>;
@@ -1170,36 +1181,19 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
   if (m0 >= live_rows) return;                   // (no barrier below: each wave has its own LDS)
   int32_t *pix = sm.pix_out + wave * (32 * DXT_RT);
   float2 *psz = sm.pix_sz + wave * (32 * DXT_RT);
-  // This lane's pixels: position under tap (0, 0), first code row, scale and offset.
-  int hb[DXT_RT], wb[DXT_RT];
-  uint32_t base[DXT_RT];
-#pragma unroll
-  for (int rt = 0; rt < DXT_RT; ++rt) {
-    const uint32_t m = m0 + 32 * rt + uint32_t(i), mm = min(m, live_rows - 1);
-    const uint32_t slot = fdiv(mm, a.divHW), p = mm - slot * a.HW;
-    const uint32_t h = fdiv(p, a.divW), w = p - h * a.W;
-    const uint32_t n = uint32_t(a.kept[slot]);
-    hb[rt] = int(h) + a.ph;
-    wb[rt] = int(w) + a.pw;
-    base[rt] = slot * a.P;
-    if (g == 0) {
-      pix[32 * rt + i] = m < live_rows ? int(n * a.CHW + p) : -1;
-      psz[32 * rt + i] = a.slot_sz ? a.slot_sz[slot] : make_float2(a.scale[n], a.offset[n]);
-    }
-  }
-  // Output position that tap (ti, tj) of pixel rt meets; false where there is none.
-  auto meets = [&](int rt, int ti, int tj, uint32_t &ho, uint32_t &wo) -> bool {
-    const int th = hb[rt] - ti, tw = wb[rt] - tj;
-    ho = uint32_t(th);
-    wo = uint32_t(tw);
-    bool ok = true;
-    if (a.sh != 1 || a.sw != 1) {                // (uniform)
-      ho = fdiv(uint32_t(max(th, 0)), a.divSh);
-      wo = fdiv(uint32_t(max(tw, 0)), a.divSw);
-      ok = int(ho) * a.sh == th && int(wo) * a.sw == tw;
-    }
-    return ok && ho < a.Ho && wo < a.Wo;
-  };
+  uint64_t *reach = sm.reach + wave * (32 * DXT_RT);
+  uint32_t *lds = sm.lds[wave];
+  // Lane l's own pixel m0 + l: position under tap (0, 0) divided by the strides (quotients, and both
+  // remainders in one word), first code row.
+  const uint32_t m = m0 + uint32_t(lane), mm = min(m, live_rows - 1);
+  const uint32_t slot = fdiv(mm, a.divHW), p = mm - slot * a.HW;
+  const uint32_t h = fdiv(p, a.divW), w = p - h * a.W, n = uint32_t(a.kept[slot]);
+  const uint32_t hq = fdiv(h + uint32_t(a.ph), a.divSh), wq = fdiv(w + uint32_t(a.pw), a.divSw);
+  const uint32_t rem = tap_rem(min(h + uint32_t(a.ph) - hq * uint32_t(a.sh), uint32_t(DX_MAX_TAPS)),
+                               min(w + uint32_t(a.pw) - wq * uint32_t(a.sw), uint32_t(DX_MAX_TAPS)));
+  const uint32_t first = slot * a.P;
+  pix[lane] = m < live_rows ? int(n * a.CHW + p) : -1;
+  psz[lane] = a.slot_sz ? a.slot_sz[slot] : make_float2(a.scale[n], a.offset[n]);
   uint32_t abase[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
@@ -1208,65 +1202,28 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
   }
   const __amdgpu_buffer_rsrc_t ars = buffer_of(a.wsb, a.wsb_bytes);
   const __amdgpu_buffer_rsrc_t brs = buffer_of(a.codes, a.codes_bytes);
-  const uint32_t steps = a.taps * a.nch, wstride = a.C * 32;
+  const uint32_t wstride = a.C * 32;
   Acc acc[DXT_RT][CT];
 #pragma unroll
   for (int rt = 0; rt < DXT_RT; ++rt)
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = Acc{0};
-  // Operands of the zero-point term (below): the sign sums of 16 taps of this lane's channels and
-  // the flags of the taps that reach its pixels, loaded and formed ahead of the contraction.
+  // The sign sums of 16 taps of this lane's channels (an operand of the zero-point term below),
+  // loaded ahead of the contraction.
   const bool few = a.taps <= 16 && a.D <= 2048;  // one f16 MFMA per tile
   auto line_sum = [&](uint32_t ch, uint32_t tap) {
     return tap < a.taps && ch < a.C ? a.wlsum[ch * a.taps + tap] : 0;
   };
-  auto reaches = [&](int rt, uint32_t tap) {
-    const uint32_t tr = fdiv(tap, a.divKw);
-    uint32_t ho, wo;
-    return tap < a.taps && meets(rt, int(tr), int(tap) - int(tr) * a.kw, ho, wo);
-  };
   f16x8 wsum[LIN ? 1 : CT];
-  uint32_t flags[DXT_RT];
   if (!LIN && few) {
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int k = 0; k < 8; ++k)
         wsum[ct][k] = _Float16(float(line_sum(c0 + uint32_t(32 * ct + i), 8 * g + k)));
-#pragma unroll
-    for (int rt = 0; rt < DXT_RT; ++rt) {
-      flags[rt] = 0;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) flags[rt] |= reaches(rt, 8 * g + k) ? 1u << k : 0u;
-    }
   }
-  int ti = 0, tj = 0;
-  uint32_t kc = 0;
   struct Batch {
     v4i A[DXT_NB][CT], B[DXT_NB][DXT_RT];
-  };
-  // The loads of a batch of steps (a step past the end multiplies by zero signs).
-  auto issue = [&](uint32_t s0, Batch &b) {
-#pragma unroll
-    for (int u = 0; u < DXT_NB; ++u) {
-      const bool live = s0 + u < steps;
-      const uint32_t ws = min(s0 + u, steps - 1) * wstride;
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) b.A[u][ct] = load16(ars, live ? abase[ct] : BUF_NONE, ws);
-      const uint32_t cs = min(kc, a.nch - 1) * a.R * 32;
-#pragma unroll
-      for (int rt = 0; rt < DXT_RT; ++rt) {
-        uint32_t ho, wo;
-        const bool ok = meets(rt, ti, tj, ho, wo);
-        b.B[u][rt] = load16(brs, ok ? (base[rt] + ho * a.Wo + wo) * 32 + 16 * g : BUF_NONE, cs);
-      }
-      ++tj;
-      ti += tj == a.kw ? 1 : 0;
-      tj = tj == a.kw ? 0 : tj;
-      kc += ti == a.kh ? 1 : 0;
-      ti = ti == a.kh ? 0 : ti;
-    }
-    __builtin_amdgcn_sched_barrier(0);
   };
   auto consume = [&](const Batch &q) {
 #pragma unroll
@@ -1285,18 +1242,89 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
       }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // Two batches in turn: one loads behind the other's products.
-  Batch b0, b1;
-  issue(0, b0);
-  for (uint32_t s0 = 0;;) {
-    issue(s0 + DXT_NB, b1);
-    consume(b0);
-    s0 += DXT_NB;
-    if (s0 >= steps) break;
-    issue(s0 + DXT_NB, b0);
-    consume(b1);
-    s0 += DXT_NB;
-    if (s0 >= steps) break;
+  // Taps in groups of DXT_TAPS: each lane tabulates its pixel's code rows (BUF_NONE where the tap meets
+  // no output pixel, and a bit of the reach mask where it does), then the group's steps run.
+  uint64_t mask = 0;
+  int tj = 0;
+  uint32_t tq = 0, tr = 0, uq = 0, ur = 0;       // tap (ti, tj): ti = sh tq + tr, tj = sw uq + ur
+  for (uint32_t g0 = 0; g0 < a.taps; g0 += DXT_TAPS) {
+    const uint32_t nt = min(a.taps - g0, uint32_t(DXT_TAPS)), steps = nt * a.nch;
+    if constexpr (!LIN) {
+      __builtin_amdgcn_wave_barrier();           // (LDS operations of a wave run in order)
+      for (uint32_t t = 0; t < nt; ++t) {
+        const uint32_t ho = hq - tq, wo = wq - uq;
+        const bool ok = rem == tap_rem(tr, ur) && ho < a.Ho && wo < a.Wo;
+        lds[64 * t + lane] = ok ? (first + ho * a.Wo + wo) * 32 : BUF_NONE;
+        mask |= uint64_t(ok ? 1 : 0) << (g0 + t);
+        ++tj;
+        ++ur;
+        if (ur == uint32_t(a.sw)) {
+          ur = 0;
+          ++uq;
+        }
+        if (tj == a.kw) {
+          tj = 0;
+          uq = ur = 0;
+          ++tr;
+          if (tr == uint32_t(a.sh)) {
+            tr = 0;
+            ++tq;
+          }
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    // The code rows of a batch of steps, read a batch ahead of their loads; (kc, t) the step's
+    // chunk and tap.
+    uint32_t row[DXT_NB][DXT_RT], t = 0, kc = 0, tn = 0;
+    auto rows = [&]() {
+#pragma unroll
+      for (int u = 0; u < DXT_NB; ++u) {
+#pragma unroll
+        for (int rt = 0; rt < DXT_RT; ++rt) row[u][rt] = lds[64 * tn + 32 * rt + i] + 16 * g;
+        ++tn;
+        tn = tn == nt ? 0 : tn;
+      }
+    };
+    if constexpr (LIN) {
+#pragma unroll
+      for (int rt = 0; rt < DXT_RT; ++rt)
+#pragma unroll
+        for (int u = 0; u < DXT_NB; ++u)
+          row[u][rt] = fdiv(min(m0 + 32 * rt + uint32_t(i), live_rows - 1), a.divHW) * 32 + 16 * g;
+    } else {
+      rows();
+    }
+    // The loads of a batch of steps (a step past the end multiplies by zero signs).
+    auto issue = [&](uint32_t s0, Batch &b) {
+#pragma unroll
+      for (int u = 0; u < DXT_NB; ++u) {
+        const bool live = s0 + u < steps;
+        const uint32_t kl = min(kc, a.nch - 1), ws = (kl * a.taps + g0 + t) * wstride;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) b.A[u][ct] = load16(ars, live ? abase[ct] : BUF_NONE, ws);
+#pragma unroll
+        for (int rt = 0; rt < DXT_RT; ++rt) b.B[u][rt] = load16(brs, row[u][rt], kl * a.R * 32);
+        ++t;
+        kc += t == nt ? 1 : 0;
+        t = t == nt ? 0 : t;
+      }
+      if constexpr (!LIN) rows();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // Two batches in turn: one loads behind the other's products.
+    Batch b0, b1;
+    issue(0, b0);
+    for (uint32_t s0 = 0;;) {
+      issue(s0 + DXT_NB, b1);
+      consume(b0);
+      s0 += DXT_NB;
+      if (s0 >= steps) break;
+      issue(s0 + DXT_NB, b0);
+      consume(b1);
+      s0 += DXT_NB;
+      if (s0 >= steps) break;
+    }
   }
 
   if constexpr (LIN) {
@@ -1323,7 +1351,13 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
     }
     return;
   }
-  float *st = sm.stage[wave];
+  __builtin_amdgcn_wave_barrier();        // the tile's copy takes the place of the code rows
+  reach[lane] = mask;
+  __builtin_amdgcn_wave_barrier();
+  uint64_t rmask[DXT_RT];
+#pragma unroll
+  for (int rt = 0; rt < DXT_RT; ++rt) rmask[rt] = reach[32 * rt + i];
+  auto reaches = [&](int rt, uint32_t tap) { return ((rmask[rt] >> tap) & 1u) != 0; };
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const uint32_t ch = c0 + uint32_t(32 * ct + i);
@@ -1346,7 +1380,7 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
       if (few) {
         f16x8 rb;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) rb[k] = (flags[rt] >> k) & 1u ? _Float16(1.0f) : _Float16(0.0f);
+        for (int k = 0; k < 8; ++k) rb[k] = reaches(rt, 8 * g + k) ? _Float16(1.0f) : _Float16(0.0f);
         cz = __builtin_amdgcn_mfma_f32_32x32x16_f16(wsum[ct], rb, cz, 0, 0, 0);
       } else if (a.D <= 2048) {
         for (uint32_t tb = 0; tb < a.taps; tb += 16) {
@@ -1354,14 +1388,15 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
             wa[k] = _Float16(float(line_sum(ch, tb + 8 * g + k)));
-            rb[k] = reaches(rt, tb + 8 * g + k) ? _Float16(1.0f) : _Float16(0.0f);
+            rb[k] = tb + 8 * g + k < a.taps && reaches(rt, tb + 8 * g + k) ? _Float16(1.0f) : _Float16(0.0f);
           }
           cz = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa, rb, cz, 0, 0, 0);
         }
       } else {
         for (uint32_t j = 0; 2 * j < a.taps; ++j)
           cz = __builtin_amdgcn_mfma_f32_32x32x2f32(float(line_sum(ch, 2 * j + g)),
-                                                    reaches(rt, 2 * j + g) ? 1.0f : 0.0f, cz, 0, 0, 0);
+                                                    2 * j + g < a.taps && reaches(rt, 2 * j + g) ? 1.0f : 0.0f,
+                                                    cz, 0, 0, 0);
       }
       const float S = psz[32 * rt + i].x, Z = psz[32 * rt + i].y;
       const int off = pix[32 * rt + i];
@@ -1372,7 +1407,7 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
         const int I = int(acc[rt][ct][v]) + (B8 ? 128 * __shfl(wtot, row) : 0);
         float out = rescale(S, I, Z, cz[v]);
         if (a.vec) {
-          st[row * DXT_PITCH + 32 * rt + i] = out;
+          lds[row * DXT_PITCH + 32 * rt + i] = __float_as_uint(out);
         } else if (off >= 0 && cc < a.C) {
           const size_t o = size_t(off) + size_t(cc) * a.HW;
           out = ste_pass(a, o) ? out : 0.0f;
@@ -1384,7 +1419,7 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
     }
     if (a.vec) {
       __builtin_amdgcn_wave_barrier();    // LDS operations of a wave run in order
-      dx_store_tile(a, pix, st, c0 + uint32_t(32 * ct), lane);
+      dx_store_tile(a, pix, lds, c0 + uint32_t(32 * ct), lane);
       __builtin_amdgcn_wave_barrier();    // the next tile's copy waits for these reads
     }
   }

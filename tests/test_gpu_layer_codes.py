@@ -109,6 +109,54 @@ def test_layer_matches_the_entries(layer, bits, agp, dtype, spread):
     assert torch.count_nonzero(dw).item() > 0
 
 
+# Register tiles of dX: two groups of taps, strides and paddings that differ by direction, one and two
+# channel tiles, D past the f16 line sums, b = 8's bias, a ragged last tile.
+TILES = [
+    (LayerShape("c", "conv2d", 20, 40, 33, 48, 48, 7, 7, 1, 1, 3, 3), 2, 2),
+    (LayerShape("c", "conv2d", 60, 9, 70, 61, 45, 5, 3, 2, 3, 2, 0), 3, 0),
+    (LayerShape("c", "conv2d", 60, 9, 70, 45, 61, 8, 8, 3, 2, 0, 4), 8, 2),
+    (LayerShape("c", "conv2d", 90, 70, 20, 40, 52, 3, 3, 2, 2, 1, 1), 8, 0),
+    (LayerShape("c", "conv2d", 48, 200, 2100, 16, 16, 2, 2, 1, 1, 1, 1), 1, 2),
+    (LayerShape("c", "conv2d", 96, 40, 65, 30, 30, 1, 1, 2, 2, 0, 0), 4, 2),
+]
+
+
+@pytest.mark.parametrize("layer,bits,agp", TILES)
+def test_register_tiles_against_fold(layer, bits, agp):
+    """dX of the entry and of the layer, bit for bit, against the float64 product of the byte codes and
+    the signs, folded, and rescaled in float32 as the method states it."""
+    from paper_2408_14267_amd import fqt
+    print(f"[gpu layer codes] tiles {layer} b={bits} agp={agp}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(12)
+    x, w, dy = (torch.randn(s, generator=g, device="cuda") for s in (layer.x_shape, layer.w_shape, layer.dy_shape))
+    desc, cfg = fqt.layer_desc(layer), fqt.quant_cfg(bits, agp, 17, 3, 2)
+    q = fqt.QGrad(desc, cfg)
+    fqt.fqt_agp_scq_quantize(desc, cfg, dy, q, fqt.workspace(desc, cfg, fqt.FQT_WS_QUANTIZE))
+    C, D, P, K = layer.C, layer.D, layer.Ho * layer.Wo, layer.C * layer.kh * layer.kw
+    Wd = (D + 63) // 64
+    wsb = torch.empty(K * 64 * Wd, dtype=torch.int8, device="cuda")
+    wsum = torch.empty(K, dtype=torch.int32, device="cuda")
+    fqt.fqt_pack_weight_signs(desc, w, wsb, wsum)
+    kept = q.psq_kept[:int(q.psq_count)].long()
+    signs = torch.where(w.view(D, K) > 0, 1.0, -1.0).double().t().contiguous()
+    fold = lambda cols: torch.nn.functional.fold(cols, (layer.H, layer.W), (layer.kh, layer.kw),
+                                                 padding=layer.pad, stride=layer.stride)
+    c = fold(signs.sum(1).view(1, K, 1).expand(1, K, P).contiguous()).float()
+    codes = q.psq_codes.view(2 * Wd, layer.N * P, 32)
+    want = torch.zeros_like(x)
+    for j, n in enumerate(kept.tolist()):
+        rows = codes[:, j * P:(j + 1) * P].permute(0, 2, 1).reshape(64 * Wd, P)[:D].double()
+        i = fold((signs @ rows).view(1, K, P)).float()          # (integers below 2^24)
+        want[n] = (q.psq_scale[n] * i + q.psq_offset[n] * c)[0]
+    dx, dx2, dw = torch.full_like(x, 7.0), torch.full_like(x, 7.0), torch.empty_like(w)
+    fqt.fqt_binary_gemm_dx(desc, cfg, q, wsb, wsum, dx)
+    fqt.fqt_layer_backward(desc, cfg, x, w, dy, dx2, dw, fqt.workspace(desc, cfg))
+    torch.cuda.synchronize()
+    assert len(kept) > 0
+    assert torch.equal(dx, want), "dX of the entry"
+    assert torch.equal(dx2, want), "dX of the layer"
+
+
 @pytest.mark.parametrize("stride,pad", [(2, 1), (3, 1), (1, 1), (2, 2)])
 @pytest.mark.parametrize("bits", [2, 4])
 def test_padded_one_tap_on_one_pixel_maps(stride, pad, bits):
