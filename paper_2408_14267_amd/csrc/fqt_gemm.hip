@@ -858,7 +858,7 @@ struct DxArgs {
   void *dX;                      // [N][C][H][W]
   int32_t *I_out;
   int dx_t;
-  uint32_t N, C, H, W, HW, Ho, Wo, P, R, Dp, ctiles, CHW, taps, nch;   // nch = Dp / 32
+  uint32_t N, C, H, W, HW, Ho, Wo, P, R, Dp, ctiles, CHW, taps, nch;   // nch = ceil(D / 32)
   uint32_t codes_bytes, wsb_bytes;
   int kh, kw, sh, sw, ph, pw;
   FastDiv divHW, divW, divKw, divNch, divCt, divSh, divSw;
@@ -1316,11 +1316,11 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
     Batch b0, b1;
     issue(0, b0);
     for (uint32_t s0 = 0;;) {
-      issue(s0 + DXT_NB, b1);
+      if (s0 + DXT_NB < steps) issue(s0 + DXT_NB, b1);
       consume(b0);
       s0 += DXT_NB;
       if (s0 >= steps) break;
-      issue(s0 + DXT_NB, b0);
+      if (s0 + DXT_NB < steps) issue(s0 + DXT_NB, b0);
       consume(b1);
       s0 += DXT_NB;
       if (s0 >= steps) break;
@@ -1803,7 +1803,7 @@ DxArgs make_dx_args(const Layer &L, const fqt_qgrad &q, const int8_t *wsb,
   a.ctiles = uint32_t((L.C + 31) / 32);
   a.CHW = uint32_t(L.C * L.HW);
   a.taps = uint32_t(L.kh * L.kw);
-  a.nch = a.Dp / 32;
+  a.nch = uint32_t((L.D + 31) / 32);     // (a chunk past D would be all zeros)
   a.codes_bytes = uint32_t(L.R * L.Wd * 64);
   a.wsb_bytes = uint32_t(L.K * L.Wd * 64);
   a.kh = L.kh; a.kw = L.kw; a.sh = L.sh; a.sw = L.sw; a.ph = L.ph; a.pw = L.pw;
@@ -2026,7 +2026,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
   }
   DgArgs dg{};
   if (fp4) {                              // nibble operands: half the chunks and bytes
-    dxa.nch /= 2;
+    dxa.nch = uint32_t((L.D + 63) / 64);
     dxa.divNch = make_fastdiv(dxa.nch);
     dxa.codes_bytes /= 2;
     dxa.wsb_bytes /= 2;
