@@ -1776,20 +1776,32 @@ uint32_t dw_part_blocks(const Layer &L, const DwArgs &a) {
   return a.S * a.kgroups * uint32_t((L.D + 31) / 32);
 }
 
-// Register tiles once the capacity has DX_TILES tiles of 32 x 32.
-constexpr int64_t DX_TILES = 8192;
-uint32_t dx_form(const Layer &L) {
-  const int64_t ctiles = (L.C + 31) / 32, tiles = ((L.N * L.HW + 31) / 32) * ctiles;
-  // (strided layers twice as many: most of a pixel's taps meet nothing, and the split form
-  // spreads what is left over four waves; 29 against 33 us at 12544 tiles)
-  if (tiles < (L.sh * L.sw > 1 ? 2 : 1) * DX_TILES) return DX_SPLIT;
+// Register tiles where the samples expected to be kept (all, or about N / b under AGP) give enough
+// waves, the more the longer the contraction: with few, the chip idles through a wave's whole
+// contraction, which the split form spreads over four.  Time of the launch in register tiles over
+// that in the split form, by waves (1 x 1 to 7 x 7 layers, strided ones among them, b = 1, 2, 3, 4
+// and 8, 100 cases): 256 waves 1.1 - 2.8; about 400 with up to 18 steps 0.8 - 0.96, with 36 and
+// more 1.1 - 1.5; 512 with 9, 18 and 36 steps 0.96, 0.77, 0.9; 784 0.67 - 0.82; 1568 and more
+// 0.44 - 0.94.  Where the dW blocks share the launch (fewer than DW_SPLIT_MIN words) they run at the
+// register tiles' occupancy too: 400 to 512 waves 1.1 - 1.25, 784 and 894 with byte codes 1.04 and 1.1,
+// with nibbles 0.77 - 0.92, 1568 0.7 - 0.94.  Linear layers: 512 waves 0.77 - 1.23, 1024 0.5 - 0.75.
+uint32_t dx_form(const Layer &L, const fqt_quant_cfg &cfg) {
+  const int64_t live =
+      cfg.agp_mode == FQT_AGP_OFF ? L.N : std::max<int64_t>(1, (L.N + cfg.bits - 1) / cfg.bits);
+  const int64_t ctiles = (L.C + 31) / 32, chunk = cfg.bits <= 2 ? 64 : 32;
+  const int64_t steps = int64_t(L.kh) * L.kw * ((L.D + chunk - 1) / chunk);
+  const int64_t waves = (live * L.HW + 32 * DXT_RT - 1) / (32 * DXT_RT) * ((ctiles + 1) / 2);
   // (padding puts output pixels where the one tap does not reach the map, and a stride may leave
   // only such pixels: those need the reach flags of the other forms)
-  if (L.HW == 1 && L.kh * L.kw == 1 && L.ph == 0 && L.pw == 0) return DX_LIN;
-  return ctiles > 1 ? DX_CT2 : DX_CT1;
+  const bool lin = L.HW == 1 && L.kh * L.kw == 1 && L.ph == 0 && L.pw == 0;
+  const int64_t need = lin ? 640
+                       : L.Wr < DW_SPLIT_MIN ? (cfg.bits <= 2 ? 640 : 1024)
+                                             : std::min<int64_t>(640, 300 + 5 * steps);
+  if (waves < need) return DX_SPLIT;
+  return lin ? DX_LIN : ctiles > 1 ? DX_CT2 : DX_CT1;
 }
 
-DxArgs make_dx_args(const Layer &L, const fqt_qgrad &q, const int8_t *wsb,
+DxArgs make_dx_args(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q, const int8_t *wsb,
                     const int32_t *wlsum, void *dX, int32_t *I_out) {
   DxArgs a;
   a.codes = q.psq_codes; a.kept = q.psq_kept; a.count = q.psq_count;
@@ -1816,7 +1828,7 @@ DxArgs make_dx_args(const Layer &L, const fqt_qgrad &q, const int8_t *wsb,
   // min(2048, N * pieces) blocks are left for the zeroing.
   a.zpieces = uint32_t((int64_t(a.CHW) + DX_ZCHUNK - 1) / DX_ZCHUNK);
   a.D = uint32_t(L.D);
-  a.wide = dx_form(L);
+  a.wide = dx_form(L, cfg);
   const uint32_t ct = a.wide == DX_CT1 ? 1 : 2;
   a.cblocks = a.wide ? (a.ctiles + ct - 1) / ct : a.ctiles;
   const size_t es = L.dx_t == FQT_BF16 ? 2 : 4;
@@ -1905,7 +1917,7 @@ bool dw_fp4_form(const Layer &L, const fqt_quant_cfg &cfg) {
 
 // Nibble codes and signs for dX: codes of at most 3, register tiles, sums below 2^24.
 bool dx_fp4_form(const Layer &L, const fqt_quant_cfg &cfg) {
-  return cfg.bits <= 2 && dx_form(L) != DX_SPLIT &&
+  return cfg.bits <= 2 && dx_form(L, cfg) != DX_SPLIT &&
          ((1 << cfg.bits) - 1) * L.D * L.kh * L.kw < (int64_t(1) << 24);
 }
 
@@ -1947,7 +1959,7 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                    const int8_t *wsb, const int32_t *wlsum, void *dX, int32_t *I_out,
                    hipStream_t s) {
   if (L.kh * L.kw > DX_MAX_TAPS) return FQT_E_SHAPE;
-  const DxArgs a = make_dx_args(L, q, wsb, wlsum, dX, I_out);
+  const DxArgs a = make_dx_args(L, cfg, q, wsb, wlsum, dX, I_out);
   const dim3 grid(a.nblocks);
   const int nb = dx_batch(a);
   auto go = [&]<bool B8, int WT>() {
@@ -1981,7 +1993,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
                     const void *wrows, bool fp4, bool dw4) {
   if (L.kh * L.kw > DX_MAX_TAPS || (wrows && fp4)) return FQT_E_SHAPE;
   DwArgs dwa = make_dw_args(L, cfg, q, xsign, dW, nullptr, dw_ws);
-  DxArgs dxa = make_dx_args(L, q, wsb, wlsum, dX, nullptr);
+  DxArgs dxa = make_dx_args(L, cfg, q, wsb, wlsum, dX, nullptr);
   dwa.slot_sz = cslot;
   dxa.slot_sz = sslot;
   // A large one-split dW runs as its own launch in the 2 x 2-tile form; the products

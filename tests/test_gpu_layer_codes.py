@@ -43,8 +43,8 @@ CASES = [
     (LayerShape("fc", "linear", 65, 6000, 1000), 1, 2, "f32", 1.0),
     (LayerShape("fc", "linear", 64, 2051, 2100), 4, 0, "f32", 1.5),
     (LayerShape("fc", "linear", 33, 3000, 1500), 4, 1, "bf16", 3.0),
-    # Few rows and as many outputs as the register tiles take (8192 tiles of 32 x 32; the first
-    # case has eight fewer): dX from W itself reads byte codes also for b <= 2.
+    # Few rows and so many outputs that the register tiles would take them: dX from W itself reads
+    # byte codes also for b <= 2.
     (LayerShape("fc", "linear", 128, 65472, 18), 2, 0, "f32", 1.5),
     (LayerShape("fc", "linear", 128, 65536, 18), 2, 0, "f32", 1.5),
     (LayerShape("fc", "linear", 100, 65536, 70), 1, 2, "bf16", 1.0),
