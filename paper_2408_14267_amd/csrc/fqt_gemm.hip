@@ -1425,7 +1425,7 @@ __device__ __forceinline__ void dx_body_tiles(const DxArgs &a, uint32_t bid, DxT
   }
 }
 
-// Linear layers of at most DXR_ROWS rows with large W: the product is bound by reading W, so W is
+// Linear layers of at most DXR_ROWS rows with large W (dx_rows_form): the product is bound by reading W, so W is
 // read once, as it is (no byte copy of its signs).  A block takes 64 channels, its waves every
 // DXR_WAVES-th chunk of 32 output channels d; lane (i = lane % 32, g = lane / 32) loads channels
 // 2 i, 2 i + 1 of rows d = 16 g .. 16 g + 15 (256 contiguous bytes per row) and packs their
@@ -1444,7 +1444,6 @@ struct DxRowsArgs {
 };
 constexpr int DXR_WAVES = 8, DXR_THREADS = 64 * DXR_WAVES;
 constexpr uint32_t DXR_ROWS = 128;
-constexpr int64_t DXR_MIN_W_BYTES = int64_t(4) << 20;
 
 template <bool B8, int NT, int WDT>
 __global__ __launch_bounds__(DXR_THREADS) void k_dx_rows(DxRowsArgs a) {
@@ -1847,10 +1846,10 @@ int dx_batch(const DxArgs &a) {
   return per_wave <= 4 ? 4 : per_wave <= 8 ? 8 : 10;
 }
 
-// One split and at least 1024 waves of 64 x 64: the 2 x 2-tile form.
-bool dw_big(const Layer &L, const DwArgs &a) {
-  return a.S == 1 && ((L.D + 63) / 64) * ((L.K + 63) / 64) >= 1024;
-}
+// One split (contractions of at most DW_PREF words always are) and at least 1024 waves of 64 x 64:
+// the 2 x 2-tile form.
+bool dw_big_tiles(const Layer &L) { return ((L.D + 63) / 64) * ((L.K + 63) / 64) >= 1024; }
+bool dw_big(const Layer &L, const DwArgs &a) { return a.S == 1 && dw_big_tiles(L); }
 
 // Split-R products over long contractions (N*Ho*Wo of DW_SPLIT_MIN words and more, slices
 // of 16 words and more): the partials in the big form's wave tiles, in a launch of their
@@ -1921,13 +1920,16 @@ bool dx_fp4_form(const Layer &L, const fqt_quant_cfg &cfg) {
          ((1 << cfg.bits) - 1) * L.D * L.kh * L.kw < (int64_t(1) << 24);
 }
 
-// The linear layers k_dx_rows takes: few rows, W of 4 MB and more (below, the product shares its
-// launch with dW and packing W hides beside the selection), pairs of channels on 4-byte
-// addresses, 32 rows of W in one buffer.
+// The linear layers k_dx_rows takes: few rows; dW in a launch of its own (else the packed form's dX
+// shares the dW blocks' launch and packing W hides beside the selection: layer time 1.06 - 1.36 of
+// the packed form's for N = 1 .. 128, C = 1024 .. 25088); enough blocks of 64 channels (float32 W,
+// D = 512 .. 4096: C = 1024 1.07 - 1.15, 2048 0.96 - 1.14, 4096 0.92 - 1.02 up to 64 rows and
+// 0.99 - 1.09 above, 8192 0.85 - 1.04, 16384 0.77 - 0.98); pairs of channels on 4-byte addresses,
+// 32 rows of W in one buffer.
 bool dx_rows_form(const Layer &L, const void *W) {
   const int64_t es = L.w_t == FQT_BF16 ? 2 : 4;
-  return L.kind == FQT_LINEAR && L.N <= int64_t(DXR_ROWS) && L.D * L.C * es >= DXR_MIN_W_BYTES &&
-         L.C % 2 == 0 && aligned(W, 4) && 32 * L.C * es < (int64_t(1) << 31);
+  return L.kind == FQT_LINEAR && L.N <= int64_t(DXR_ROWS) && L.C >= (L.N <= 64 ? 4096 : 8192) &&
+         dw_big_tiles(L) && L.C % 2 == 0 && aligned(W, 4) && 32 * L.C * es < (int64_t(1) << 31);
 }
 
 int launch_gemm_dw(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,

@@ -43,6 +43,10 @@ CASES = [
     (LayerShape("fc", "linear", 65, 6000, 1000), 1, 2, "f32", 1.0),
     (LayerShape("fc", "linear", 64, 2051, 2100), 4, 0, "f32", 1.5),
     (LayerShape("fc", "linear", 33, 3000, 1500), 4, 1, "bf16", 3.0),
+    (LayerShape("fc", "linear", 20, 8198, 1030), 3, 0, "f32", 1.5),
+    (LayerShape("fc", "linear", 128, 8194, 1100), 8, 0, "f32", 1.0),
+    (LayerShape("fc", "linear", 65, 9000, 600), 1, 2, "bf16", 1.0),
+    (LayerShape("fc", "linear", 33, 5000, 1500), 4, 1, "bf16", 3.0),
     # Few rows and so many outputs that the register tiles would take them: dX from W itself reads
     # byte codes also for b <= 2.
     (LayerShape("fc", "linear", 128, 65472, 18), 2, 0, "f32", 1.5),
