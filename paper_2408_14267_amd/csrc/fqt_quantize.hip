@@ -365,17 +365,17 @@ __global__ __launch_bounds__(THREADS) void k_stats(const void *__restrict__ dy, 
   }
 }
 
-// Larger maps (Ho*Wo >= 256, whole quads): a wave streams channel planes of one sample, the four
-// waves of a block the same channels of four samples; lanes keep float minima and maxima (one
-// v_min3 / v_max3 per two elements: with the integer keys of the tile form, formed per element,
-// the VALU took as long as the memory), a sample's over the wave's channels, a channel's met over
-// the block in LDS, and both merge into the group keys by atomics.  Batches of LINE_U quads per
-// lane are double-buffered.  Grid: segments of the planes (where planes are few) x sample
-// groups x channel groups of cpw channels, the channel groups fastest.
+// Larger maps (Ho*Wo >= 256, whole quads): a wave streams cpw channel planes of one sample, the four
+// waves of a block adjacent channels; lanes keep float minima and maxima (one v_min3 / v_max3 per
+// two elements: with the integer keys of the tile form, formed per element, the VALU took as
+// long as the memory).  A sample's keys meet over the block in LDS and merge into the group keys by
+// one atomic each; the block's channels, adjacent, merge together.  Batches of LINE_U quads per
+// lane are double-buffered.  Grid: segments of the planes (where planes are few) x samples x
+// channel groups of 4 cpw channels, the channel groups fastest.
 constexpr int LINE_U = 4, LINE_MAX_CPW = 16;
 struct LineGeom {
-  uint32_t N, D, P4, cpw, cgroups, sgroups, seg;   // seg: quads per segment, a multiple of 64 LINE_U
-  FastDiv divCg, divSg;
+  uint32_t N, D, P4, cpw, cgroups, seg;            // seg: quads per segment, a multiple of 64 LINE_U
+  FastDiv divCg, divN;
 };
 __device__ __forceinline__ float min3(float a, float b, float c) {
   float r;
@@ -391,16 +391,19 @@ template <int DT, bool TR>
 __global__ __launch_bounds__(256) void k_stats_lines(const void *__restrict__ dy, LineGeom g,
                                                      uint2 *__restrict__ mks,
                                                      uint2 *__restrict__ mkc, StatsTrain tr) {
-  __shared__ int32_t clo[4][LINE_MAX_CPW], chi[4][LINE_MAX_CPW];
-  __shared__ float cg[4][LINE_MAX_CPW];
+  __shared__ int32_t clo[4 * LINE_MAX_CPW], chi[4 * LINE_MAX_CPW], wlo[4], whi[4];
+  __shared__ float cg[4 * LINE_MAX_CPW];
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t rest = fdiv(blockIdx.x, g.divCg), cgrp = blockIdx.x - rest * g.cgroups;
-  const uint32_t sgm = fdiv(rest, g.divSg), n = 4 * (rest - sgm * g.sgroups) + wave;
-  const uint32_t d0 = cgrp * g.cpw, nc = min(g.cpw, g.D - d0);
+  const uint32_t sgm = fdiv(rest, g.divN), n = rest - sgm * g.N;
+  const uint32_t b0 = cgrp * 4 * g.cpw, w0 = wave * g.cpw, d0 = b0 + w0;
+  // (not d0 < D ? min(cpw, D - d0) : 0: the compiler kept the minimum of that and dropped the test, and
+  // waves past the last channel read past dY)
+  const uint32_t nc = min(d0 + g.cpw, g.D) - min(d0, g.D);
   const uint32_t q0 = sgm * g.seg, q1 = min(g.P4, q0 + g.seg);
-  const uint32_t rep = (blockIdx.x % MKEY_REP) * MKEY_GROUPS;
-  if (n < g.N) {
+  int klo = INT_MAX, khi = INT_MIN;
+  if (nc) {
     const float inf = __builtin_inff();
     float slo = inf, shi = -inf, lo = inf, hi = -inf, gsum = 0.0f;
     float xa[LINE_U][4], xb[LINE_U][4];
@@ -442,12 +445,12 @@ __global__ __launch_bounds__(256) void k_stats_lines(const void *__restrict__ dy
         slo = fminf(slo, lo);
         shi = fmaxf(shi, hi);
         // (adding zero turns -0 into +0)
-        const int klo = wave_min(f2key(lo + 0.0f)), khi = wave_max(f2key(hi + 0.0f));
+        const int plo = wave_min(f2key(lo + 0.0f)), phi = wave_max(f2key(hi + 0.0f));
         if constexpr (TR) gsum = lanes_sum<6>(gsum);
         if (lane == 0) {
-          clo[wave][was] = klo;
-          chi[wave][was] = khi;
-          if (TR) cg[wave][was] = gsum;
+          clo[w0 + was] = plo;
+          chi[w0 + was] = phi;
+          if (TR) cg[w0 + was] = gsum;
         }
         lo = inf;
         hi = -inf;
@@ -455,33 +458,44 @@ __global__ __launch_bounds__(256) void k_stats_lines(const void *__restrict__ dy
         if (TR && c < nc) gam = tr.gamma[d0 + c];
       }
     };
-    load(cn, qn, xa, ia);
-    step(cn, qn);
-    for (;;) {
-      if (cn < nc) load(cn, qn, xb, ib);
+    // (no load under a condition inside the loop: the waits for one batch would cover the other)
+    const uint32_t total = nc * ((q1 - q0 + 64 * LINE_U - 1) / (64 * LINE_U));
+    auto next = [&](float (&x)[LINE_U][4], int4 (&iv)[TR ? LINE_U : 1]) {
+      load(cn, qn, x, iv);
+      step(cn, qn);
       __builtin_amdgcn_sched_barrier(0);
+    };
+    uint32_t done = 0;
+    next(xa, ia);
+    for (; done + 2 < total; done += 2) {
+      next(xb, ib);
       take(xa, ia);
-      if (cn >= nc) break;
-      step(cn, qn);
-      if (cn < nc) load(cn, qn, xa, ia);
-      __builtin_amdgcn_sched_barrier(0);
+      next(xa, ia);
       take(xb, ib);
-      if (cn >= nc) break;
-      step(cn, qn);
     }
-    const int klo = wave_min(f2key(slo + 0.0f)), khi = wave_max(f2key(shi + 0.0f));
-    if (lane == 0) merge_key(mks + rep + n, klo, khi);
-  } else if (lane < int(nc)) {
-    clo[wave][lane] = INT_MAX;
-    chi[wave][lane] = INT_MIN;
-    if (TR) cg[wave][lane] = 0.0f;
+    if (done + 1 < total) {
+      next(xb, ib);
+      take(xa, ia);
+      take(xb, ib);
+    } else {
+      take(xa, ia);
+    }
+    klo = wave_min(f2key(slo + 0.0f));
+    khi = wave_max(f2key(shi + 0.0f));
+  }
+  if (lane == 0) {
+    wlo[wave] = klo;
+    whi[wave] = khi;
   }
   __syncthreads();
+  // (replicas by the index that a key's other merges differ in)
   const uint32_t t = threadIdx.x;
-  if (t >= nc) return;
-  merge_key(mkc + rep + d0 + t, min(min(clo[0][t], clo[1][t]), min(clo[2][t], clo[3][t])),
-            max(max(chi[0][t], chi[1][t]), max(chi[2][t], chi[3][t])));
-  if (TR) tr.part[size_t(rest) * g.D + d0 + t] = (cg[0][t] + cg[1][t]) + (cg[2][t] + cg[3][t]);
+  if (t == 64)
+    merge_key(mks + (cgrp % MKEY_REP) * MKEY_GROUPS + n, min(min(wlo[0], wlo[1]), min(wlo[2], wlo[3])),
+              max(max(whi[0], whi[1]), max(whi[2], whi[3])));
+  if (t >= 4 * g.cpw || b0 + t >= g.D) return;
+  merge_key(mkc + (rest % MKEY_REP) * MKEY_GROUPS + b0 + t, clo[t], chi[t]);
+  if (TR) tr.part[size_t(rest) * g.D + b0 + t] = cg[t];
 }
 
 // Large group sets: block b < N reduces sample b over its slots, block N + d channel d
@@ -1910,28 +1924,31 @@ int64_t stats_row_blocks(const Layer &L) {
   return (L.Wr + rs - 1) / rs;
 }
 
-// Line statistics: channels per wave for about 4096 waves, and planes cut into segments (at
-// least two batches each) where even one channel per wave gives fewer than 2048.
+// Line statistics: channels per wave for about 4096 waves and at most 64 blocks a sample (whose
+// key they all merge into), and planes cut into segments (at least two batches each) where fewer than
+// 2048 waves come together.  Statistics and selection, us, this / tiles (k_stats): N x D on 16 x 16:
+// 31 x 261 12.0 / 12.4, 8 x 512 10.4 / 10.5, 64 x 64 8.9 / 10.4, 256 x 512 31 / 42; on 28 x 28: 31 x 261
+// 14.6 / 18.5, 64 x 512 24 / 38; on 56 x 56: 64 x 64 16 / 27.  (A block over four samples of cpw channels
+// merged four sample keys instead of one: 31 x 261 on 16 x 16 25.6.)
 bool line_geom(const Layer &L, LineGeom *g) {
   if (L.P < 256 || L.P % 4 || L.N > 1024 || L.D > 1024) return false;
   g->N = uint32_t(L.N); g->D = uint32_t(L.D); g->P4 = uint32_t(L.P / 4);
-  g->cpw = uint32_t(std::min<int64_t>(LINE_MAX_CPW, std::max<int64_t>(1, L.N * L.D / 4096)));
-  g->cgroups = (g->D + g->cpw - 1) / g->cpw;
-  g->sgroups = (g->N + 3) / 4;
+  g->cpw = uint32_t(std::min<int64_t>(LINE_MAX_CPW, std::max<int64_t>((L.D + 255) / 256, L.N * L.D / 4096)));
+  g->cgroups = (g->D + 4 * g->cpw - 1) / (4 * g->cpw);
   const uint32_t batch = 64 * LINE_U, batches = (g->P4 + batch - 1) / batch;
-  const uint32_t want = 2048 / (g->cgroups * std::min<uint32_t>(g->N, 4 * g->sgroups)) + 1;
+  const uint32_t want = 512 / (g->cgroups * g->N) + 1;
   const uint32_t segs = std::max(1u, std::min(want, batches / 2));
   g->seg = (batches + segs - 1) / segs * batch;
   g->divCg = make_fastdiv(g->cgroups);
-  g->divSg = make_fastdiv(g->sgroups);
+  g->divN = make_fastdiv(g->N);
   return true;
 }
-uint32_t line_parts(const Layer &, const LineGeom &g) {   // (segment, sample group) pairs
-  return g.sgroups * ((g.P4 + g.seg - 1) / g.seg);
+uint32_t line_parts(const Layer &, const LineGeom &g) {   // (segment, sample) pairs
+  return g.N * ((g.P4 + g.seg - 1) / g.seg);
 }
 
-// Partial sums of dgamma: one row per row block of the statistics, or per segment and sample
-// group of the lines.
+// Partial sums of dgamma: one row per row block of the statistics, or per segment and sample of
+// the lines.
 size_t train_part_bytes(const Layer &L) {
   LineGeom g;
   const int64_t parts = line_geom(L, &g) ? int64_t(line_parts(L, g)) : stats_row_blocks(L);

@@ -113,6 +113,32 @@ def test_layer_matches_the_entries(layer, bits, agp, dtype, spread):
     assert torch.count_nonzero(dw).item() > 0
 
 
+@pytest.mark.parametrize("N,D,H,W,dtype", [
+    (31, 261, 16, 16, "bf16"),     # a last block whose waves lie past the last channel
+    (3, 1, 32, 33, "f32"), (2, 6, 20, 13, "f32"), (1, 1024, 16, 17, "f32"), (1024, 5, 16, 16, "bf16"),
+    (2, 65, 112, 112, "f32"),      # planes in segments, a ragged last batch
+    (700, 130, 16, 18, "f32"),     # several channels per wave
+])
+def test_line_statistics(N, D, H, W, dtype):
+    """Without AGP the offsets are the groups' minima and the scales their ranges over B, exactly."""
+    from paper_2408_14267_amd import fqt
+    layer = LayerShape("c", "conv2d", N, 1, D, H, W)
+    print(f"[gpu layer codes] statistics {layer} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    dy = torch.randn(layer.dy_shape, generator=g, device="cuda") + 0.5
+    if dtype == "bf16":
+        dy = dy.to(torch.bfloat16)
+    desc, cfg = fqt.layer_desc(layer, fqt.dtype_code(dtype)), fqt.quant_cfg(2, fqt.FQT_AGP_OFF)
+    q, ws = fqt.QGrad(desc, cfg), fqt.workspace(desc, cfg, fqt.FQT_WS_QUANTIZE)
+    y = dy.float()
+    for _ in range(2):                                  # (the merged keys are left zero)
+        fqt.fqt_agp_scq_quantize(desc, cfg, dy, q, ws)
+        torch.cuda.synchronize()
+        for dims, offset, scale in (((1, 2, 3), q.psq_offset, q.psq_scale), ((0, 2, 3), q.pcq_offset, q.pcq_scale)):
+            lo, hi = y.amin(dims), y.amax(dims)
+            assert torch.equal(offset, lo) and torch.equal(scale, ((hi - lo).double() / 3).float())
+
+
 # Register tiles of dX: two groups of taps, strides and paddings that differ by direction, one and two
 # channel tiles, D past the f16 line sums, b = 8's bias, a ragged last tile.
 TILES = [
