@@ -19,13 +19,7 @@
 namespace fqt {
 namespace {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ int acc_row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
-__device__ __forceinline__ float rescale(float S, int I, float Zp, float c) {
-  return __fadd_rn(__fmul_rn(S, float(I)), __fmul_rn(Zp, c));
-}
 
 struct PlaneArgs {
   const uint64_t *planes;        // [b][D][Wr] PCQ code planes, kept channels compacted
@@ -167,10 +161,6 @@ struct Fp4Args {
   const uint8_t *B;              // [Wr][Kp][32] nibbles of the sign bits (t = 1 for +1)
   uint32_t Dp, Kp, a_bytes, b_bytes, kgroups;
 };
-
-// The e2m1 operand of the scaled MFMA: four dwords (32 nibbles) per lane; the instruction
-// reads no more for fp4.
-__device__ __forceinline__ v8i as_v8(v4i v) { return v8i{v.x, v.y, v.z, v.w, 0, 0, 0, 0}; }
 
 // Wave tile 64 x 64 (2 x 2 MFMA tiles); a block's four waves take four adjacent column
 // tiles of the same 64 slots.  Grid: ceil(Dp / 64) slot blocks (slowest) x ceil(Kp / 256).

@@ -18,19 +18,10 @@
 namespace fqt {
 namespace {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int THREADS = 256;
 constexpr int WAVES = THREADS / 64;
-
-__device__ __forceinline__ v8i as_v8(v4i v) { return v8i{v.x, v.y, v.z, v.w, 0, 0, 0, 0}; }
-__device__ __forceinline__ uint32_t wave_id() {
-  return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-}
-// Output row (0..31) of accumulator v of a lane in half-wave g of a 32 x 32 MFMA tile.
-__device__ __forceinline__ int acc_row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
 
 // sign(x) as the e2m1 nibble at nibble position m of a dword.
 __device__ __forceinline__ uint32_t nib(float x, int m) {
@@ -205,16 +196,7 @@ struct FwdArgs {
   uint64_t xstride, wstride;     // bytes per chunk of X and per step of W
   FastDiv divP, divWo, divDb;
 };
-constexpr uint32_t XCDS = 8, FWD_RUN = 16;
-
-// Workgroups go to the eight XCDs in turn; every XCD takes runs of FWD_RUN consecutive tiles
-// (neighbouring tiles read the same X rows and share its L2).  A bijection of [0, n).
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t s, uint32_t n) {
-  constexpr uint32_t ROUND = XCDS * FWD_RUN;
-  if (s >= n / ROUND * ROUND) return s;
-  const uint32_t x = s % XCDS, i = s / XCDS;
-  return ((i / FWD_RUN) * XCDS + x) * FWD_RUN + i % FWD_RUN;
-}
+constexpr uint32_t FWD_RUN = 16;      // (xcd_tile: neighbouring tiles read the same X rows)
 
 // Stores of one tile of 32 channels from d0 x 32 RT rows from r0 of integers from its LDS copy
 // [channel][row] (pitch st_pitch(RT)) when P % 4 == 0: pieces of 4 consecutive pixels of one
@@ -290,7 +272,7 @@ void k_fwd(FwdArgs a, uint32_t vec) {
   __shared__ __align__(16) int32_t lds[RED > STG ? RED : STG];
   const int lane = threadIdx.x & 63, i = lane & 31, g = lane >> 5;
   const uint32_t wave = wave_id(), tile = wave / KS, part = wave - tile * KS;
-  const uint32_t bid = xcd_tile(blockIdx.x, a.nblocks);
+  const uint32_t bid = xcd_tile<FWD_RUN>(blockIdx.x, a.nblocks);
   const uint32_t rb = fdiv(bid, a.divDb), db = bid - rb * a.dblocks;
   const uint32_t d0 = db * (32 * CT), r0 = (rb * TPB + tile) * (32 * RT);
   // The input pixel under tap (0, 0) of this lane's output pixels.

@@ -36,16 +36,7 @@
 namespace fqt {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef int v8i __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-// The wave index as a scalar, so that per-wave loop bounds and strides stay in SGPRs.
-__device__ __forceinline__ uint32_t wave_id() {
-  return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-}
 
 // 16 sign bits (LSB first) -> 16 signed bytes, +1 for a set bit and -1 for a clear one
 // (byte m of dword k holds bit 4k + m).  A nibble times 0x00408102 puts bit m at bit
@@ -69,29 +60,6 @@ __device__ __forceinline__ v4i bias128(v4i a) {
 __device__ __forceinline__ v16i mfma_i8(v4i a, v4i b, v16i c) {
   return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
 }
-
-__device__ __forceinline__ float rescale(float S, int I, float Zp, float c) {
-  return __fadd_rn(__fmul_rn(S, float(I)), __fmul_rn(Zp, c));
-}
-
-// The dispatcher hands the workgroups of a launch to the eight XCDs in turn (block b to
-// XCD b % 8), and each XCD has its own L2.  xcd_tile maps the s-th block of a segment of n
-// blocks to a tile index so that every XCD walks runs of RUN consecutive tiles: its k-th
-// run (in dispatch order) is tiles [RUN (8 k + x), RUN (8 k + x + 1)) for x = s % 8, and
-// neighbouring tiles, which read the same operand rows, share one L2.  A bijection of
-// [0, n): blocks past the last whole round of 8 runs keep their own index.  (Any other
-// dispatch order changes only which L2 a tile's operands go through.)
-constexpr uint32_t XCDS = 8;
-template <uint32_t RUN>
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t s, uint32_t n) {
-  constexpr uint32_t ROUND = XCDS * RUN;
-  if (s >= n / ROUND * ROUND) return s;
-  const uint32_t x = s % XCDS, i = s / XCDS;
-  return ((i / RUN) * XCDS + x) * RUN + i % RUN;
-}
-
-// Output row (0..31) of accumulator v of a lane in half-wave g.
-__device__ __forceinline__ int acc_row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
 
 // Zero `count` elements of `esize` bytes starting at element `first` of `base`, by the
 // `nthr` threads of a block: 16-byte stores where the run is 16-byte aligned, bytes of
@@ -1116,8 +1084,6 @@ struct alignas(16) DxTileLds {
 };
 constexpr int DXT_TAPS = 32;                         // taps tabulated at once
 static_assert(DXT_TAPS * 32 * DXT_RT <= 32 * DXT_PITCH && 32 * DXT_RT == 64, "code rows in the tile's place");
-
-__device__ __forceinline__ v8i as_v8(v4i v) { return v8i{v.x, v.y, v.z, v.w, 0, 0, 0, 0}; }
 
 // Stores of one wave's 32 channels x 64 pixels from their LDS copy [channel][pixel]: pieces of
 // 4 pixels of one channel (HW % 4 == 0: of one sample), consecutive lanes on consecutive

@@ -328,21 +328,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // Keeps the compiler from merging the stores of a streaming branch with those of the other one
 // (which drops the hint): before and after them.
 __device__ __forceinline__ void stream_fence() { asm volatile("; stream"); }
-// N values to p[0], p[step], ... (the branch outside the stores, so that they issue together).
-template <int N>
-__device__ __forceinline__ void store16s(uint4 *p, size_t step, const uint4 (&v)[N], bool stream) {
-  if (stream) {
-    stream_fence();
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-      __builtin_nontemporal_store(u32x4{v[k].x, v[k].y, v[k].z, v[k].w},
-                                  reinterpret_cast<u32x4 *>(p + k * step));
-    stream_fence();
-  } else {
-#pragma unroll
-    for (int k = 0; k < N; ++k) p[k * step] = v[k];
-  }
-}
 
 // Calls F.template operator()<DT>() with DT the compile-time dtype code of `dt`.
 template <typename F>
@@ -372,6 +357,42 @@ __device__ __forceinline__ v4i load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, u
 }
 __device__ __forceinline__ uint64_t load8(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
   return __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+}
+
+// ----------------------------------------------------------------------------- matrix tiles
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// The e2m1 operand of the scaled MFMA: four dwords (32 nibbles) per lane; the instruction
+// reads no more for fp4.
+__device__ __forceinline__ v8i as_v8(v4i v) { return v8i{v.x, v.y, v.z, v.w, 0, 0, 0, 0}; }
+// Output row (0..31) of accumulator v of a lane in half-wave g of a 32 x 32 MFMA tile.
+__device__ __forceinline__ int acc_row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
+// Output of the integer product I with zero-point term c.
+__device__ __forceinline__ float rescale(float S, int I, float Zp, float c) {
+  return __fadd_rn(__fmul_rn(S, float(I)), __fmul_rn(Zp, c));
+}
+
+// The wave index as a scalar, so that per-wave loop bounds and strides stay in SGPRs.
+__device__ __forceinline__ uint32_t wave_id() {
+  return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
+// The dispatcher hands the workgroups of a launch to the eight XCDs in turn (block b to
+// XCD b % 8), and each XCD has its own L2.  xcd_tile maps the s-th block of a segment of n
+// blocks to a tile index so that every XCD walks runs of RUN consecutive tiles: its k-th
+// run (in dispatch order) is tiles [RUN (8 k + x), RUN (8 k + x + 1)) for x = s % 8, and
+// neighbouring tiles, which read the same operand rows, share one L2.  A bijection of
+// [0, n): blocks past the last whole round of 8 runs keep their own index.  (Any other
+// dispatch order changes only which L2 a tile's operands go through.)
+constexpr uint32_t XCDS = 8;
+template <uint32_t RUN>
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t s, uint32_t n) {
+  constexpr uint32_t ROUND = XCDS * RUN;
+  if (s >= n / ROUND * ROUND) return s;
+  const uint32_t x = s % XCDS, i = s / XCDS;
+  return ((i / RUN) * XCDS + x) * RUN + i % RUN;
 }
 
 // ----------------------------------------------------------------------------- cross-lane

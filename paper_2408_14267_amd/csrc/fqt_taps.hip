@@ -27,12 +27,7 @@ namespace fqt {
 namespace {
 
 typedef int v3i __attribute__((ext_vector_type(3)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ v8i as_v8(v4i v) { return v8i{v.x, v.y, v.z, v.w, 0, 0, 0, 0}; }
-__device__ __forceinline__ int acc_row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
 
 struct TapsArgs {
   const uint8_t *codes;          // PCQ codes in the formats above
