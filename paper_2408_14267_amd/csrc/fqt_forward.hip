@@ -589,9 +589,12 @@ size_t forward_ws_bytes(const Layer &L) {
   const uint64_t few = uint64_t((L.C + 127) / 128) * 16 * few_rows_tiles(L) * 64;
   const uint64_t x = L.kind == FQT_LINEAR && L.N <= FEW_ROWS ? std::max(z.xbytes, few) : z.xbytes;
   const uint64_t need = align256(x) + align256(z.wbytes);
-  // The reported size is never below that of unfolded sign bits, once per word and once per
-  // row block, beside sign bytes of W (K and D rounded up to 64): callers that reserve by that
-  // formula, and those that reserve by the reported size, are both served.
+  // The reported size, which a call requires, is never below that of the unfolded operands (sign
+  // bits of X once per word and once per row block, beside sign bytes of W, K and D rounded up to
+  // 64): a lower bound that callers may hold it to.  It is above that where an input pixel's
+  // 32 ceil(C / 64) bytes exceed the C kh kw / 4 of an output pixel's unfolded bits (linear layers,
+  // 1 x 1 kernels, few channels, strides): a caller that reserves by the formula alone falls
+  // short there.
   const uint64_t Kp = uint64_t((L.K + 63) / 64 * 64);
   const uint64_t unfolded = align256(uint64_t(L.Wr) * L.K * 8) + align256(Kp / 64 * L.Wr * 512) +
                             align256(z.Dp * Kp);
