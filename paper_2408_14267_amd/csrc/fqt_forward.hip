@@ -426,8 +426,8 @@ void k_fwd(FwdArgs a, uint32_t vec) {
 
 // ----------------------------------------------------------------------------- few rows
 
-// Linear layers of at most FEW_ROWS rows: the weights are all the traffic, so each is read
-// once, from W itself.  A block takes 16 output channels, its waves every NW-th chunk of 128
+// Linear layers of at most FEW_ROWS rows and large W (few_rows): the weights are all the traffic, so each
+// is read once, from W itself.  A block takes 16 output channels, its waves every NW-th chunk of 128
 // input channels.  Lane (i = lane % 16, k = lane / 16) loads 16-byte pieces of W row d0 + i:
 // piece j holds the VW channels from 4 VW j + VW k of the chunk, so the four lanes of a row read
 // 64 contiguous bytes, and packs their signs to the 32 nibbles it feeds to
@@ -442,7 +442,8 @@ struct RowsArgs {
   int y_t;
   uint32_t N, C, D, nch, xf_bytes;
 };
-constexpr uint32_t FEW_ROWS = 128;
+constexpr uint32_t FEW_ROWS = 128;         // what eight row tiles hold
+constexpr int64_t FEW_ROWS_MIN_D = 3072, FEW_ROWS_MIN_C = 2048;
 
 template <int XDT, int VW>
 __global__ __launch_bounds__(THREADS) void k_fwd_rows_pack(RowsArgs a, uint32_t np) {
@@ -571,12 +572,16 @@ Sizes sizes_of(const Layer &L) {
   return z;
 }
 int few_rows_tiles(const Layer &L) { return L.N <= 16 ? 1 : L.N <= 32 ? 2 : L.N <= 64 ? 4 : 8; }
-// The layers k_fwd_rows takes: few rows (above, the product is no longer bound by reading W,
-// and packing it once is cheaper than turning it to nibbles beside every 16 rows), sums exact
-// in float32, a block's rows of W inside one buffer, loads on 4-byte addresses.
+// The layers k_fwd_rows takes: few rows; outputs enough that its blocks of 16 cover the chip and W
+// enough that one launch over it beats packing it first, both launches over the whole chip; sums
+// exact in float32, a block's rows of W inside one buffer, loads on 4-byte addresses.  Time of the
+// packed form over that of k_fwd_rows, N = 8 .. 128, W in float32: D = 64 .. 1024 0.3 - 0.7,
+// 2048 0.74 - 0.95, 3072 0.93 - 1.45; D = 4096 .. 16000 with C = 512 0.6 - 0.9, 1024 0.6 - 0.87,
+// 2048 0.88 - 1.3, 4096 0.97 - 1.7, 16384 and 25088 1.1 - 1.5.
 bool few_rows(const Layer &L, const void *W) {
   const int es = L.w_t == FQT_BF16 ? 2 : 4;
-  return L.kind == FQT_LINEAR && L.N <= FEW_ROWS && L.C < (int64_t(1) << 24) &&
+  return L.kind == FQT_LINEAR && L.N <= FEW_ROWS && L.D >= FEW_ROWS_MIN_D &&
+         L.C >= FEW_ROWS_MIN_C && L.C < (int64_t(1) << 24) &&
          L.C * 16 * es < (int64_t(1) << 31) - 4096 &&
          (es == 4 || (L.C % 2 == 0 && aligned(W, 4)));
 }
@@ -624,7 +629,7 @@ int launch_few_rows(const Layer &L, const void *X, const void *W, const float *g
   // Waves per block: 8, or 16 where the grid has few blocks and the contraction enough chunks
   // (with more row tiles 16 waves would leave too few registers for the loads in flight).
   const uint32_t blocks = uint32_t((L.D + 15) / 16);
-  const uint32_t nw = a.nch <= 4 ? 4 : blocks < 256 && a.nch >= 32 && nt <= 2 ? 16 : 8;
+  const uint32_t nw = blocks < 256 && a.nch >= 32 && nt <= 2 ? 16 : 8;
   const size_t lds = size_t(nw) * nt * 1024;
   dispatch_dtype(L.w_t, [&]<int WDT>() {
     if (nt == 1) hipLaunchKernelGGL((k_fwd_rows<1, WDT>), dim3(blocks), dim3(64 * nw), lds, s, a);

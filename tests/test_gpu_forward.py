@@ -49,6 +49,18 @@ CASES = [
     (_linear(128, 1026, 515), "f32", "bf16", 0),
     (_linear(20, 1027, 64), "f32", "bf16", 0),
     (_linear(9, 4994, 40), "f32", "bf16", 1),
+    # The same with W large enough for that form (and just not).
+    (_linear(1, 2048, 3072), "f32", "f32", 0),
+    (_linear(16, 2047, 3072), "f32", "f32", 0),
+    (_linear(16, 2050, 3071), "bf16", "f32", 0),
+    (_linear(16, 2049, 3073), "f32", "f32", 1),
+    (_linear(17, 4097, 3100), "bf16", "f32", 0),
+    (_linear(32, 2176, 4100), "f32", "bf16", 0),
+    (_linear(33, 4994, 3090), "f32", "bf16", 0),
+    (_linear(64, 2050, 3089), "bf16", "bf16", 1),
+    (_linear(65, 2051, 3075), "f32", "bf16", 0),
+    (_linear(128, 2057, 5003), "f32", "f32", 0),
+    (_linear(129, 2057, 3075), "f32", "f32", 0),
 ]
 
 
