@@ -1659,7 +1659,7 @@ void k_products(DxArgs dxa, DwArgs dwa, uint32_t nfront, uint32_t ndw, DgArgs dg
   __shared__ ProductsLds<WT> sm;
   const uint32_t b = blockIdx.x;
   if constexpr (!TR) dxa.ste = nullptr;
-  if constexpr (!TR && DWF == DWF_DIRECT) {     // (never reordered: fewer dW blocks than that)
+  if constexpr (!TR && DWF == DWF_DIRECT) {     // (never reordered)
     if (b < ndw) dw_part_body<B8, true>(dwa, b);
     else dx_form_body<FP4, B8, NB, WT>(dxa, b - ndw, sm.dx);
     return;
@@ -1968,11 +1968,20 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
   return last_launch_status();
 }
 
-// dW blocks past the kept channels follow the dX blocks when they are more than what the chip
-// holds at once (four per CU); fewer do not hold the dX blocks back, and writing their zeros
-// first is the better order (256 -> 256 on 8x8 maps, 432 of them: layer 29.4 us against 33.4;
-// 512 -> 512 on 7x7, 1728: 45.6 against 41.4).
-constexpr uint32_t PRODUCTS_RESIDENT = 1024;
+// Whether the dW blocks past the channels expected to be kept, which only write zeros, follow the dX
+// blocks of the products launch: in the in-block reduction, where they are many beside the dX tiles
+// expected to be live, the more the longer the live dW blocks' contractions run on beside them.
+// Else their zeros go out first, under those contractions.  Layer time with them last over that with
+// them first (194 layers, 3 x 3 and 1 x 1, b = 3, 4, 8): up to 64 words, 700 zeroing blocks and two per
+// live dX tile 0.80 - 0.96 (two layers of 256 channels 1.02 and 1.07), fewer per tile 0.99 - 1.08, fewer
+// blocks 0.96 - 1.10; 74 to 135 words, six per tile 0.87 - 0.98, five (also of 172 words) 1.00 - 1.02,
+// fewer 0.96 - 1.21; split-R partials 0.97 - 1.21.
+bool dw_zeros_last(const Layer &L, const fqt_quant_cfg &cfg, uint32_t zeroing) {
+  constexpr int64_t FEW_WORDS = 64, MIN_BLOCKS = 700;
+  const int64_t live = (L.N + cfg.bits - 1) / cfg.bits;
+  const int64_t tiles = (live * L.HW + 31) / 32 * ((L.C + 31) / 32);
+  return zeroing >= MIN_BLOCKS && zeroing >= (L.Wr <= FEW_WORDS ? 2 : 6) * tiles;
+}
 
 int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
                     const uint64_t *xsign, const int8_t *wsb, const int32_t *wlsum, void *dX,
@@ -2041,7 +2050,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
   const uint32_t keep = uint32_t(
       cfg.agp_mode == FQT_AGP_OFF ? stiles : ((L.D + cfg.bits - 1) / cfg.bits + 31) / 32);
   uint32_t nfront = ndw / stiles * keep;
-  if (ndw - nfront < PRODUCTS_RESIDENT || dwa.S == 1) nfront = ndw;
+  if (!kred || !dw_zeros_last(L, cfg, ndw - nfront)) nfront = ndw;
   const dim3 grid(ndw + dxa.nblocks + (train ? unsigned((L.D + 63) / 64) : 0u));
   const int nb = dx_batch(dxa);
   auto go_tr = [&]<bool B8, int DWF, int WT, bool TR>() {

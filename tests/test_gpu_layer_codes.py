@@ -65,9 +65,12 @@ CASES = [
     (_conv(300, 40, 2112, 16, 16, 3, 1, 1), 2, 0, "f32", 1.0),
     (_conv(90, 40, 20, 75, 75, 3, 2, 1), 1, 2, "bf16", 1.0),
     (_conv(90, 20, 70, 57, 57, 3, 1, 1), 8, 0, "f32", 1.0),
-    # More dW blocks of pruned slots than the chip holds (they follow the dX blocks): the in-block
-    # reduction and the split partials, and a set where every channel may be kept.
+    # Many dW blocks of pruned slots: after the dX blocks in the in-block reduction of up to 64 words
+    # and of more, before them where dX has more tiles and with split partials; a set where every
+    # channel may be kept.
     (_conv(40, 512, 300, 7, 7, 3, 1, 1), 8, 0, "f32", 1.5),
+    (_conv(100, 256, 600, 7, 7, 3, 1, 1), 8, 0, "f32", 1.5),
+    (_conv(100, 512, 300, 7, 7, 3, 1, 1), 8, 0, "f32", 1.5),
     (_conv(40, 64, 300, 28, 28, 3, 1, 1), 8, 0, "bf16", 1.5),
     (_conv(40, 512, 300, 7, 7, 3, 1, 1), 4, 2, "f32", 1.0),
 ]
