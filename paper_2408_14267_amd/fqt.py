@@ -128,6 +128,8 @@ def current_stream():
 def _stream(stream):
     if stream is None:
         return current_stream()
+    if type(stream) is int:
+        return stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

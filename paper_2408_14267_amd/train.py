@@ -33,7 +33,8 @@ class _BinaryLayerFn(torch.autograd.Function):
         desc = layer.desc(x.shape)
         y = torch.empty(layer.y_shape(x.shape), dtype=torch.float32, device=x.device)
         i = torch.empty(y.shape, dtype=torch.int32, device=x.device)
-        fqt.fqt_binary_forward(desc, x, w, gamma, y, i, layer.ws_forward(desc))
+        slot = x.get_device(), fqt.current_stream()
+        fqt.fqt_binary_forward(desc, x, w, gamma, y, i, layer.ws_forward(desc, slot), slot[1])
         ctx.save_for_backward(x, w, gamma, i)
         ctx.layer, ctx.desc = layer, desc
         return y
@@ -45,13 +46,14 @@ class _BinaryLayerFn(torch.autograd.Function):
         dx = torch.empty_like(x)
         dw = torch.empty_like(w)
         cfg = fqt.quant_cfg(layer.bits, layer.agp_mode, layer.seed, layer.step, layer.layer_id)
-        ws = layer.ws_backward(desc, cfg)
+        slot = x.get_device(), fqt.current_stream()
+        ws = layer.ws_backward(desc, cfg, slot)
         if torch.is_grad_enabled():
             # A graph of this backward is asked for (create_graph): its parts that torch can
             # differentiate stay torch operations.
             shape = (1, -1) + (1,) * (dy.dim() - 2)
             g = (dy * gamma.view(shape)).contiguous()      # gradient of the binary product
-            fqt.fqt_layer_backward(desc, cfg, x, w, g, dx, dw, ws)
+            fqt.fqt_layer_backward(desc, cfg, x, w, g, dx, dw, ws, slot[1])
             dx = dx * (x.abs() <= 1)                        # straight-through estimator
             dims = [0] + list(range(2, dy.dim()))
             dgamma = (dy * i.to(torch.float32)).sum(dim=dims)
@@ -59,7 +61,7 @@ class _BinaryLayerFn(torch.autograd.Function):
             # The same three steps inside the library's launches.
             dgamma = torch.empty_like(gamma)
             fqt.fqt_train_backward(desc, cfg, x, w, gamma, _aligned(i), _aligned(dy), dx, dw, dgamma,
-                                   ws)
+                                   ws, slot[1])
         layer.step += 1
         return dx, dw, dgamma, None
 
@@ -83,29 +85,33 @@ class _BinaryBase(nn.Module):
         self.step = 0
         self._ws = {}
 
-    def _workspace(self, key, make):
+    def _workspace(self, key, slot, make):
         # A workspace serves one call at a time, and calls on different streams may overlap.  A capture
         # takes one that is there (a new one's preparation would only be recorded); whoever replays the
-        # graph orders it with other calls, as for all that a graph writes.
-        by_stream = self._ws.setdefault(key, {})
-        stream = torch.cuda.current_device(), fqt.current_stream()
-        ws = by_stream.get(stream)
+        # graph orders it with other calls, as for all that a graph writes.  slot: device and stream.
+        slots = self._ws.get(key)
+        if slots is None:
+            slots = self._ws[key] = {}
+        if slot is None:
+            slot = torch.cuda.current_device(), fqt.current_stream()
+        ws = slots.get(slot)
         if ws is None:
-            if by_stream and torch.cuda.is_current_stream_capturing():
-                for (device, _), ws in by_stream.items():
-                    if device == stream[0]:
+            if slots and torch.cuda.is_current_stream_capturing():
+                for (device, _), ws in slots.items():
+                    if device == slot[0]:
                         return ws
-            ws = by_stream[stream] = make()
+            ws = slots[slot] = make()
         return ws
 
-    def ws_forward(self, desc):
-        return self._workspace(("f", desc.N, desc.H, desc.W), lambda: fqt.workspace(
+    def ws_forward(self, desc, slot=None):
+        return self._workspace(("f", desc.N, desc.H, desc.W), slot, lambda: fqt.workspace(
             desc, None, fqt.FQT_WS_FORWARD, device=self.weight.device))
 
-    def ws_backward(self, desc, cfg):
+    def ws_backward(self, desc, cfg, slot=None):
         # (the size depends on the code width and, through the expected kept groups, on the pruning)
         key = "b", desc.N, desc.H, desc.W, cfg.bits, cfg.agp_mode
-        return self._workspace(key, lambda: fqt.train_workspace(desc, cfg, device=self.weight.device))
+        return self._workspace(key, slot, lambda: fqt.train_workspace(
+            desc, cfg, device=self.weight.device))
 
     def forward(self, x):
         return _BinaryLayerFn.apply(x.contiguous(), self.weight, self.gamma, self)
