@@ -28,7 +28,6 @@ namespace {
 
 typedef int v3i __attribute__((ext_vector_type(3)));
 
-
 struct TapsArgs {
   const uint8_t *codes;          // PCQ codes in the formats above
   const int32_t *kept, *count;
