@@ -39,8 +39,8 @@ CASES = [
     (_conv(130, 64, 64, 2, 2, 3, 1, 1), "f32", "f32", 0),
     (_conv(130, 64, 64, 1, 1, 3, 1, 1), "f32", "f32", 0),
     (_linear(129, 65, 31), "f32", "f32", 0),
-    # Linear layers of few rows (weights read as they are): every tile count, last chunks of
-    # the contraction, odd and misaligned rows of W.
+    # Linear layers of few rows, W packed: last chunks of the contraction, odd and misaligned
+    # rows of W.
     (_linear(1, 1, 1), "f32", "f32", 0),
     (_linear(16, 127, 17), "f32", "f32", 1),
     (_linear(17, 129, 100), "bf16", "f32", 0),
@@ -49,7 +49,8 @@ CASES = [
     (_linear(128, 1026, 515), "f32", "bf16", 0),
     (_linear(20, 1027, 64), "f32", "bf16", 0),
     (_linear(9, 4994, 40), "f32", "bf16", 1),
-    # The same with W large enough for that form (and just not).
+    # The same with W large enough to be read as it is (and just not): every tile count, ragged
+    # rows and outputs, the last blocks and chunks.
     (_linear(1, 2048, 3072), "f32", "f32", 0),
     (_linear(16, 2047, 3072), "f32", "f32", 0),
     (_linear(16, 2050, 3071), "bf16", "f32", 0),

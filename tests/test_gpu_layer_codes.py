@@ -35,8 +35,9 @@ CASES = [
     (_conv(13, 65, 150, 64, 64, 3, 1, 1), 3, 2, "f32", 1.0),
     (_conv(800, 27, 80, 1, 64, 3, 1, 1), 5, 0, "f32", 1.0),
     (_conv(2, 23, 20, 224, 224, 3, 1, 1), 2, 2, "f32", 1.0),     # (too few channels for it)
-    # Linear layers of few rows and large W (dX from W itself, dW bound by its stores): one, two
-    # and four row tiles, ragged D and C, b = 8, the many-group selection.
+    # Linear layers of few rows (dW bound by its stores), dX from W itself where W has the channels
+    # and dW a launch of its own, else from packed signs: one, two and four row tiles, ragged D and
+    # C, b = 8, the many-group selection.
     (LayerShape("fc", "linear", 20, 2050, 1030), 3, 0, "f32", 1.5),
     (LayerShape("fc", "linear", 64, 4096, 2600), 2, 0, "bf16", 1.5),
     (LayerShape("fc", "linear", 128, 1026, 2050), 8, 0, "f32", 1.0),
@@ -62,7 +63,8 @@ CASES = [
     (LayerShape("fc", "linear", 513, 2050, 2051), 1, 2, "f32", 1.0),
     # Register-tile dX of convolutions: 25 taps, D above 2048, stride 2, one channel tile.
     (_conv(50, 40, 16, 60, 60, 5, 1, 2), 2, 2, "f32", 1.0),
-    (_conv(300, 40, 2112, 16, 16, 3, 1, 1), 2, 0, "f32", 1.0),
+    (_conv(300, 40, 2112, 16, 16, 3, 1, 1), 2, 0, "f32", 1.0),   # (just too few kept samples)
+    (_conv(330, 40, 2112, 16, 16, 3, 1, 1), 2, 0, "f32", 1.0),
     (_conv(90, 40, 20, 75, 75, 3, 2, 1), 1, 2, "bf16", 1.0),
     (_conv(90, 20, 70, 57, 57, 3, 1, 1), 8, 0, "f32", 1.0),
     # Many dW blocks of pruned slots: after the dX blocks in the in-block reduction of up to 64 words
@@ -146,9 +148,9 @@ def test_line_statistics(N, D, H, W, dtype):
 # channel tiles, D past the f16 line sums, b = 8's bias, a ragged last tile.
 TILES = [
     (LayerShape("c", "conv2d", 20, 40, 33, 48, 48, 7, 7, 1, 1, 3, 3), 2, 2),
-    (LayerShape("c", "conv2d", 60, 9, 70, 61, 45, 5, 3, 2, 3, 2, 0), 3, 0),
+    (LayerShape("c", "conv2d", 80, 9, 70, 61, 45, 5, 3, 2, 3, 2, 0), 3, 0),
     (LayerShape("c", "conv2d", 60, 9, 70, 45, 61, 8, 8, 3, 2, 0, 4), 8, 2),
-    (LayerShape("c", "conv2d", 90, 70, 20, 40, 52, 3, 3, 2, 2, 1, 1), 8, 0),
+    (LayerShape("c", "conv2d", 110, 70, 20, 40, 52, 3, 3, 2, 2, 1, 1), 8, 0),
     (LayerShape("c", "conv2d", 48, 200, 2100, 16, 16, 2, 2, 1, 1, 1, 1), 1, 2),
     (LayerShape("c", "conv2d", 96, 40, 65, 30, 30, 1, 1, 2, 2, 0, 0), 4, 2),
 ]
@@ -227,7 +229,8 @@ def test_padded_one_tap_on_one_pixel_maps(stride, pad, bits):
 
 @pytest.mark.parametrize("layer,bits,agp", [
     (_conv(13, 40, 70, 64, 64, 3, 1, 1), 2, 0),                  # dW by taps
-    (LayerShape("fc", "linear", 64, 4096, 1030), 4, 0),          # few rows
+    (LayerShape("fc", "linear", 64, 4096, 1030), 4, 0),          # few rows, dX from W itself
+    (LayerShape("fc", "linear", 20, 4100, 3080), 4, 0),          # the forward too
     (LayerShape("fc", "linear", 2050, 8196, 1030), 1, 2),        # W by row passes, nibble codes
 ])
 def test_captured_calls_replay(layer, bits, agp):

@@ -18,12 +18,16 @@ CASES = [
     (_conv(9, 16, 70, 8, 8, 3, 1, 1), 4, 0),          # 64-pixel tiles, merged keys
     (_conv(5, 7, 70, 9, 9, 3, 1, 1), 3, 0),           # odd maps: element by element
     (_conv(3, 20, 66, 36, 36, 3, 1, 1), 2, 0),        # per-plane statistics, a ragged last batch
-    (_conv(40, 3, 10, 40, 40, 3, 2, 1), 8, 2),        # several row tiles per block, AGP off
+    (_conv(40, 3, 10, 40, 40, 3, 2, 1), 8, 2),        # planes of a strided layer, AGP off
     (_conv(2, 70, 9, 362, 362, 3, 1, 1), 2, 0),       # register-tile dX: 16-byte and element stores
     (_conv(1, 1, 4, 1024, 513, 3, 1, 1), 2, 0),       # one channel tile per wave in dX
     (LayerShape("fc", "linear", 37, 300, 132), 4, 0),     # channel quads
     (LayerShape("fc", "linear", 70, 64, 77), 1, 0),       # odd rows
     (LayerShape("fc", "linear", 1500, 96, 1300), 2, 0),   # more than 1024 groups
+    (_conv(64, 8, 300, 14, 14, 3, 1, 1), 4, 0),       # several row tiles per block, whole quads
+    (_conv(64, 8, 300, 15, 15, 3, 1, 1), 4, 0),       # and element by element
+    (LayerShape("fc", "linear", 33, 5000, 1030), 4, 0),   # few rows, dX from W itself
+    (LayerShape("fc", "linear", 2050, 4100, 300), 2, 0),  # register-tile dX along the channels
 ]
 
 
