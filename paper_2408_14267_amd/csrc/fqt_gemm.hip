@@ -1619,24 +1619,29 @@ void k_mfma_dx(DxArgs a) {
 // waves and reduced in LDS (KRED).
 enum DwForm { DWF_PARTS = 0, DWF_DIRECT = 1, DWF_KRED = 2 };
 
-// Training: dgamma of 64 channels per block, the sum of their partial sums [parts][D] (in
-// float64: the partial sums are what rounds).
+// Training: dgamma of DG_CH channels per block, the sum of their partial sums [parts][D] (in
+// float64: the partial sums are what rounds), DG_ROWS rows side by side: these blocks are the launch's
+// last, and a long walk down the rows ends it late (3 -> 32 on 20 x 20, 1000 rows: layer 82 us with four
+// rows side by side, 76 with sixteen; 16 -> 64 on 16 x 16, 1024 rows 87.5 and 82.4).
 struct DgArgs {
   const float *part;
   float *out;
   uint32_t parts, D;
 };
-__device__ __forceinline__ void dgamma_body(const DgArgs &a, uint32_t bid, double (*sm)[64]) {
-  const uint32_t lane = threadIdx.x & 63, d = bid * 64 + lane;
-  const uint32_t wave = wave_id();
+constexpr uint32_t DG_CH = 16, DG_ROWS = DX_THREADS / DG_CH;    // channels per block, rows side by side
+__device__ __forceinline__ void dgamma_body(const DgArgs &a, uint32_t bid, double (*sm)[DG_CH]) {
+  const uint32_t c = threadIdx.x % DG_CH, row = threadIdx.x / DG_CH, d = bid * DG_CH + c;
   double s = 0.0;
   if (d < a.D) {
 #pragma unroll 8
-    for (uint32_t p = wave; p < a.parts; p += DX_WAVES) s += double(a.part[size_t(p) * a.D + d]);
+    for (uint32_t p = row; p < a.parts; p += DG_ROWS) s += double(a.part[size_t(p) * a.D + d]);
   }
-  sm[wave][lane] = s;
+  sm[row][c] = s;
   __syncthreads();
-  if (wave == 0 && d < a.D) a.out[d] = float(sm[0][lane] + sm[1][lane] + sm[2][lane] + sm[3][lane]);
+  if (row || d >= a.D) return;
+#pragma unroll
+  for (uint32_t r = 1; r < DG_ROWS; ++r) s += sm[r][c];
+  a.out[d] = float(s);
 }
 
 // Both products in one launch (the layer backward): blocks [0, nfront) are the dW blocks of the
@@ -1648,7 +1653,7 @@ template <int WT>
 union ProductsLds {
   DxLdsOf<WT> dx;
   DwRedLds dw;
-  double dg[DX_WAVES][64];
+  double dg[DG_ROWS][DG_CH];
 };
 // TR: a training step (the straight-through mask, dgamma's blocks); a template parameter because
 // the tests alone cost small layers a microsecond (256 -> 256 on 2x2 maps, N = 128: layer 23.3 us
@@ -2051,7 +2056,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
       cfg.agp_mode == FQT_AGP_OFF ? stiles : ((L.D + cfg.bits - 1) / cfg.bits + 31) / 32);
   uint32_t nfront = ndw / stiles * keep;
   if (!kred || !dw_zeros_last(L, cfg, ndw - nfront)) nfront = ndw;
-  const dim3 grid(ndw + dxa.nblocks + (train ? unsigned((L.D + 63) / 64) : 0u));
+  const dim3 grid(ndw + dxa.nblocks + (train ? unsigned((L.D + DG_CH - 1) / DG_CH) : 0u));
   const int nb = dx_batch(dxa);
   auto go_tr = [&]<bool B8, int DWF, int WT, bool TR>() {
     if constexpr (WT != 0) {
