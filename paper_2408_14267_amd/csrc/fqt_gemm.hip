@@ -1774,7 +1774,11 @@ uint32_t dw_part_blocks(const Layer &L, const DwArgs &a) {
 // more 1.1 - 1.5; 512 with 9, 18 and 36 steps 0.96, 0.77, 0.9; 784 0.67 - 0.82; 1568 and more
 // 0.44 - 0.94.  Where the dW blocks share the launch (fewer than DW_SPLIT_MIN words) they run at the
 // register tiles' occupancy too: 400 to 512 waves 1.1 - 1.25, 784 and 894 with byte codes 1.04 and 1.1,
-// with nibbles 0.77 - 0.92, 1568 0.7 - 0.94.  Linear layers: 512 waves 0.77 - 1.23, 1024 0.5 - 0.75.
+// with nibbles 0.77 - 0.92, 1568 0.7 - 0.94.
+// Linear layers: blocks of pruned samples count too, sixteen times as many in the split form and all
+// of its time at b = 8, so a wave of the capacity weighs a fifth of a live one.  Layer time in register
+// tiles over that in the split form (118 layers, C = 512 .. 8192, D = 64 .. 2048), by 4 live + capacity: up to
+// 2000 0.98 - 1.28, 2000 - 3000 0.96 - 1.14 (median 1.0), 3000 - 4000 0.88 - 1.01, more 0.76 - 1.03.
 uint32_t dx_form(const Layer &L, const fqt_quant_cfg &cfg) {
   const int64_t live =
       cfg.agp_mode == FQT_AGP_OFF ? L.N : std::max<int64_t>(1, (L.N + cfg.bits - 1) / cfg.bits);
@@ -1784,10 +1788,10 @@ uint32_t dx_form(const Layer &L, const fqt_quant_cfg &cfg) {
   // (padding puts output pixels where the one tap does not reach the map, and a stride may leave
   // only such pixels: those need the reach flags of the other forms)
   const bool lin = L.HW == 1 && L.kh * L.kw == 1 && L.ph == 0 && L.pw == 0;
-  const int64_t need = lin ? 640
-                       : L.Wr < DW_SPLIT_MIN ? (cfg.bits <= 2 ? 640 : 1024)
-                                             : std::min<int64_t>(640, 300 + 5 * steps);
-  if (waves < need) return DX_SPLIT;
+  const int64_t all = (L.N * L.HW + 32 * DXT_RT - 1) / (32 * DXT_RT) * ((ctiles + 1) / 2);
+  const int64_t need = L.Wr < DW_SPLIT_MIN ? (cfg.bits <= 2 ? 640 : 1024)
+                                           : std::min<int64_t>(640, 300 + 5 * steps);
+  if (lin ? 4 * waves + all < 3000 : waves < need) return DX_SPLIT;
   return lin ? DX_LIN : ctiles > 1 ? DX_CT2 : DX_CT1;
 }
 
