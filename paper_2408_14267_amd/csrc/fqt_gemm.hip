@@ -1984,11 +1984,14 @@ int launch_gemm_dx(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q,
 // them first (194 layers, 3 x 3 and 1 x 1, b = 3, 4, 8): up to 64 words, 700 zeroing blocks and two per
 // live dX tile 0.80 - 0.96 (two layers of 256 channels 1.02 and 1.07), fewer per tile 0.99 - 1.08, fewer
 // blocks 0.96 - 1.10; 74 to 135 words, six per tile 0.87 - 0.98, five (also of 172 words) 1.00 - 1.02,
-// fewer 0.96 - 1.21; split-R partials 0.97 - 1.21.
-bool dw_zeros_last(const Layer &L, const fqt_quant_cfg &cfg, uint32_t zeroing) {
+// fewer 0.96 - 1.21; split-R partials 0.97 - 1.21.  Beside register tiles, by live waves (50 layers):
+// one and a half per wave and more 0.91 - 1.01, 1.1 - 1.4 0.94 - 1.06, fewer 0.90 - 1.08.
+bool dw_zeros_last(const Layer &L, const fqt_quant_cfg &cfg, uint32_t zeroing, bool wide) {
   constexpr int64_t FEW_WORDS = 64, MIN_BLOCKS = 700;
-  const int64_t live = (L.N + cfg.bits - 1) / cfg.bits;
-  const int64_t tiles = (live * L.HW + 31) / 32 * ((L.C + 31) / 32);
+  const int64_t live = (L.N + cfg.bits - 1) / cfg.bits, ctiles = (L.C + 31) / 32;
+  if (wide)
+    return 2 * int64_t(zeroing) >= 3 * ((live * L.HW + 32 * DXT_RT - 1) / (32 * DXT_RT) * ((ctiles + 1) / 2));
+  const int64_t tiles = (live * L.HW + 31) / 32 * ctiles;
   return zeroing >= MIN_BLOCKS && zeroing >= (L.Wr <= FEW_WORDS ? 2 : 6) * tiles;
 }
 
@@ -2059,7 +2062,7 @@ int launch_products(const Layer &L, const fqt_quant_cfg &cfg, const fqt_qgrad &q
   const uint32_t keep = uint32_t(
       cfg.agp_mode == FQT_AGP_OFF ? stiles : ((L.D + cfg.bits - 1) / cfg.bits + 31) / 32);
   uint32_t nfront = ndw / stiles * keep;
-  if (!kred || !dw_zeros_last(L, cfg, ndw - nfront)) nfront = ndw;
+  if (!kred || !dw_zeros_last(L, cfg, ndw - nfront, dxa.wide != DX_SPLIT)) nfront = ndw;
   const dim3 grid(ndw + dxa.nblocks + (train ? unsigned((L.D + DG_CH - 1) / DG_CH) : 0u));
   const int nb = dx_batch(dxa);
   auto go_tr = [&]<bool B8, int DWF, int WT, bool TR>() {

@@ -75,6 +75,10 @@ CASES = [
     (_conv(100, 512, 300, 7, 7, 3, 1, 1), 8, 0, "f32", 1.5),
     (_conv(40, 64, 300, 28, 28, 3, 1, 1), 8, 0, "bf16", 1.5),
     (_conv(40, 512, 300, 7, 7, 3, 1, 1), 4, 2, "f32", 1.0),
+    (LayerShape("fc", "linear", 4800, 2050, 900), 3, 0, "f32", 1.5),     # after register tiles
+    # Register tiles of a linear layer with few live waves, and the split form just below the line.
+    (LayerShape("fc", "linear", 2050, 4100, 130), 8, 0, "bf16", 1.0),
+    (LayerShape("fc", "linear", 1540, 4100, 130), 6, 0, "f32", 1.0),
 ]
 
 
